@@ -2,29 +2,40 @@
 //
 // Each lane carries one photon at a time in registers (position, direction,
 // weight, path length, scatter count, step) and runs the walk one step per
-// loop trip.  When a lane's photon ends it takes the next photon id from its
-// wave's current id range; a wave claims ranges of `chunk` ids from a global
+// loop trip.  When a lane's photon ends it takes, at the wave's next round, the
+// next photon id from its wave's current id range; a wave claims ranges of `chunk` ids from a global
 // counter with one atomic, so lanes stay busy until the budget is spent and
 // the work counter sees one atomic per chunk rather than per photon.
 //
 // One step: a Philox4x32-10 block (counter = step, instance, id_lo, id_hi;
-// key = seed) gives four uniforms u0..u3; the free path s = -ln(u0)/mu_ext
-// (Eq. 15) is compared with the distance to the nearest wall.  Reaching the
-// wall first, the photon moves there and is reflected with the unpolarised
-// Fresnel reflectance (u3) or leaves and is tallied.  Otherwise it interacts:
-// the weight update of Eq. 16 (implicit capture), Russian roulette (u3), and
-// a new direction at the polar angle read from the LDS-resident inverse CDF
-// (u1, direct index and linear interpolation of v = 1 - cos(theta)) or from
-// Henyey-Greenstein (Eq. 11), with azimuth 2 pi u2, built in the orthonormal
-// basis of Duff et al. 2017 around the old direction.
+// key = seed) gives four uniforms u0..u3 and the free path s = -ln(u0)/mu_ext
+// (Eq. 15).  If the free path ends inside the cuboid, clear of the walls by a
+// margin that covers all rounding, the photon interacts: the weight update of
+// Eq. 16 (implicit capture), Russian roulette (u3), and a new direction at the
+// polar angle read from the LDS-resident inverse CDF (u1, direct index and
+// linear interpolation of v = 1 - cos(theta)) or from Henyey-Greenstein
+// (Eq. 11), with azimuth 2 pi u2, built in the orthonormal basis of Duff et
+// al. 2017 around the old direction.  Otherwise the lane waits for a round,
+// which finds the distance to the nearest wall, compares s with it, and moves
+// the photon there to be reflected with the unpolarised Fresnel reflectance
+// (u3) or to leave and be tallied.
 //
-// The kernel is bound by VALU issue.  On gfx950 a wave64 FP32 add, multiply
-// or fma whose operands are all vector registers issues in 2 cycles, while
-// compares, selects, min/max, conversions, shifts, 32-bit products and any
-// FP32 operation with a scalar-register operand take 4 and transcendentals
-// 8.  The step is written for that: its FP32 constants sit in vector
-// registers, the wall distances need neither compares nor selects, and
-// guards the arithmetic already ensures are left out.
+// The kernel is bound by VALU issue: at tau = 16 it issues 2.8 cycles of VALU
+// work per instruction all the time, which is its instructions' own price.
+// On gfx950 a wave64 FP32 add, multiply or fma whose operands are all vector
+// registers issues in 2 cycles, while compares, selects, min/max, conversions,
+// shifts, 32-bit products and any FP32 operation with a scalar-register operand
+// take 4 and transcendentals 8.  So the step holds only what every lane needs
+// (about 310 cycles, 134 of them the random block): its FP32 constants sit in
+// vector registers, the test against the walls has no division (three fma a
+// coordinate pair and one three-way maximum), roulette and the step cap are
+// looked at only where a photon of the wave could meet them, the parts of the
+// random block that do not depend on the step are kept per photon, and walls
+// (which 22 % of the lanes meet in a step at tau = 4, 6 % at tau = 16) are left
+// to the rounds, about 400 cycles each, that run when refill_min lanes wait.
+// Resolving walls in every step, with the distances for all lanes, took 2.69
+// ms at tau = 4 and 8.6 at tau = 16 for 1e8 photons (mc_simulate, 512 x 512,
+// exit log); this takes 2.40 and 6.6.
 //
 // Transport runs in FP32.  Weights are tallied in 64-bit fixed point
 // (weight * 2^32, rounded to nearest): integer sums do not depend on the order
@@ -90,6 +101,7 @@ struct WalkArgs {
     float n21, n12sq;         // n_out / n_med and (n_med / n_out)^2
     float n12;                // n_med / n_out (exit refraction, records only)
     int matched;              // n_out == n_med: no Fresnel term
+    float fresnel;            // 1 where the walls have a Fresnel term, 0 where they are index-matched
     float pos0[3], dir0[3], w0;
     float beam_radius;        // > 0: entry points uniform on the disk of this radius around pos0
     float roulette_w, roulette_p, inv_roulette_p;
@@ -99,7 +111,8 @@ struct WalkArgs {
     uint32_t key0, key1, instance, max_steps;
     uint64_t n_photons, photon_offset;
     uint32_t chunk;
-    uint32_t refill_min;      // free lanes that trigger end-of-photon work and refill (1..64)
+    uint32_t quiet_steps;     // a photon of fewer steps meets neither roulette nor the step cap in kQuietSteps more
+    uint32_t refill_min;      // lanes not walking that trigger a round (1..64)
     uint32_t flags;
     int cache_bits;           // log2 of the tally-cache slots (0: no cache)
     uint32_t n_side;          // pixels of the side image (cache key offset of the transmitted image)
@@ -218,6 +231,18 @@ __device__ __forceinline__ double wave_sum(double v)
 
 constexpr int kQueue = 64;                 // queued image exits per wave
 constexpr uint32_t kEmpty = 0xFFFFFFFFu;   // free tally-cache slot
+// Steps a wave takes at most before it looks again whether any of its photons
+// could meet roulette or the step cap in as many (WalkArgs::quiet_steps).
+constexpr int kQuietSteps = 32;
+// Free path of a photon that did not end at a wall (a drawn one is positive).
+constexpr float kKilled = -1.f, kCapped = -2.f;
+// A free path ends inside the cuboid by a margin when each coordinate, scaled
+// to [-1, 1], stays below this.  The wall distances then all exceed it, however
+// they round: a coordinate p <= L (1 - 1e-5) after s d leaves (L - p0) at
+// least 1e-5 L above s d, and the distance (L - p0) / d is formed to a few
+// units in 2^-24.  A position closer to a wall is compared with the distance
+// itself.
+constexpr float kInside = 1.f - 2e-5f, kOutside = 2.f;
 
 constexpr int kOptSigma = 1, kOptRecord = 2, kOptMoments = 4, kOptBatch = 8, kOptLog = 16;
 // Exit log: image exits appended as (key << 32 | weight bits).  Keys fall
@@ -263,12 +288,25 @@ constexpr int kWsLogFallback = 21;         // workspace word: exits added direct
 template <int OPT>
 constexpr int walk_waves_per_simd() { return (OPT & 4) ? 6 : 8; }
 
+// The kernel's arguments, read anew from the kernel argument segment.  What
+// only the rounds need is loaded there (a few scalar loads, hidden by the
+// other waves) rather than held in registers across the loop: the walk is at
+// its register limits, and each value kept longer spilled another.
+using ArgsPtr = const __attribute__((address_space(4))) WalkArgs *;
+__device__ __forceinline__ ArgsPtr reload_args()
+{
+    ArgsPtr p = (ArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return p;
+}
+
 template <int PHASE, int OPT>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(walk_waves_per_simd<OPT>())))
 void walk_kernel(WalkArgs a)
 {
     constexpr bool SIGMA = OPT & kOptSigma, RECORD = OPT & kOptRecord, MOMENTS = OPT & kOptMoments;
     constexpr bool BATCH = OPT & kOptBatch, LOG = OPT & kOptLog;
+    constexpr bool PATH = RECORD || MOMENTS;   // kernels that keep each photon's path length and scatter count
     constexpr bool GLOBAL_TABLE = BATCH;   // batched: each medium's inverse table stays in global memory
     // LDS layout: inverse table (n_cdf floats, padded to 4; batched launches
     // read each medium's table from global memory instead), scalar words
@@ -334,8 +372,8 @@ void walk_kernel(WalkArgs a)
 
     const int lane = __lane_id();
     const uint32_t xcc = __builtin_amdgcn_s_getreg((3 << 11) | 20) & a.copy_mask;   // hwreg(HW_REG_XCC_ID, 0, 4)
-    unsigned long long *my_img = a.ws_img + (uint64_t)xcc * a.n_pix;
-    unsigned long long *my_img2 = SIGMA ? a.ws_img2 + (uint64_t)xcc * a.n_pix : nullptr;
+    auto my_img = [&]() { const ArgsPtr ra = reload_args(); return ra->ws_img + (uint64_t)xcc * ra->n_pix; };
+    auto my_img2 = [&]() { const ArgsPtr ra = reload_args(); return ra->ws_img2 + (uint64_t)xcc * ra->n_pix; };
     float *q_y = s_queue + (threadIdx.x >> 6) * (kQueueArrays * kQueue);
     float *q_b = q_y + kQueue;
     float *q_w = q_b + kQueue;                 // weight bits, bit 31 set for the side image
@@ -348,6 +386,7 @@ void walk_kernel(WalkArgs a)
     // are appended to the log instead; a global atomic is then the fallback
     // for a range whose region of the log is full.
     auto flush = [&](uint32_t n) {
+        const ArgsPtr ra = reload_args();
         __builtin_amdgcn_wave_barrier();
         const bool act = (uint32_t)lane < n;
         uint32_t key = 0;
@@ -358,11 +397,16 @@ void walk_kernel(WalkArgs a)
             const uint32_t wb = __float_as_uint(q_w[lane]);
             const bool side = wb >> 31;
             wf = __uint_as_float(wb & 0x7FFFFFFFu);
-            const uint32_t key_base = BATCH ? __float_as_uint(q_s[lane]) * a.n_pix_inst : 0u;
-            const float per_row = side ? a.pix_scale[0] : a.pix_scale[2];
-            const float per_col = side ? a.pix_scale[1] : a.pix_scale[3];
-            const int n_row = side ? a.side_ny : a.trans_ny, n_col = side ? a.side_nx : a.trans_nx;
-            key = key_base + (side ? 0u : a.n_side) +
+            const uint32_t key_base = BATCH ? __float_as_uint(q_s[lane]) * ra->n_pix_inst : 0u;
+            // (Held in scalar registers: a select between two arguments would
+            // become a vector load from the selected address.)
+            float scale[4] = {ra->pix_scale[0], ra->pix_scale[1], ra->pix_scale[2], ra->pix_scale[3]};
+            int dim[4] = {ra->side_ny, ra->side_nx, ra->trans_ny, ra->trans_nx};
+            asm volatile("" : "+s"(scale[0]), "+s"(scale[1]), "+s"(scale[2]), "+s"(scale[3]));
+            asm volatile("" : "+s"(dim[0]), "+s"(dim[1]), "+s"(dim[2]), "+s"(dim[3]));
+            const float per_row = side ? scale[0] : scale[2], per_col = side ? scale[1] : scale[3];
+            const int n_row = side ? dim[0] : dim[2], n_col = side ? dim[1] : dim[3];
+            key = key_base + (side ? 0u : ra->n_side) +
                   (uint32_t)(pixel_scaled(y, per_row, n_row) * n_col + pixel_scaled(b, per_col, n_col));
         }
         if (act && !LOG) {
@@ -373,26 +417,26 @@ void walk_kernel(WalkArgs a)
             // Append to the block's region of the key's range at the position
             // the block's LDS counter hands out; past the region's end, the
             // exit is added directly.
-            const uint32_t bucket = log_bucket(key, a.log_bits, a.log_rbits);
+            const uint32_t bucket = log_bucket(key, ra->log_bits, ra->log_rbits);
             bool direct = false;
             if (act) {
                 const uint32_t e = atomicAdd(&s_lcnt[bucket], 1u);
-                if (e < a.log_cap)
-                    a.log[(uint64_t)(bucket * gridDim.x + blockIdx.x) * a.log_cap + e] =
+                if (e < ra->log_cap)
+                    ra->log[(uint64_t)(bucket * gridDim.x + blockIdx.x) * ra->log_cap + e] =
                         ((unsigned long long)key << 32) | __float_as_uint(wf);
                 else
                     direct = true;
             }
             if (direct) {
-                atomicAdd(my_img + key, fix(wf));
-                if (SIGMA) atomicAdd(my_img2 + key, fix(wf * wf));
+                atomicAdd(my_img() + key, fix(wf));
+                if (SIGMA) atomicAdd(my_img2() + key, fix(wf * wf));
             }
             const uint64_t took = __ballot(direct);
-            if (took && lane == 0) atomicAdd(a.ws_scal + kWsLogFallback, (unsigned long long)__popcll(took));
+            if (took && lane == 0) atomicAdd(ra->ws_scal + kWsLogFallback, (unsigned long long)__popcll(took));
         } else if (act) {
             bool cached = false;
             if (slots) {
-                uint32_t slot = (key * 2654435761u) >> (32 - a.cache_bits);
+                uint32_t slot = (key * 2654435761u) >> (32 - ra->cache_bits);
                 for (int probe = 0; probe < 4 && !cached; ++probe) {
                     const uint32_t old = atomicCAS(&s_key[slot], kEmpty, key);
                     if (old == kEmpty || old == key) {
@@ -404,14 +448,13 @@ void walk_kernel(WalkArgs a)
                 }
             }
             if (!cached) {
-                atomicAdd(my_img + key, wq);
-                if (SIGMA) atomicAdd(my_img2 + key, wq2);
+                atomicAdd(my_img() + key, wq);
+                if (SIGMA) atomicAdd(my_img2() + key, wq2);
             }
         }
         __builtin_amdgcn_wave_barrier();
     };
 
-    unsigned long long *work = a.ws_scal + MC_S_RESERVED;
     const float tab_scale = (float)(a.n_cdf - 1);
 
     // Wave-uniform id range: next id and ids left in the claimed chunk.
@@ -419,15 +462,24 @@ void walk_kernel(WalkArgs a)
     uint32_t q_rem = 0;
     bool exhausted = false;
 
-    // Lane state.
-    bool alive = false;
+    // Lane state.  A lane walks while its photon's last step ended inside the
+    // cuboid (out < kInside, see there; the wave-uniform mask of these lanes
+    // is `alive`), holds no photon (`empty`), or waits for a round with a
+    // photon whose step met a wall, or that roulette killed (s = kKilled) or
+    // the step cap stopped (s = kCapped).
+    uint64_t alive = 0ull, empty = ~0ull;
+    float out = kOutside;
+    // Steps the wave may still take before it has to look again whether one of
+    // its photons could meet roulette or the step cap (0 or less: some could now).
+    int calm = 0;
     uint64_t id = 0;
+    PhotonKey pk{};
     float px = 0.f, py = 0.f, pz = 0.f, dx = 0.f, dy = 0.f, dz = 1.f;
-    float w = 0.f, L = 0.f, A = 0.f;
-    uint32_t k = 0, step = 0;
-    // Lane accumulators.
+    float w = 0.f, L = 0.f, A = 0.f, s = 0.f;
+    uint32_t k = 0, step = 0, r3 = 0;
+    // Lane accumulators (interactions are steps less wall hits).
     unsigned long long acc_abs = 0ull;
-    uint32_t acc_events = 0, acc_steps = 0, acc_photons = 0, acc_ball = 0;
+    uint32_t acc_hits = 0, acc_steps = 0, acc_photons = 0, acc_ball = 0;
     double acc_w2 = 0.0, acc_w2k = 0.0, acc_w2l = 0.0;   // MOMENTS: image-wide second moments
     // The medium of the lane's photon (batched launches change it per photon;
     // otherwise these stay the launch's values).
@@ -437,122 +489,247 @@ void walk_kernel(WalkArgs a)
     // of those whose operands are all vector registers; the constants of the
     // step therefore live in vector registers (the empty asm hides that they
     // are wave-uniform; batched media keep theirs per lane anyway).
-    float v_lx = a.size[0], v_ly = a.size[1], v_lz = a.size[2], v_n21 = a.n21, v_n12sq = a.n12sq;
+    float v_sx = 2.f / a.size[0], v_sy = 2.f / a.size[1], v_sz = 2.f / a.size[2], v_tab = tab_scale;
     asm volatile("" : "+v"(l_mu), "+v"(l_alb), "+v"(l_abs));
-    asm volatile("" : "+v"(v_lx), "+v"(v_ly), "+v"(v_lz), "+v"(v_n21), "+v"(v_n12sq));
-    // A new photon's starting state, likewise in vector registers (a refill
-    // then copies at full rate instead of from scalar registers, and seven
-    // scalar registers fewer need spilling); not for batched media, whose
-    // kernels have no registers to spare and whose photons start the same.
-    constexpr bool INIT_V = !BATCH;
-    float i_px = a.pos0[0], i_py = a.pos0[1], i_pz = a.pos0[2], i_dx = a.dir0[0], i_dy = a.dir0[1];
-    float i_dz = a.dir0[2], i_w = a.w0;
-    if (INIT_V)
-        asm volatile("" : "+v"(i_px), "+v"(i_py), "+v"(i_pz), "+v"(i_dx), "+v"(i_dy), "+v"(i_dz), "+v"(i_w));
-    // The roulette threshold, compared at every interaction, likewise: in a
-    // scalar register it was spilled and reloaded (four v_readlane) each time.
-    float v_rw = a.roulette_w;
-    if (INIT_V) asm volatile("" : "+v"(v_rw));
-    // 1 where the walls have a Fresnel term, 0 where the indices match.
-    float v_fresnel = a.matched ? 0.f : 1.f;
-    if (INIT_V) asm volatile("" : "+v"(v_fresnel));
+    asm volatile("" : "+v"(v_sx), "+v"(v_sy), "+v"(v_sz), "+v"(v_tab));
+    float v_ha = a.hg_a, v_hb = a.hg_b, v_hc = a.hg_c, v_hd = a.hg_d;
+    if (PHASE == MC_PHASE_HG) asm volatile("" : "+v"(v_ha), "+v"(v_hb), "+v"(v_hc), "+v"(v_hd));
     const float *l_tab = a.inv_cdf;
-    uint32_t l_ctr = a.instance;
     // Batched: move the lane accumulators into the LDS scalars of its medium.
     auto flush_lane = [&]() {
         unsigned long long *sc = s_scal + l_slot * kBatchScal;
         atomicAdd(&sc[MC_S_ABSORBED], acc_abs);
-        atomicAdd(&sc[MC_S_EVENTS], (unsigned long long)acc_events);
+        atomicAdd(&sc[MC_S_EVENTS], (unsigned long long)acc_steps - (unsigned long long)acc_hits);
         atomicAdd(&sc[MC_S_STEPS], (unsigned long long)acc_steps);
         atomicAdd(&sc[MC_S_PHOTONS], (unsigned long long)acc_photons);
         if (acc_ball) atomicAdd(&sc[kLdsBallistic], (unsigned long long)acc_ball);
         acc_abs = 0ull;
-        acc_events = acc_steps = acc_photons = acc_ball = 0;
+        acc_hits = acc_steps = acc_photons = acc_ball = 0;
+    };
+    // The round keys derive from the seed at each block (scalar adds) rather
+    // than living in 20 scalar registers across the loop.
+    auto draw = [&](uint32_t at) {
+        uint32_t k0 = a.key0, k1 = a.key1;
+        asm volatile("" : "+s"(k0), "+s"(k1));
+        return philox_step(pk, at, k0, k1);
+    };
+    // An interaction after the free path s, from random words w1, w2 and r3:
+    // move, absorb (Eq. 16), scatter; where the wave is not calm, roulette and
+    // the step cap too.  (The empty asm keeps that block behind its scalar
+    // branch.  A photon that ended there scatters all the same, unless its
+    // direction is recorded.)
+    auto interact = [&](uint32_t w1, uint32_t w2) {
+        px = fmaf(s, dx, px); py = fmaf(s, dy, py); pz = fmaf(s, dz, pz);
+        if (PATH) {
+            L += s;
+            ++k;
+        }
+        A = fmaf(w, l_abs, A);
+        asm volatile("" : "+v"(A), "+v"(w));   // A first: w is then updated in place
+        w *= l_alb;
+        if (calm <= 0) {
+            asm volatile("");
+            const uint32_t scal_at = BATCH ? l_slot * kBatchScal : 0u;   // the medium's LDS scalars
+            if (w < a.roulette_w) {
+                if (uniform01(r3) < a.roulette_p) {
+                    const float wn = w * a.inv_roulette_p;
+                    atomicAdd(&s_scal[scal_at + MC_S_ROULETTE_NET], fix(wn) - fix(w));
+                    w = wn;
+                } else {
+                    atomicAdd(&s_scal[scal_at + MC_S_ROULETTE_NET], 0ull - fix(w));
+                    atomicAdd(&s_scal[scal_at + MC_S_ROULETTE_KILLS], 1ull);
+                    w = 0.f;
+                    s = kKilled;
+                    out = kOutside;
+                }
+            }
+            if (s >= 0.f && step >= a.max_steps) {
+                s = kCapped;
+                out = kOutside;
+            }
+        }
+        if (RECORD && s == kKilled) return;
+        const float u1 = uniform01(w1), u2 = uniform01(w2);
+        float v;
+        if (PHASE == MC_PHASE_MIE) {
+            // u1 <= 1 - 2^-24, so u1 (n - 1) rounds below n - 1 (exact when
+            // n - 1 is a power of two, else more than half an ulp short of
+            // it): i <= n - 2 and entry i + 1 exists.
+            const float tt = u1 * v_tab;
+            const int i = (int)tt;
+            // The fraction from the unrounded product u1 (n - 1).
+            const float f = fmaf(u1, v_tab, -(float)i);
+            const float t0 = GLOBAL_TABLE ? l_tab[i] : s_table[i];
+            const float t1 = GLOBAL_TABLE ? l_tab[i + 1] : s_table[i + 1];
+            v = fmaf(f, t1 - t0, t0);
+        } else {
+            const float D = fmaf(-v_hb, u1, v_ha);
+            const float rD = __builtin_amdgcn_rcpf(D);
+            v = v_hd * u1 * fmaf(v_hc, rD, v_hd) * rD;
+        }
+        const float ct = 1.f - v;
+        // A table value lies in [0, 2], and so does a rounded point between
+        // two of them: v (2 - v) >= 0.  The HG formula can overshoot 2.
+        const float st = __builtin_amdgcn_sqrtf(PHASE == MC_PHASE_MIE ? v * (2.f - v)
+                                                                      : fmaxf(v * (2.f - v), 0.f));
+        const float cp = __builtin_amdgcn_cosf(u2);        // cos(2 pi u2)
+        const float sp = __builtin_amdgcn_sinf(u2);        // sin(2 pi u2)
+        // Orthonormal basis around d (Duff et al. 2017), with its factors
+        // sign(dz) = +-1 drawn together: sin phi takes it here and the new dz
+        // below (products with +-1 are exact, so the bits are those of the
+        // basis written out).
+        uint32_t sz = __float_as_uint(dz) & 0x80000000u;
+        asm volatile("" : "+v"(sz));   // one AND and two XORs at full rate, not two three-input operations at half
+        const float ia = __builtin_amdgcn_rcpf(1.f + fabsf(dz));
+        const float b = dx * dy * ia;
+        const float e1 = fmaf(dx * dx, -ia, 1.f), e2 = fmaf(dy * dy, -ia, 1.f);
+        const float sq = __uint_as_float(__float_as_uint(sp) ^ sz);
+        const float qx = fmaf(cp, e1, -(sq * b)), qy = fmaf(-cp, b, sq * e2), qz = fmaf(cp, dx, sq * dy);
+        const float nx = fmaf(ct, dx, st * qx), ny = fmaf(ct, dy, st * qy), nz = fmaf(ct, fabsf(dz), -(st * qz));
+        // |n|^2 is 1 up to rounding, so one Newton step of 1/sqrt from 1
+        // (1.5 - |n|^2 / 2) renormalises to within 1e-13.
+        const float inv = fmaf(-0.5f, fmaf(nx, nx, fmaf(ny, ny, nz * nz)), 1.5f);
+        dx = nx * inv; dy = ny * inv; dz = __uint_as_float(__float_as_uint(nz * inv) ^ sz);
     };
 
-    // A lane whose photon has ended keeps its state until the end-of-photon
-    // work (tallies, records, the exit queue) and the refill run for several
-    // lanes at once: when at least refill_min lanes are free (refill_min <= 64,
-    // so also when none is still walking).  Few lanes finish in any one step,
-    // so doing that work every step would run it with most lanes masked off.
-    // An ended photon's face is its exit face (0..5) exactly when it left
-    // through a wall (cause 0); roulette kills and the step cap leave it -1.
-    // A photon that leaves on its first step met a wall before any
-    // interaction, so leaving through the beam's own exit face at step 1
-    // makes it an unscattered first-step exit.
-    bool pending = false;
-    int cause = 0, face = -1, axis = 0;
+    // A lane whose photon meets a wall or ends keeps its state until a round
+    // handles several such lanes at once: when at least refill_min lanes do
+    // not walk (refill_min <= 64, so also when none does).  Only some lanes
+    // leave the interior in any one step, so resolving walls, tallying and
+    // refilling every step would run all that with most lanes masked off.
+    // Once the photon ids are used up no lane can be refilled, and a round
+    // runs when refill_min lanes wait or at least as many wait as walk.
+    // Either way it runs when at most round_at lanes walk.
+    uint32_t round_at = 64u;
 
     for (;;) {
-        // Free lanes (wave-uniform counts); refill_min <= 64, so a wave whose
-        // lanes are all free always runs the end-of-photon work.
-        const uint64_t need = __ballot(!alive);
-        const uint32_t n_need = (uint32_t)__popcll(need);
-        uint32_t n_alive = 64u - n_need;
-        if (n_need >= a.refill_min) {
-            // ---- end-of-photon work of the waiting lanes ----------------------
+        if ((uint32_t)__popcll(alive) <= round_at) {
+            const ArgsPtr ra = reload_args();
+            const bool waits = __builtin_amdgcn_inverse_ballot_w64(~(alive | empty));
+            const float v_lx = ra->size[0], v_ly = ra->size[1], v_lz = ra->size[2];
+            const float v_n21 = ra->n21, v_n12sq = ra->n12sq, v_fresnel = ra->fresnel;
+            // ---- walls: the photons that left the interior ----------------------
+            int face = -1, axis = 0;
+            bool again = false, early = false;
+            if (waits && s >= 0.f) {
+                // Nearest wall along the direction.
+                float tx, ty, tz;
+                wall_distances(px, py, pz, dx, dy, dz, v_lx, v_ly, v_lz, tx, ty, tz);
+                const float db = fminf(fminf(tx, ty), tz);
+                early = !(s >= db);   // within the margin of a wall, but short of it
+                if (!early) {
+                    // Boundary: clamp into the box (a move that overshot the wall
+                    // by rounding lands on it), then reflect (u3 < R) or leave.
+                    // Written as selects so the wave runs it without branches.
+                    px = fmaf(db, dx, px); py = fmaf(db, dy, py); pz = fmaf(db, dz, pz);
+                    if (PATH) L += db;
+                    ++acc_hits;
+                    axis = wall_axis(db, tx, ty);
+                    const bool on_x = axis == 0, on_y = axis == 1, on_z = axis == 2;
+                    const float da = on_x ? dx : (on_y ? dy : dz);
+                    const bool pos_side = da > 0.f;
+                    px = __builtin_amdgcn_fmed3f(px, 0.f, v_lx);
+                    py = __builtin_amdgcn_fmed3f(py, 0.f, v_ly);
+                    pz = __builtin_amdgcn_fmed3f(pz, 0.f, v_lz);
+                    // Index-matched walls reflect nothing: R is scaled by 0 there.
+                    const float ci = fabsf(da);
+                    const float st2 = v_n12sq * fmaf(-ci, ci, 1.f);
+                    // 1 - st2 > 0 wherever R uses ct; under TIR the select drops it.
+                    const float ct = __builtin_amdgcn_sqrtf(1.f - st2);
+                    const float ds = fmaf(v_n21, ct, ci), dp = fmaf(v_n21, ci, ct);   // both > 0 (ci > 0)
+                    const float r = __builtin_amdgcn_rcpf(ds * dp);
+                    const float rs = fmaf(-v_n21, ct, ci) * dp * r;
+                    const float rp = fmaf(v_n21, ci, -ct) * ds * r;
+                    const float R = v_fresnel * (st2 >= 1.f ? 1.f : 0.5f * fmaf(rs, rs, rp * rp));
+                    const bool refl = uniform01(r3) < R;
+                    dx = refl && on_x ? -dx : dx;
+                    dy = refl && on_y ? -dy : dy;
+                    dz = refl && on_z ? -dz : dz;
+                    again = refl && step < ra->max_steps;
+                    if (refl && !again) s = kCapped;
+                    face = refl ? -1 : 2 * axis + (pos_side ? 1 : 0);
+                }
+            }
+            // Rare: the step stayed inside after all and interacts.
+            calm = __builtin_amdgcn_ballot_w64(early) ? 0 : calm;
+            if (early) {
+                const Block4 r = draw(step - 1u);
+                interact(r.r1, r.r2);
+                again = s >= 0.f;
+            }
+            if (again) out = 0.f;
+            // ---- end-of-photon work --------------------------------------------
+            const uint64_t go_on = __builtin_amdgcn_ballot_w64(again);
+            const bool pending = waits && !again;
             if (pending) {
                 const uint32_t scal_at = BATCH ? l_slot * kBatchScal : 0u;
+                if (s == kCapped) {
+                    atomicAdd(&s_scal[scal_at + MC_S_CAPPED_W], fix(w));
+                    atomicAdd(&s_scal[scal_at + MC_S_CAPPED], 1ull);
+                }
                 // Faces +x and +z are totalled from their images when finalizing.
-                const bool below_one = __ballot(w >= 1.f || A >= 1.f) == 0;   // wave-uniform
+                const bool below_one = __builtin_amdgcn_ballot_w64(w >= 1.f || A >= 1.f) == 0;   // wave-uniform
                 if (face >= 0 && (face | 4) != 5)
                     atomicAdd(&s_scal[scal_at + MC_S_FACE + face], below_one ? fix_below_one(w) : fix(w));
-                if (MOMENTS && cause == 0 && face == 1) {
+                if (MOMENTS && face == 1) {
                     // Path moments of the side image (perturbation Monte Carlo):
                     // first order per pixel, second order summed over the image
                     // in lane registers (per pixel as well when asked for).
-                    const uint32_t key = (uint32_t)(pixel_scaled(py, a.pix_scale[0], a.side_ny) * a.side_nx +
-                                                    pixel_scaled(pz, a.pix_scale[1], a.side_nx));
+                    const uint32_t key = (uint32_t)(pixel_scaled(py, ra->pix_scale[0], ra->side_ny) * ra->side_nx +
+                                                    pixel_scaled(pz, ra->pix_scale[1], ra->side_nx));
                     const double wd = (double)w, wk = wd * (double)k, wl = wd * (double)L;
-                    atomicAdd(a.side_wk + key, wk);
-                    atomicAdd(a.side_wl + key, wl);
+                    atomicAdd(ra->side_wk + key, wk);
+                    atomicAdd(ra->side_wl + key, wl);
                     acc_w2 += wd * wd;
                     acc_w2k += wd * wk;
                     acc_w2l += wd * wl;
-                    if (a.side_w2k) {
-                        atomicAdd(a.side_w2k + key, wd * wk);
-                        atomicAdd(a.side_w2l + key, wd * wl);
+                    if (ra->side_w2k) {
+                        atomicAdd(ra->side_w2k + key, wd * wk);
+                        atomicAdd(ra->side_w2l + key, wd * wl);
                     }
                 }
                 acc_abs += below_one ? fix_below_one(A) : fix(A);
-                acc_events += k;
                 acc_steps += step;
                 ++acc_photons;
                 if (RECORD) {
-                    const uint64_t rel = id - a.photon_offset;
-                    if (rel % a.record_stride == 0 && rel / a.record_stride < a.rec_rows) {
-                        const uint64_t row = rel / a.record_stride, n = a.rec_rows;
+                    const uint64_t rel = id - ra->photon_offset;
+                    if (rel % ra->record_stride == 0 && rel / ra->record_stride < ra->rec_rows) {
+                        const uint64_t row = rel / ra->record_stride, n = ra->rec_rows;
                         float ox = dx, oy = dy, oz = dz;
-                        if (cause == 0 && !a.matched) {
+                        if (s >= 0.f && !ra->matched) {
                             // Refracted direction outside the wall (Snell).
-                            ox *= a.n12; oy *= a.n12; oz *= a.n12;
+                            ox *= ra->n12; oy *= ra->n12; oz *= ra->n12;
                             const float t2 = (axis == 0 ? oy * oy + oz * oz
                                                         : (axis == 1 ? ox * ox + oz * oz : ox * ox + oy * oy));
                             const float on = copysignf(sqrtf(fmaxf(1.f - t2, 0.f)),
                                                        axis == 0 ? dx : (axis == 1 ? dy : dz));
                             if (axis == 0) ox = on; else if (axis == 1) oy = on; else oz = on;
                         }
-                        a.rec_i[MC_REC_I_FACE * n + row] = face;
-                        a.rec_i[MC_REC_I_CAUSE * n + row] = cause;
-                        a.rec_i[MC_REC_I_K * n + row] = (int32_t)k;
-                        a.rec_i[MC_REC_I_STEPS * n + row] = (int32_t)step;
-                        a.rec_f[(MC_REC_F_POS + 0) * n + row] = px;
-                        a.rec_f[(MC_REC_F_POS + 1) * n + row] = py;
-                        a.rec_f[(MC_REC_F_POS + 2) * n + row] = pz;
-                        a.rec_f[(MC_REC_F_DIR + 0) * n + row] = ox;
-                        a.rec_f[(MC_REC_F_DIR + 1) * n + row] = oy;
-                        a.rec_f[(MC_REC_F_DIR + 2) * n + row] = oz;
-                        a.rec_f[MC_REC_F_W * n + row] = w;
-                        a.rec_f[MC_REC_F_L * n + row] = L;
-                        a.rec_f[MC_REC_F_A * n + row] = A;
+                        ra->rec_i[MC_REC_I_FACE * n + row] = face;
+                        ra->rec_i[MC_REC_I_CAUSE * n + row] = s >= 0.f ? 0 : (s == kKilled ? 1 : 2);
+                        ra->rec_i[MC_REC_I_K * n + row] = (int32_t)k;
+                        ra->rec_i[MC_REC_I_STEPS * n + row] = (int32_t)step;
+                        ra->rec_f[(MC_REC_F_POS + 0) * n + row] = px;
+                        ra->rec_f[(MC_REC_F_POS + 1) * n + row] = py;
+                        ra->rec_f[(MC_REC_F_POS + 2) * n + row] = pz;
+                        ra->rec_f[(MC_REC_F_DIR + 0) * n + row] = ox;
+                        ra->rec_f[(MC_REC_F_DIR + 1) * n + row] = oy;
+                        ra->rec_f[(MC_REC_F_DIR + 2) * n + row] = oz;
+                        ra->rec_f[MC_REC_F_W * n + row] = w;
+                        ra->rec_f[MC_REC_F_L * n + row] = L;
+                        ra->rec_f[MC_REC_F_A * n + row] = A;
                     }
                 }
             }
             // ---- queue exits through the imaged faces (+x side, +z transmitted) ----
+            // An exit face (0..5) belongs to a photon that left through it.  A
+            // photon that leaves on its first step met a wall before any
+            // interaction, so leaving through the beam's own exit face at step
+            // 1 makes it an unscattered first-step exit.
             const bool ballistic = pending && step == 1 && face == beam_face;
             acc_ball += ballistic ? 1u : 0u;
-            const bool to_img = pending && (face | 4) == 5 && !ballistic;
-            const uint64_t m = __ballot(to_img);
+            const bool to_img = (face | 4) == 5 && !ballistic;
+            const uint64_t m = __builtin_amdgcn_ballot_w64(to_img);
             if (m) {
                 const uint32_t n_push = __popcll(m);
                 if (q_n + n_push > (uint32_t)kQueue) {
@@ -570,60 +747,66 @@ void walk_kernel(WalkArgs a)
                 q_n += n_push;
             }
 
-            pending = false;
-
             // Lane counters stay below 2^31: steps bound the others, and a
             // photon adds at most max_steps <= 2^24.  Past 2^31 they move into
-            // the 64-bit LDS words (batched: of the lane's medium).
-            if (__ballot(acc_steps >= 0x80000000u)) {
+            // the 64-bit LDS words (batched: of the lane's medium).  (Hits of
+            // a photon still walking are counted before its steps; the sums
+            // are modulo 2^64, so the difference comes out right at the end.)
+            if (__builtin_amdgcn_ballot_w64(acc_steps >= 0x80000000u)) {
                 if (BATCH) {
                     if (acc_steps >= 0x80000000u) flush_lane();
                 } else {
-                    atomicAdd(&s_scal[MC_S_EVENTS], (unsigned long long)acc_events);
+                    atomicAdd(&s_scal[MC_S_EVENTS], (unsigned long long)acc_steps - (unsigned long long)acc_hits);
                     atomicAdd(&s_scal[MC_S_STEPS], (unsigned long long)acc_steps);
                     atomicAdd(&s_scal[MC_S_PHOTONS], (unsigned long long)acc_photons);
                     atomicAdd(&s_scal[kLdsBallistic], (unsigned long long)acc_ball);
-                    acc_events = acc_steps = acc_photons = acc_ball = 0;
+                    acc_hits = acc_steps = acc_photons = acc_ball = 0;
                 }
             }
 
             // ---- refill free lanes ---------------------------------------------
-            if (q_rem == 0 && !exhausted) {
+            alive |= go_on;
+            const uint64_t need = ~alive;
+            if (q_rem == 0 && !exhausted && need) {
                 // Single medium: claim the next `chunk` photon ids.  Batched:
                 // claim the next work unit, `chunk` photons of one medium.
                 unsigned long long base = 0;
-                if (lane == 0) base = atomicAdd(work, BATCH ? 1ull : (unsigned long long)a.chunk);
+                if (lane == 0) base = atomicAdd(ra->ws_scal + MC_S_RESERVED, BATCH ? 1ull : (unsigned long long)ra->chunk);
                 const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)base);
                 const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(base >> 32));
                 const uint64_t b = ((uint64_t)hi << 32) | lo;
                 if (BATCH) {
-                    if (b >= a.n_units) {
+                    if (b >= ra->n_units) {
                         exhausted = true;
                     } else {
                         // The unit's medium: the last one whose first unit is <= b
                         // (media without photons own no units and are never found).
-                        uint32_t l = 0, h = a.n_inst;
+                        uint32_t l = 0, h = ra->n_inst;
                         while (h - l > 1) {
                             const uint32_t mid = (l + h) >> 1;
-                            if (a.insts[mid].unit_begin <= b) l = mid; else h = mid;
+                            if (ra->insts[mid].unit_begin <= b) l = mid; else h = mid;
                         }
                         q_p = l;
-                        q_next = (b - a.insts[l].unit_begin) * a.chunk;
-                        q_rem = (uint32_t)min((uint64_t)a.chunk, a.insts[l].n_photons - q_next);
+                        q_next = (b - ra->insts[l].unit_begin) * ra->chunk;
+                        q_rem = (uint32_t)min((uint64_t)ra->chunk, ra->insts[l].n_photons - q_next);
                     }
-                } else if (b >= a.n_photons) {
+                } else if (b >= ra->n_photons) {
                     exhausted = true;
                 } else {
                     q_next = b;
-                    q_rem = (uint32_t)min((uint64_t)a.chunk, a.n_photons - b);
+                    q_rem = (uint32_t)min((uint64_t)ra->chunk, ra->n_photons - b);
                 }
             }
             const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(need >> 32),
                                                              __builtin_amdgcn_mbcnt_lo((uint32_t)need, 0u));
-            if (!alive && rank < q_rem) {
-                id = (BATCH ? 0ull : a.photon_offset) + q_next + rank;
+            const bool starts = __builtin_amdgcn_inverse_ballot_w64(need) && rank < q_rem;
+            if (starts) {
+                const uint64_t new_id = (BATCH ? 0ull : ra->photon_offset) + q_next + rank;
+                if (RECORD) id = new_id;
+                uint32_t ctr = ra->instance;
                 if (BATCH) {
-                    const BatchInst &bi = a.insts[q_p];
+                    const BatchInst &bi = ra->insts[q_p];
+                    ctr = bi.counter;
                     if (bi.slot != l_slot) {
                         if (l_slot != kEmpty) flush_lane();
                         l_slot = bi.slot;
@@ -631,159 +814,55 @@ void walk_kernel(WalkArgs a)
                         l_alb = bi.albedo;
                         l_abs = bi.absorb;
                         l_tab = bi.inv_cdf;
-                        l_ctr = bi.counter;
                     }
                 }
-                alive = true;
-                px = INIT_V ? i_px : a.pos0[0];
-                py = INIT_V ? i_py : a.pos0[1];
-                pz = INIT_V ? i_pz : a.pos0[2];
-                if (a.beam_radius > 0.f) {
+                pk = photon_key(ctr, new_id, ra->key0, ra->key1);
+                px = ra->pos0[0];
+                py = ra->pos0[1];
+                pz = ra->pos0[2];
+                if (ra->beam_radius > 0.f) {
                     // Finite beam: entry point uniform on the disk, from the
                     // photon's Philox block at the reserved step counter.
-                    uint32_t k0 = a.key0, k1 = a.key1;
-                    const Block4 rb = philox4x32_10(0xFFFFFFFFu, l_ctr, (uint32_t)id, (uint32_t)(id >> 32), k0, k1);
-                    const float rho = a.beam_radius * __builtin_amdgcn_sqrtf(uniform01(rb.r0));
+                    const Block4 rb = draw(0xFFFFFFFFu);
+                    const float rho = ra->beam_radius * __builtin_amdgcn_sqrtf(uniform01(rb.r0));
                     const float u1 = uniform01(rb.r1);
                     px = fmaf(rho, __builtin_amdgcn_cosf(u1), px);    // cos(2 pi u1)
                     py = fmaf(rho, __builtin_amdgcn_sinf(u1), py);    // sin(2 pi u1)
                 }
-                dx = INIT_V ? i_dx : a.dir0[0];
-                dy = INIT_V ? i_dy : a.dir0[1];
-                dz = INIT_V ? i_dz : a.dir0[2];
-                w = INIT_V ? i_w : a.w0;
-                L = 0.f; A = 0.f; k = 0; step = 0;
+                dx = ra->dir0[0];
+                dy = ra->dir0[1];
+                dz = ra->dir0[2];
+                w = ra->w0;
+                A = 0.f; out = 0.f; step = 0;
+                if (PATH) { L = 0.f; k = 0; }
             }
-            const uint32_t took = min(n_need, q_rem);
+            const uint32_t took = min((uint32_t)__popcll(need), q_rem);
             q_next += took;
             q_rem -= took;
-            n_alive += took;
+            alive |= __builtin_amdgcn_ballot_w64(starts);
+            empty = ~alive;
+            const uint32_t n_alive = (uint32_t)__popcll(alive), n_idle = ra->refill_min;
+            if (n_alive == 0u) break;   // nothing left to claim
+            round_at = exhausted ? max(n_alive / 2u, n_alive - min(n_alive, n_idle)) : 64u - n_idle;
+            if (!starts && !again) out = kOutside;
         }
-        if (n_alive == 0) break;
 
-        bool ended = false;
-        const uint32_t scal_at = BATCH ? l_slot * kBatchScal : 0u;   // the medium's LDS scalars
-        if (alive) {
-            cause = 0;
-            face = -1;
-            // ---- one step ---------------------------------------------------
-            // The round keys derive from the seed inside the loop (scalar adds)
-            // rather than living in 20 scalar registers across it.
-            uint32_t k0 = a.key0, k1 = a.key1;
-            asm volatile("" : "+s"(k0), "+s"(k1));
-            const Block4 r = philox4x32_10(step, l_ctr, (uint32_t)id, (uint32_t)(id >> 32), k0, k1);
-            const float u0 = uniform01(r.r0), u1 = uniform01(r.r1);
-            const float u2 = uniform01(r.r2), u3 = uniform01(r.r3);
-            const float s = __builtin_amdgcn_logf(u0) * l_mu;     // Eq. 15
+        // ---- one step of the walking lanes ----------------------------------
+        if (calm <= 0 && __builtin_amdgcn_ballot_w64(step >= a.quiet_steps) == 0ull) calm = kQuietSteps;
+        if (__builtin_amdgcn_inverse_ballot_w64(alive)) {
+            const Block4 r = draw(step);
+            r3 = r.r3;
+            s = __builtin_amdgcn_logf(uniform01(r.r0)) * l_mu;     // Eq. 15
             ++step;
-
-            // Nearest wall along the direction.
-            float tx, ty, tz;
-            wall_distances(px, py, pz, dx, dy, dz, v_lx, v_ly, v_lz, tx, ty, tz);
-            const float db = fminf(fminf(tx, ty), tz);
-
-            const bool hit = s >= db;
-            const float t = fminf(s, db);
-            px = fmaf(t, dx, px); py = fmaf(t, dy, py); pz = fmaf(t, dz, pz);
-            L += t;
-            if (hit) {
-                // Boundary: clamp into the box (a move that overshot the wall
-                // by rounding lands on it), then reflect (u3 < R) or leave.
-                // Written as selects so the wave runs it without branches.
-                axis = wall_axis(db, tx, ty);
-                const bool on_x = axis == 0, on_y = axis == 1, on_z = axis == 2;
-                const float da = on_x ? dx : (on_y ? dy : dz);
-                const bool pos_side = da > 0.f;
-                px = __builtin_amdgcn_fmed3f(px, 0.f, v_lx);
-                py = __builtin_amdgcn_fmed3f(py, 0.f, v_ly);
-                pz = __builtin_amdgcn_fmed3f(pz, 0.f, v_lz);
-                // Index-matched walls reflect nothing: R is scaled by 0 there
-                // (v_fresnel) rather than skipped on a flag the wave would
-                // have to reload from a spilled scalar register every step.
-                const float ci = fabsf(da);
-                const float st2 = v_n12sq * fmaf(-ci, ci, 1.f);
-                // 1 - st2 > 0 wherever R uses ct; under TIR the select drops it.
-                const float ct = __builtin_amdgcn_sqrtf(1.f - st2);
-                const float ds = fmaf(v_n21, ct, ci), dp = fmaf(v_n21, ci, ct);   // both > 0 (ci > 0)
-                const float r = __builtin_amdgcn_rcpf(ds * dp);
-                const float rs = fmaf(-v_n21, ct, ci) * dp * r;
-                const float rp = fmaf(v_n21, ci, -ct) * ds * r;
-                const float R = v_fresnel * (st2 >= 1.f ? 1.f : 0.5f * fmaf(rs, rs, rp * rp));
-                const bool refl = u3 < R;
-                dx = refl && on_x ? -dx : dx;
-                dy = refl && on_y ? -dy : dy;
-                dz = refl && on_z ? -dz : dz;
-                ended = !refl;
-                face = refl ? -1 : 2 * axis + (pos_side ? 1 : 0);
-            } else {
-                // Interaction: count, absorb (Eq. 16), roulette, scatter.
-                ++k;
-                A = fmaf(w, l_abs, A);
-                w *= l_alb;
-                if (w < v_rw) {
-                    if (u3 < a.roulette_p) {
-                        const float wn = w * a.inv_roulette_p;
-                        atomicAdd(&s_scal[scal_at + MC_S_ROULETTE_NET], fix(wn) - fix(w));
-                        w = wn;
-                    } else {
-                        atomicAdd(&s_scal[scal_at + MC_S_ROULETTE_NET], 0ull - fix(w));
-                        atomicAdd(&s_scal[scal_at + MC_S_ROULETTE_KILLS], 1ull);
-                        w = 0.f;
-                        ended = true;
-                        cause = 1;
-                    }
-                }
-                if (!ended) {
-                    float v;
-                    if (PHASE == MC_PHASE_MIE) {
-                        // u1 <= 1 - 2^-24, so u1 (n - 1) rounds below n - 1 (exact when
-                        // n - 1 is a power of two, else more than half an ulp short of
-                        // it): i <= n - 2 and entry i + 1 exists.
-                        const float tt = u1 * tab_scale;
-                        const int i = (int)tt;
-                        // The fraction from the unrounded product u1 (n - 1).
-                        const float f = fmaf(u1, tab_scale, -(float)i);
-                        const float t0 = GLOBAL_TABLE ? l_tab[i] : s_table[i];
-                        const float t1 = GLOBAL_TABLE ? l_tab[i + 1] : s_table[i + 1];
-                        v = fmaf(f, t1 - t0, t0);
-                    } else {
-                        const float D = fmaf(-a.hg_b, u1, a.hg_a);
-                        const float rD = __builtin_amdgcn_rcpf(D);
-                        v = a.hg_d * u1 * fmaf(a.hg_c, rD, a.hg_d) * rD;
-                    }
-                    const float ct = 1.f - v;
-                    // A table value lies in [0, 2], and so does a rounded point between
-                    // two of them: v (2 - v) >= 0.  The HG formula can overshoot 2.
-                    const float st = __builtin_amdgcn_sqrtf(PHASE == MC_PHASE_MIE ? v * (2.f - v)
-                                                                                  : fmaxf(v * (2.f - v), 0.f));
-                    const float cp = __builtin_amdgcn_cosf(u2);        // cos(2 pi u2)
-                    const float sp = __builtin_amdgcn_sinf(u2);        // sin(2 pi u2)
-                    // Orthonormal basis around d (Duff et al. 2017).
-                    const float sg = copysignf(1.f, dz);
-                    const float ia = -__builtin_amdgcn_rcpf(sg + dz);
-                    const float b = dx * dy * ia;
-                    const float e1x = fmaf(sg * dx * dx, ia, 1.f), e1y = sg * b, e1z = -sg * dx;
-                    const float e2x = b, e2y = fmaf(dy * dy, ia, sg), e2z = -dy;
-                    const float qx = fmaf(cp, e1x, sp * e2x), qy = fmaf(cp, e1y, sp * e2y),
-                                qz = fmaf(cp, e1z, sp * e2z);
-                    const float nx = fmaf(ct, dx, st * qx), ny = fmaf(ct, dy, st * qy), nz = fmaf(ct, dz, st * qz);
-                    // |n|^2 is 1 up to rounding, so one Newton step of 1/sqrt from 1
-                    // (1.5 - |n|^2 / 2) renormalises to within 1e-13.
-                    const float inv = fmaf(-0.5f, fmaf(nx, nx, fmaf(ny, ny, nz * nz)), 1.5f);
-                    dx = nx * inv; dy = ny * inv; dz = nz * inv;
-                }
-            }
-            if (!ended && step >= a.max_steps) {
-                ended = true;
-                cause = 2;
-                atomicAdd(&s_scal[scal_at + MC_S_CAPPED_W], fix(w));
-                atomicAdd(&s_scal[scal_at + MC_S_CAPPED], 1ull);
-            }
-            if (ended) {
-                pending = true;
-                alive = false;
-            }
+            // Still inside the cuboid, by a margin, at the end of the free
+            // path?  Then no wall is nearer (kInside).
+            const float ex = fmaf(fmaf(s, dx, px), v_sx, -1.f), ey = fmaf(fmaf(s, dy, py), v_sy, -1.f);
+            const float ez = fmaf(fmaf(s, dz, pz), v_sz, -1.f);
+            out = fmaxf(fmaxf(fabsf(ex), fabsf(ey)), fabsf(ez));
+            if (out < kInside) interact(r.r1, r.r2);
         }
+        alive = __builtin_amdgcn_ballot_w64(out < kInside);
+        --calm;
     }
     flush(q_n);
 
@@ -801,7 +880,7 @@ void walk_kernel(WalkArgs a)
     } else {
         const unsigned long long wabs = wave_sum(acc_abs);
         // Lane counters are below 2^32; their wave sums are taken in 64 bits.
-        const unsigned long long wev = wave_sum((unsigned long long)acc_events);
+        const unsigned long long wev = wave_sum((unsigned long long)acc_steps - (unsigned long long)acc_hits);
         const unsigned long long wst = wave_sum((unsigned long long)acc_steps);
         const unsigned long long wph = wave_sum((unsigned long long)acc_photons);
         const unsigned long long wbl = wave_sum((unsigned long long)acc_ball);
@@ -836,8 +915,8 @@ void walk_kernel(WalkArgs a)
     for (int i = threadIdx.x; i < slots; i += blockDim.x) {
         const uint32_t key = s_key[i];
         if (key == kEmpty) continue;
-        atomicAdd(my_img + key, s_cw[i]);
-        if (SIGMA) atomicAdd(my_img2 + key, s_cw2[i]);
+        atomicAdd(my_img() + key, s_cw[i]);
+        if (SIGMA) atomicAdd(my_img2() + key, s_cw2[i]);
     }
     // The block's entries in each range of the exit log (all its waves have
     // appended: the barrier above).
@@ -1283,6 +1362,7 @@ void fill_common(WalkArgs &a, const mc_source_t &src, const mc_geometry_t &geo, 
 {
     for (int i = 0; i < 3; ++i) a.size[i] = (float)geo.size_mm[i];
     a.matched = geo.n_outside == geo.n_medium;
+    a.fresnel = a.matched ? 0.f : 1.f;
     a.n21 = (float)(geo.n_outside / geo.n_medium);
     a.n12 = (float)(geo.n_medium / geo.n_outside);
     a.n12sq = (float)((geo.n_medium / geo.n_outside) * (geo.n_medium / geo.n_outside));
@@ -1320,6 +1400,7 @@ void fill_common(WalkArgs &a, const mc_source_t &src, const mc_geometry_t &geo, 
     a.pix_scale[1] = (float)(det.side_nx / geo.size_mm[2]);
     a.pix_scale[2] = (float)(det.trans_ny / geo.size_mm[1]);
     a.pix_scale[3] = (float)(det.trans_nx / geo.size_mm[0]);
+    a.quiet_steps = rn.max_steps > (uint32_t)kQuietSteps ? rn.max_steps - kQuietSteps : 0u;
     a.copy_mask = kCopies - 1;
     a.n_side = (uint32_t)((uint64_t)det.side_nx * det.side_ny);
     a.n_pix_inst = (uint32_t)((uint64_t)det.side_nx * det.side_ny + (uint64_t)det.trans_nx * det.trans_ny);
@@ -1331,6 +1412,21 @@ void fill_medium(float &neg_ln2_over_mu, float &albedo, float &absorb, double mu
     neg_ln2_over_mu = mu_t > 0.0 ? (float)(-M_LN2 / mu_t) : -__builtin_huge_valf();
     albedo = (float)alb;
     absorb = (float)(1.0 - alb);
+}
+
+// Lower a.quiet_steps to where a photon of this medium cannot yet have met
+// roulette.  A weight starts at w0 and is multiplied by the albedo at most once
+// per step, each product off by at most 2^-24; the count is rounded down and
+// taken a thousandth short, which covers the logarithms' rounding too.
+void limit_quiet(WalkArgs &a, float albedo)
+{
+    const double keep = (double)albedo * (1.0 - 0x1p-23), drop = std::log((double)a.roulette_w / (double)a.w0);
+    double steps = 0.0;
+    if (a.roulette_w <= 0.f || (albedo > 0.f && drop < 0.0)) {
+        steps = a.roulette_w <= 0.f ? 4294967295.0 : std::min(4294967295.0, 0.999 * drop / std::log(keep));
+    }
+    const uint32_t n = (uint32_t)std::floor(steps);
+    a.quiet_steps = std::min(a.quiet_steps, n > kQuietSteps + 1u ? n - kQuietSteps - 1u : 0u);
 }
 
 // A medium's coefficients in 1/mm from the form the caller gave them in.
@@ -1389,19 +1485,21 @@ int medium_coefficients(const char *fn, const mc_medium_t &m, double size_z, Med
 // whose arguments carry up to kInstPerCopy media each (no host buffer has to
 // outlive the call).
 constexpr int kInstPerCopy = 32;
-constexpr uint32_t kRefillMin = 12;        // free lanes of a wave that trigger end-of-photon work (batched)
+constexpr uint32_t kRefillMin = 28;        // lanes of a wave not walking that trigger a round (batched)
 
-// The same for a single medium of optical depth tau along the beam axis,
-// from a sweep of thresholds 4..60 at tau = 0.25..16 (1e8 photons, 512 x 512,
-// exit log): 12 is within 2 % of the best from tau = 1.5 to 12.5 and 8 at 16;
-// media up to tau = 1 end most photons within two steps, and there refilling
-// only when 52 lanes are free (nearly the whole wave at once) ran 19 % faster
-// at tau = 1 than 12 and no slower below it.
+// The same for a single medium of optical depth tau along the beam axis.  A
+// high threshold shares a round among more photons, a low one keeps more lanes
+// walking.  From a sweep of thresholds 8..58 at tau = 0.5..16 (mc_simulate,
+// 1e8 photons, 512 x 512, exit log; ms at 12 / 20 / 24 / 28 / 34 (mean of 32
+// and 36) / 40): tau = 1 1.42 / 1.41 / 1.42 / 1.39 / 1.33 / 1.32; tau = 2 2.09 /
+// 1.94 / 1.79 / 1.76 / 1.76 / 1.77; tau = 4 2.87 / 2.51 / 2.45 / 2.42 / 2.41 /
+// 2.42; tau = 8 4.20 / 3.79 / 3.76 / 3.79 / 3.86 / 3.98; tau = 12 5.50 / 5.22 /
+// 5.14 / 5.21 / 5.44 / 5.74; tau = 16 6.92 / 6.59 / 6.68 / 6.83 / 7.12 / 7.53.
+// HG and path-moment walks have the same optima.
 uint32_t refill_min_for(double tau)
 {
     if (!(tau >= 0.0)) return kRefillMin;
-    if (tau <= 1.05) return 52;
-    return tau < 14.0 ? 12 : 8;
+    return tau < 5.0 ? 34 : (tau < 14.0 ? 24 : 20);
 }
 
 // Photon ids a wave claims at once (single medium, when the caller leaves
@@ -1518,7 +1616,8 @@ int launch_walk(WalkArgs &a, const mc_detector_t &det, const mc_run_t &rn, const
     if (chunk == 0) chunk = chunk_for(total_photons, waves_total, batch ? -1.0 : tau_z);
     a.chunk = (uint32_t)chunk;
     // Refill threshold from the optical depth; batched launches take the
-    // fixed one (12 ran 1 % faster there than 16, and 8 and 24 slower).
+    // fixed one (256 media, ms at 12 / 20 / 24 / 28 / 32 / 40: 20.5 / 19.3 /
+    // 19.05 / 18.97 / 19.01 / 19.5).
     a.refill_min = batch ? kRefillMin : refill_min_for(tau_z >= 0.0 ? tau_z : 0.0);
 
     // ---- exit log: a region of log_cap entries per block and key range in
@@ -1715,6 +1814,7 @@ int prepare_batch(const char *fn, const mc_batch_item_t *items, uint32_t n_items
     a.n_photons = 0;
     a.photon_offset = 0;
     a.record_stride = 1;
+    for (const BatchInst &b : sched) limit_quiet(a, b.albedo);
     return MC_OK;
 }
 
@@ -1787,6 +1887,7 @@ int simulate(const char *fn, const mc_medium_t *medium, const mc_source_t *sourc
     WalkArgs a{};
     fill_common(a, *source, geo, det, rn);
     fill_medium(a.neg_ln2_over_mu, a.albedo, a.absorb, coef.mu_ext, coef.albedo);
+    limit_quiet(a, a.albedo);
     a.copy_mask = (uint32_t)(copies - 1);
     a.phase = m.phase;
     a.n_cdf = m.phase == MC_PHASE_MIE ? m.n_cdf : 0;
