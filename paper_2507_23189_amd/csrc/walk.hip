@@ -3,9 +3,10 @@
 // Each lane carries one photon at a time in registers (position, direction,
 // weight, path length, scatter count, step) and runs the walk one step per
 // loop trip.  When a lane's photon ends it takes, at the wave's next round, the
-// next photon id from its wave's current id range; a wave claims ranges of `chunk` ids from a global
-// counter with one atomic, so lanes stay busy until the budget is spent and
-// the work counter sees one atomic per chunk rather than per photon.
+// next photon id from its wave's current id range.  A wave takes ranges of
+// `chunk` ids from its block's pool in LDS, and the block refills the pool from
+// a global counter, so lanes stay busy until the budget is spent and the
+// counter, one device-scope atomic per claim, sees a few per block.
 //
 // One step: a Philox4x32-10 block (counter = step, instance, id_lo, id_hi;
 // key = seed) gives four uniforms u0..u3 and the free path s = -ln(u0)/mu_ext
@@ -110,7 +111,10 @@ struct WalkArgs {
     float hg_a, hg_b, hg_c, hg_d;   // 1 + g, 2g, 1 - g^2, 1 - g
     uint32_t key0, key1, instance, max_steps;
     uint64_t n_photons, photon_offset;
-    uint32_t chunk;
+    uint32_t chunk;           // ids a wave takes from its block's pool (batched: photons of a work unit)
+    // Ids (work units) of the launch, those each block starts with, and the
+    // least and the share (1 / 2^shift) of the rest a block claims at once.
+    uint32_t n_ids, claim0, claim_min, claim_shift;
     uint32_t quiet_steps;     // a photon of fewer steps meets neither roulette nor the step cap in kQuietSteps more
     uint32_t refill_min;      // lanes not walking that trigger a round (1..64)
     uint32_t flags;
@@ -141,7 +145,6 @@ struct WalkArgs {
     const BatchInst *insts;
     uint32_t n_inst;          // media (slots) in the launch
     uint32_t n_pix_inst;      // side + transmitted pixels of one medium (key stride)
-    uint64_t n_units;
 };
 
 constexpr int kCopies = 8;                 // per-XCD image copies in the workspace (at most)
@@ -234,6 +237,17 @@ constexpr uint32_t kEmpty = 0xFFFFFFFFu;   // free tally-cache slot
 // Steps a wave takes at most before it looks again whether any of its photons
 // could meet roulette or the step cap in as many (WalkArgs::quiet_steps).
 constexpr int kQuietSteps = 32;
+// A block's pool of photon ids (or work units): the next id in the low word and
+// the end of its range in the high one.  A wave takes ids with one LDS add; the
+// wave that finds the range used up marks the pool as being filled, claims
+// ids from the global counter and publishes them, while the block's other
+// waves go on with the photons they hold.  Without a range the high word is 0
+// and the low one says whether the pool is being filled or closed for good.
+constexpr uint32_t kPoolFilling = 0x40000000u, kPoolClosed = 0x80000000u;
+__device__ __forceinline__ unsigned long long pool_range(uint32_t lo, uint32_t hi)
+{
+    return ((unsigned long long)hi << 32) | lo;
+}
 // Free path of a photon that did not end at a wall (a drawn one is positive).
 constexpr float kKilled = -1.f, kCapped = -2.f;
 // A free path ends inside the cuboid by a margin when each coordinate, scaled
@@ -321,7 +335,9 @@ void walk_kernel(WalkArgs a)
     unsigned long long *s_scal = (unsigned long long *)(s_table + (GLOBAL_TABLE ? 0 : ((a.n_cdf + 3) & ~3)));
     const int n_scal = BATCH ? (int)a.n_inst * kBatchScal : MC_N_SCALARS;
     const int slots = a.cache_bits ? 1 << a.cache_bits : 0;
-    unsigned long long *s_cw = s_scal + n_scal;
+    // The block's pool of photon ids (work units), see kPoolFilling.
+    unsigned long long *s_pool = s_scal + n_scal;
+    unsigned long long *s_cw = s_pool + 1;
     unsigned long long *s_cw2 = s_cw + (SIGMA ? slots : 0);
     uint32_t *s_key = (uint32_t *)(s_cw2 + slots);
     float *s_queue = (float *)(s_key + slots);
@@ -333,6 +349,11 @@ void walk_kernel(WalkArgs a)
     if (PHASE == MC_PHASE_MIE && !GLOBAL_TABLE)
         for (int i = threadIdx.x; i < a.n_cdf; i += blockDim.x) s_table[i] = a.inv_cdf[i];
     for (int i = threadIdx.x; i < n_scal; i += blockDim.x) s_scal[i] = 0ull;
+    if (threadIdx.x == 0) {
+        const uint64_t lo = min((uint64_t)blockIdx.x * a.claim0, (uint64_t)a.n_ids);
+        const uint64_t hi = min(lo + a.claim0, (uint64_t)a.n_ids);
+        *s_pool = lo < hi ? pool_range((uint32_t)lo, (uint32_t)hi) : 0ull;
+    }
     for (int i = threadIdx.x; i < slots; i += blockDim.x) {
         s_cw[i] = 0ull;
         if (SIGMA) s_cw2[i] = 0ull;
@@ -461,6 +482,45 @@ void walk_kernel(WalkArgs a)
     uint64_t q_next = 0;
     uint32_t q_rem = 0;
     bool exhausted = false;
+    // Take up to `want` ids from the block's pool, filling it from the global
+    // counter when it is empty (one lane calls this).  Returns the ids taken,
+    // first in *base, or 0: *done says whether any may still come.
+    auto take_ids = [&](ArgsPtr ra, uint32_t want, uint32_t *base, bool *done) -> uint32_t {
+        *done = false;
+        unsigned long long v = __hip_atomic_load(s_pool, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if ((uint32_t)v < (uint32_t)(v >> 32)) {
+            v = atomicAdd(s_pool, (unsigned long long)want);
+            const uint32_t next = (uint32_t)v, end = (uint32_t)(v >> 32);
+            if (next < end) {
+                *base = next;
+                return min(want, end - next);
+            }
+            v += want;
+        }
+        const uint32_t end = (uint32_t)(v >> 32);
+        if (end == 0u && (uint32_t)v >= kPoolFilling) {
+            *done = (uint32_t)v >= kPoolClosed;
+            return 0u;
+        }
+        if (atomicCAS(s_pool, v, (unsigned long long)kPoolFilling) != v) return 0u;
+        const uint32_t n = ra->n_ids;
+        const uint64_t first = (uint64_t)gridDim.x * ra->claim0;   // ids the blocks started with
+        uint64_t g = n;
+        uint32_t size = 0;
+        if (first < n) {
+            size = max((n - max(end, (uint32_t)first)) >> ra->claim_shift, ra->claim_min);
+            g = first + atomicAdd(ra->ws_scal + MC_S_RESERVED, (unsigned long long)size);
+        }
+        if (g >= n) {
+            __hip_atomic_store(s_pool, (unsigned long long)kPoolClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            *done = true;
+            return 0u;
+        }
+        const uint32_t lo = (uint32_t)g, hi = (uint32_t)min(g + size, (uint64_t)n), got = min(want, hi - lo);
+        __hip_atomic_store(s_pool, pool_range(lo + got, hi), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        *base = lo;
+        return got;
+    };
 
     // Lane state.  A lane walks while its photon's last step ended inside the
     // cuboid (out < kInside, see there; the wave-uniform mask of these lanes
@@ -668,7 +728,7 @@ void walk_kernel(WalkArgs a)
                     atomicAdd(&s_scal[scal_at + MC_S_CAPPED], 1ull);
                 }
                 // Faces +x and +z are totalled from their images when finalizing.
-                const bool below_one = __builtin_amdgcn_ballot_w64(w >= 1.f || A >= 1.f) == 0;   // wave-uniform
+                const bool below_one = __builtin_amdgcn_ballot_w64(max(__float_as_uint(w), __float_as_uint(A)) >= 0x3F800000u) == 0;   // wave-uniform
                 if (face >= 0 && (face | 4) != 5)
                     atomicAdd(&s_scal[scal_at + MC_S_FACE + face], below_one ? fix_below_one(w) : fix(w));
                 if (MOMENTS && face == 1) {
@@ -768,33 +828,28 @@ void walk_kernel(WalkArgs a)
             alive |= go_on;
             const uint64_t need = ~alive;
             if (q_rem == 0 && !exhausted && need) {
-                // Single medium: claim the next `chunk` photon ids.  Batched:
-                // claim the next work unit, `chunk` photons of one medium.
-                unsigned long long base = 0;
-                if (lane == 0) base = atomicAdd(ra->ws_scal + MC_S_RESERVED, BATCH ? 1ull : (unsigned long long)ra->chunk);
-                const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)base);
-                const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(base >> 32));
-                const uint64_t b = ((uint64_t)hi << 32) | lo;
-                if (BATCH) {
-                    if (b >= ra->n_units) {
-                        exhausted = true;
-                    } else {
-                        // The unit's medium: the last one whose first unit is <= b
-                        // (media without photons own no units and are never found).
-                        uint32_t l = 0, h = ra->n_inst;
-                        while (h - l > 1) {
-                            const uint32_t mid = (l + h) >> 1;
-                            if (ra->insts[mid].unit_begin <= b) l = mid; else h = mid;
-                        }
-                        q_p = l;
-                        q_next = (b - ra->insts[l].unit_begin) * ra->chunk;
-                        q_rem = (uint32_t)min((uint64_t)ra->chunk, ra->insts[l].n_photons - q_next);
+                // Single medium: take the next `chunk` photon ids.  Batched:
+                // the next work unit, `chunk` photons of one medium.
+                uint32_t base = 0, got = 0;
+                bool done = false;
+                if (lane == 0) got = take_ids(ra, BATCH ? 1u : ra->chunk, &base, &done);
+                base = __builtin_amdgcn_readfirstlane(base);
+                got = __builtin_amdgcn_readfirstlane(got);
+                exhausted = __builtin_amdgcn_readfirstlane((uint32_t)done) != 0u;
+                if (!BATCH) {
+                    q_next = base;
+                    q_rem = got;
+                } else if (got) {
+                    // The unit's medium: the last one whose first unit is <= base
+                    // (media without photons own no units and are never found).
+                    uint32_t l = 0, h = ra->n_inst;
+                    while (h - l > 1) {
+                        const uint32_t mid = (l + h) >> 1;
+                        if (ra->insts[mid].unit_begin <= base) l = mid; else h = mid;
                     }
-                } else if (b >= ra->n_photons) {
-                    exhausted = true;
-                } else {
-                    q_next = b;
-                    q_rem = (uint32_t)min((uint64_t)ra->chunk, ra->n_photons - b);
+                    q_p = l;
+                    q_next = (base - ra->insts[l].unit_begin) * ra->chunk;
+                    q_rem = (uint32_t)min((uint64_t)ra->chunk, ra->insts[l].n_photons - q_next);
                 }
             }
             const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(need >> 32),
@@ -842,7 +897,9 @@ void walk_kernel(WalkArgs a)
             alive |= __builtin_amdgcn_ballot_w64(starts);
             empty = ~alive;
             const uint32_t n_alive = (uint32_t)__popcll(alive), n_idle = ra->refill_min;
-            if (n_alive == 0u) break;   // nothing left to claim
+            // (Without a walking lane but not exhausted: another wave of the block
+            // is filling the pool, and the next round looks again.)
+            if (n_alive == 0u && exhausted) break;
             round_at = exhausted ? max(n_alive / 2u, n_alive - min(n_alive, n_idle)) : 64u - n_idle;
             if (!starts && !again) out = kOutside;
         }
@@ -1502,21 +1559,18 @@ uint32_t refill_min_for(double tau)
     return tau < 5.0 ? 34 : (tau < 14.0 ? 24 : 20);
 }
 
-// Photon ids a wave claims at once (single medium, when the caller leaves
-// it to the library): 16 claims per wave, at most 1024.  Every claim is one
-// device-scope atomic on one word, which takes about 78 million per second
-// (at 256 ids per claim the tau = 4 walk took 5.0 ms instead of 2.75); where
-// photons end within a few steps that rate binds, so below tau = 3 a claim
-// takes 2048 ids (up to tau = 1.05) or 3072, but no fewer than four claims
-// per wave.  mc_simulate at 1e8 photons, 512 x 512: tau = 0.5 1.84 -> 1.21
-// ms, tau = 1 1.91 -> 1.58, tau = 2 2.04 -> 1.88; tau = 4 and 8 ran alike
-// from 384 to 1536 ids.
-uint64_t chunk_for(uint64_t total_photons, uint64_t waves_total, double tau)
+// Photon ids a wave takes from its block's pool at once (single medium, when
+// the caller leaves it to the library), or photons of a batch's work unit.  A
+// large chunk leaves fewer rounds short of ids, a small one shares the end of
+// the launch better: mc_simulate at 256 / 512 ids, 1e8 photons, 512 x 512: tau
+// = 0.5 1.028 / 1.001 ms, tau = 1 1.254 / 1.238, tau = 4 2.328 / 2.318; 1e7
+// photons, tau = 16: 0.842 / 0.901.  A batch of 256 media at units of 128 / 256
+// / 512 photons: 18.9 / 18.6 / 18.9 ms, with 1/256 of its photons 0.790 / 0.806 /
+// 0.837.
+uint64_t chunk_for(uint64_t total_photons, uint64_t waves_total, bool batch)
 {
-    uint64_t chunk = std::min<uint64_t>(1024, total_photons / std::max<uint64_t>(1, waves_total * 16));
-    if (tau >= 0.0 && tau < 3.0)
-        chunk = std::max(chunk, std::min<uint64_t>(tau <= 1.05 ? 2048 : 3072,
-                                                   total_photons / std::max<uint64_t>(1, waves_total * 4)));
+    const uint64_t chunk = std::min<uint64_t>(batch ? 256 : 512,
+                                              total_photons / std::max<uint64_t>(1, waves_total * (batch ? 16 : 6)));
     return std::max<uint64_t>(64, (chunk + 63) / 64 * 64);
 }
 
@@ -1528,6 +1582,42 @@ struct InstChunk {
 __global__ void set_schedule(BatchInst *dst, InstChunk c)
 {
     if (threadIdx.x < c.n) dst[c.first + threadIdx.x] = c.v[threadIdx.x];
+}
+
+// How the blocks of a walk get their ids (or a batch's work units): see
+// WalkArgs::claim0 and kPoolFilling.  Every claim from the global counter is one
+// device-scope atomic on one word, which takes about 78 million per second.
+// When each wave claimed for itself that rate set the time of any launch up
+// to 1e7 photons (tau = 4: 1e5 0.19 ms, 1e6 0.37, 1e7 1.13); with a pool per
+// block these take 0.05, 0.11 and 0.33.
+//   * Up to four photons per lane, the ids are dealt out in equal shares and
+//     nothing is claimed (2e6 photons, shares / claims: tau = 1 0.116 / 0.132
+//     ms, tau = 4 0.140 / 0.150, tau = 16 0.309 / 0.305).
+//   * Beyond that a block starts with a quarter of its share and claims a
+//     fixed part of what it last saw left, down to four chunks: many claims
+//     where there is time for them, small ones at the end.  Parts of 1/4, 1/8
+//     and 1/16 of a share: tau = 4, 1e8 2.328 / 2.339 / 2.389 ms; tau = 16,
+//     1e8 6.61 / 6.55 / 6.56; tau = 16, 1e9 64.5 / 63.7 / 63.5.
+//   * A batch takes its units in order, eight at a time, so that all blocks
+//     work on the same few media at any time: claimed by shares, each block's
+//     exits were those of one medium, overflowed its regions of the log, and
+//     256 media took 48 ms instead of 18.6.
+void set_claims(WalkArgs &a, uint64_t units, uint64_t grid, uint64_t block, uint64_t chunk, double tau_z, bool batch)
+{
+    a.n_ids = (uint32_t)units;
+    if (batch) {
+        a.claim_shift = 31;
+        a.claim_min = 8;
+        a.claim0 = (uint32_t)std::min<uint64_t>(8, (units + grid - 1) / grid);
+        return;
+    }
+    const double work = (double)units * (1.0 + tau_z);
+    const uint64_t parts = grid * (work < 1e9 ? 4 : (work < 1e10 ? 8 : 16));
+    a.claim_shift = 2;
+    while (a.claim_shift < 31 && (1ull << a.claim_shift) < parts) ++a.claim_shift;
+    a.claim_min = (uint32_t)(4 * chunk);
+    const uint64_t even = (units + grid - 1) / grid;
+    a.claim0 = (uint32_t)(even <= 4 * block ? even : std::max<uint64_t>(even / 4, chunk));
 }
 
 // Enqueue init, walk and finalize for n_inst media (a single medium, or a
@@ -1578,7 +1668,7 @@ int launch_walk(WalkArgs &a, const mc_detector_t &det, const mc_run_t &rn, const
     // two per CU.
     const int block = rn.block_size ? rn.block_size : ((det.flags & MC_MOMENTS) ? 768 : 1024);
     const size_t table_bytes = batch ? 0 : (size_t)((a.n_cdf + 3) & ~3) * sizeof(float);
-    const size_t scal_bytes = (batch ? (size_t)n_inst * kBatchScal : MC_N_SCALARS) * sizeof(double);
+    const size_t scal_bytes = ((batch ? (size_t)n_inst * kBatchScal : MC_N_SCALARS) + 1) * sizeof(double);
     const size_t queue_arrays = batch ? 4 : 3;
     const size_t slot_bytes = sizeof(uint32_t) + sizeof(double) * ((det.flags & MC_SIGMA) ? 2 : 1);
     const size_t lds_half_cu = 80 * 1024;
@@ -1613,7 +1703,9 @@ int launch_walk(WalkArgs &a, const mc_detector_t &det, const mc_run_t &rn, const
                              ? -M_LN2 / (double)a.neg_ln2_over_mu * a.size[2]
                              : -1.0;
     uint64_t chunk = rn.chunk;
-    if (chunk == 0) chunk = chunk_for(total_photons, waves_total, batch ? -1.0 : tau_z);
+    if (chunk == 0) chunk = chunk_for(total_photons, waves_total, batch);
+    // Work units are counted in 31 bits.
+    if (batch) chunk = std::max<uint64_t>(chunk, total_photons >> 29);
     a.chunk = (uint32_t)chunk;
     // Refill threshold from the optical depth; batched launches take the
     // fixed one (256 media, ms at 12 / 20 / 24 / 28 / 32 / 40: 20.5 / 19.3 /
@@ -1675,7 +1767,6 @@ int launch_walk(WalkArgs &a, const mc_detector_t &det, const mc_run_t &rn, const
         }
         MC_HIP_CHECK(hipGetLastError());
         a.insts = dst;
-        a.n_units = units;
         static const Kern batch_kernels[4] = {
             walk_kernel<MC_PHASE_MIE, kOptBatch>, walk_kernel<MC_PHASE_MIE, kOptBatch | kOptSigma>,
             walk_kernel<MC_PHASE_MIE, kOptBatch | kOptLog>, walk_kernel<MC_PHASE_MIE, kOptBatch | kOptLog | kOptSigma>};
@@ -1706,6 +1797,7 @@ int launch_walk(WalkArgs &a, const mc_detector_t &det, const mc_run_t &rn, const
         }
         units = total_photons;
     }
+    set_claims(a, units, (uint64_t)grid, (uint64_t)block, chunk, std::max(tau_z, 0.0), batch);
     if (units > 0) {
         MC_HIP_CHECK(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         hipExtLaunchKernelGGL(kern, dim3(grid), dim3(block), (uint32_t)lds, st, (hipEvent_t)rn.walk_events[0],
