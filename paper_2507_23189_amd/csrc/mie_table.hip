@@ -1,7 +1,7 @@
 // Mie phase-function table on the device, FP64 (Sec. 2.2-2.6, Sec. 3.1.2).
 //
 // Two kernels build one table:
-//   mie_phase_kernel, one lane per angle, 256-lane workgroups:
+//   mie_phase_kernel, four lanes per angle, 256-lane workgroups:
 //   1. every workgroup runs the Bohren-Huffman series (Sec. 2.5) for itself:
 //      one lane runs the logarithmic derivative D_n(mx) by downward
 //      recurrence (in homogeneous form, D_n = P_n / Q_n, so the serial chain
@@ -9,23 +9,32 @@
 //      chi_n(x) upward; then every lane forms a_n and b_n for its n (Eqs. 7-8
 //      divided through by psi_n(mx)), and Q_ext (Eq. 13), Q_sca and the
 //      asymmetry sums (Eq. 12) are added in a fixed order;
-//   2. each lane evaluates S1, S2 (Eqs. 5-6) at its angle with the angular
-//      functions pi_n, tau_n by upward recurrence (the per-n divisions done
-//      once beforehand), giving the phase function normalised so that
-//      (1/4pi) int P dOmega = 1 (Eqs. 9-10); P sin(theta) goes to a device
-//      buffer of n_angles doubles;
+//   2. four lanes evaluate S1, S2 (Eqs. 5-6) at an angle, one each of their real
+//      and imaginary parts, with the angular functions pi_n, tau_n by upward
+//      recurrence (the per-n divisions done once beforehand), giving the phase
+//      function normalised so that (1/4pi) int P dOmega = 1 (Eqs. 9-10);
+//      P sin(theta) goes to a device buffer of n_angles doubles;
 //   mie_inverse_kernel, one lane per inverse-table entry, 1024-lane groups:
 //   3. every workgroup reads the whole P sin(theta) grid into LDS and forms
 //      its trapezoid CDF by a block scan;
 //   4. each inverse-table entry u_i = i/(N-1) finds the first angle with
 //      F >= u_i by binary search and interpolates theta linearly; the table
 //      stores v = 1 - cos(theta) = 2 sin^2(theta/2) in FP32.
-// The series is short and serial, so repeating it per workgroup costs no
-// time, while the angle grid and the inverse table, which took a single
-// compute unit's FP64 issue, spread over ~8 and ~16 of them.  Arrays live in
-// LDS (coefficients 32 KB, pi_n recurrence coefficients 16 KB, psi and chi
-// 16 KB, angle grid 24 KB at the limits; gfx950 gives a workgroup up to
-// 160 KB).
+// A size distribution has a workgroup per bin and 256 angles, one lane each
+// (mie_bin_kernel): there the series of many bins fills the chip, and four times
+// the workgroups would repeat it four times as often (58 us for 64 bins against
+// 22).
+//
+// All of it is bound by the serial chains: a dependent FP64 fma takes about 33
+// cycles on a lone wave, four of them a downward step (two for a real index),
+// two a term of a sum.  The 100 um absorbing sphere (x = 785) takes 57 us of
+// downward steps, hidden behind them 18 of upward ones (33 with a division in
+// each), and 30 of sums; the 5 um one 4.7 and 2.9 of the kernel's 12.6.  Before
+// (one lane per angle, factors formed in the steps, eight fma in every downward
+// step) mie_phase_kernel took 14.4 us at 5 um and 133 at 100 um, the 64 bins 26.5.
+// Arrays live in LDS (coefficients 32 KB, pi_n recurrence coefficients 16 KB,
+// psi and chi 16 KB, factors 6 KB, angle grid 24 KB at the limits; gfx950 gives
+// a workgroup up to 160 KB).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -37,13 +46,13 @@
 namespace mcmie {
 namespace {
 
-constexpr int kPhaseThreads = 256;    // phase kernels: one angle per lane
+constexpr int kPhaseThreads = 256;    // phase kernels
+constexpr int kAngles = kPhaseThreads / 4;   // angles of a workgroup of mie_phase_kernel
 constexpr int kInvThreads = 1024;     // CDF and inverse: one entry per lane, 1..3 angles per lane in the scan
 
 struct cplx {
     double re, im;
 };
-__device__ __forceinline__ cplx operator+(cplx a, cplx b) { return {a.re + b.re, a.im + b.im}; }
 __device__ __forceinline__ cplx operator-(cplx a, cplx b) { return {a.re - b.re, a.im - b.im}; }
 __device__ __forceinline__ cplx operator*(cplx a, cplx b)
 {
@@ -101,6 +110,190 @@ struct MieArgs {
     double *work;            // n_angles: P(theta_j) sin(theta_j), from the phase kernel to the inverse kernel
 };
 
+// The serial recurrences run on one lane of a wave of their own, whose
+// instruction count is their time (a lone wave issues one instruction every
+// four cycles or more).  So its 64 lanes first form the factors of kChunk
+// steps into LDS, and the lane's steps are the recurrence's own fma, a store,
+// and a read of two factors ahead of their use, in groups of eight without
+// branches.
+constexpr int kChunk = 256, kAhead = 16;   // kAhead: entries before the first that reading ahead may touch
+
+// One wave's downward recurrence of D_n(mx) = P_n / Q_n from n_start (see
+// mie_series_block): P_n to s_a and Q_n to s_b, index n - 1, for n = N..1.  For a
+// real index all imaginary parts are zero and the steps leave them out: two fma
+// instead of eight, P_n and Q_n stored as the pair s_a.
+// s_k holds kAhead + kChunk factors n/(mx).
+template <bool REAL>
+__device__ __forceinline__ void downward(cplx inv_mx, int N, int n_start, double2 *s_k, cplx *s_a, cplx *s_b)
+{
+    const int lane = threadIdx.x & 63;
+    cplx P = {0.0, 0.0}, Q = {1.0, 0.0};   // D_{n_start} = 0
+    auto step = [&](cplx k) {
+        if (REAL) {
+            const double Q1 = fma(k.re, Q.re, P.re);
+            P.re = fma(k.re, Q1, -Q.re);
+            Q.re = Q1;
+        } else {
+            const cplx Q1 = {fma(k.re, Q.re, fma(-k.im, Q.im, P.re)), fma(k.re, Q.im, fma(k.im, Q.re, P.im))};
+            P = {fma(k.re, Q1.re, fma(-k.im, Q1.im, -Q.re)), fma(k.re, Q1.im, fma(k.im, Q1.re, -Q.im))};
+            Q = Q1;
+        }
+    };
+    auto rescale = [&]() {   // after each step from a multiple of 8
+        double top = fmax(fabs(P.re), fabs(Q.re));
+        if (!REAL) top = fmax(fmax(fabs(P.re), fabs(P.im)), fmax(fabs(Q.re), fabs(Q.im)));
+        int e;
+        (void)frexp(top, &e);
+        P.re = ldexp(P.re, -e);
+        Q.re = ldexp(Q.re, -e);
+        if (!REAL) {
+            P.im = ldexp(P.im, -e);
+            Q.im = ldexp(Q.im, -e);
+        }
+    };
+    auto keep = [&](int n) {   // D_n = P_n / Q_n
+        if (REAL) {
+            s_a[n - 1] = cplx{P.re, Q.re};
+        } else {
+            s_a[n - 1] = P;
+            s_b[n - 1] = Q;
+        }
+    };
+    struct Eight {
+        cplx k[8];   // of n, n - 1, .., n - 7
+    };
+    double *const s_kr = (double *)s_k;
+    for (int top = n_start; top >= 1;) {
+        // Steps top..bot of this chunk; bot is one past a multiple of 8.
+        const int bot = (top - 1) / kChunk * kChunk + 1;
+        for (int i = lane; i <= top - bot; i += 64) {
+            const cplx k = (double)(bot + i) * inv_mx;
+            if (REAL) s_kr[kAhead + i] = k.re;
+            else s_k[kAhead + i] = double2{k.re, k.im};
+        }
+        if (lane == 0) {
+            auto factor = [&](int n) -> cplx {
+                if (REAL) return cplx{s_kr[kAhead + n - bot], 0.0};
+                const double2 k = s_k[kAhead + n - bot];
+                return cplx{k.x, k.y};
+            };
+            auto eight = [&](int n) {
+                Eight e;
+#pragma unroll
+                for (int u = 0; u < 8; ++u) e.k[u] = factor(n - u);
+                return e;
+            };
+            int n = top;
+            auto one = [&]() {
+                if (n <= N) keep(n);
+                step(factor(n));
+                if ((n & 7) == 0) rescale();
+                --n;
+            };
+            auto group = [&](const Eight &e, bool kept) {   // n, a multiple of 8, .. n - 7
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    if (kept) keep(n - u);
+                    step(e.k[u]);
+                    if (u == 0) rescale();
+                }
+                n -= 8;
+            };
+            while (n >= bot && ((n & 7) || (n > N && n - 7 <= N))) one();
+            // Two groups at a time, each reading the next one's factors first.
+            // (Those beyond the chunk's end are not used.)
+            Eight a = eight(n);
+            while (n >= bot) {
+                if (n > N && n - 7 <= N) {   // the group in which keeping starts
+                    for (int u = 0; u < 8; ++u) one();
+                    a = eight(n);
+                    continue;
+                }
+                const Eight b = eight(n - 8);
+                if (n <= N) group(a, true);
+                else group(a, false);
+                if (n < bot || (n > N && n - 7 <= N)) {
+                    a = b;
+                    continue;
+                }
+                a = eight(n - 8);
+                if (n <= N) group(b, true);
+                else group(b, false);
+            }
+        }
+        top = bot - 1;
+    }
+}
+
+// One wave's upward recurrences psi_n = (2n - 1)/x psi_{n-1} - psi_{n-2}, chi_n
+// likewise, into s_rec at index n = 0..N.  s_f holds kChunk factors.
+__device__ __forceinline__ void upward(double x, int N, double *s_f, double2 *s_rec)
+{
+    const int lane = threadIdx.x & 63;
+    double psi_prev = cos(x), psi = sin(x);        // psi_{-1}, psi_0
+    double chi_prev = -sin(x), chi = cos(x);       // chi_{-1}, chi_0
+    if (lane == 0) s_rec[0] = double2{psi, chi};
+    for (int n0 = 1; n0 <= N; n0 += kChunk) {
+        const int steps = min(kChunk, N + 1 - n0);
+        for (int i = lane; i < steps; i += 64) s_f[i] = (2.0 * (n0 + i) - 1.0) / x;
+        if (lane == 0) {
+            auto up = [&](int i, double f) {
+                const double psi_n = f * psi - psi_prev;
+                const double chi_n = f * chi - chi_prev;
+                s_rec[n0 + i] = double2{psi_n, chi_n};
+                psi_prev = psi;
+                psi = psi_n;
+                chi_prev = chi;
+                chi = chi_n;
+            };
+            struct Eight {
+                double f[8];
+            };
+            auto eight = [&](int i) {
+                Eight e;
+#pragma unroll
+                for (int u = 0; u < 8; ++u) e.f[u] = s_f[min(i, kChunk - 8) + u];
+                return e;
+            };
+            int i = 0;
+            Eight a = eight(0);
+            for (; i + 16 <= steps; i += 16) {
+                const Eight b = eight(i + 8);
+#pragma unroll
+                for (int u = 0; u < 8; ++u) up(i + u, a.f[u]);
+                a = eight(i + 16);
+#pragma unroll
+                for (int u = 0; u < 8; ++u) up(i + 8 + u, b.f[u]);
+            }
+            for (; i < steps; ++i) up(i, s_f[i]);
+        }
+    }
+}
+
+// v + its value 32, 16, .. 1 lanes across: the sum over the wave, in every lane,
+// in that order.  Without LDS: halves and rows are exchanged by the permlane
+// swaps; within a row of 16 a rotation by 8 is the lane 8 across, and after
+// that step a rotation by 4 the lane 4 across.
+__device__ __forceinline__ double wave_sum(double v)
+{
+    auto halves = [](double v, auto swap) {
+        const int2 x = __builtin_bit_cast(int2, v);
+        const auto lo = swap(x.x), hi = swap(x.y);
+        return __builtin_bit_cast(double, int2{(int)lo[0], (int)hi[0]}) +
+               __builtin_bit_cast(double, int2{(int)lo[1], (int)hi[1]});
+    };
+    auto row = [](double v, auto move) {
+        const int2 x = __builtin_bit_cast(int2, v);
+        return v + __builtin_bit_cast(double, int2{move(x.x), move(x.y)});
+    };
+    v = halves(v, [](int x) { return __builtin_amdgcn_permlane32_swap(x, x, false, false); });
+    v = halves(v, [](int x) { return __builtin_amdgcn_permlane16_swap(x, x, false, false); });
+    v = row(v, [](int x) { return __builtin_amdgcn_mov_dpp(x, 0x128, 0xF, 0xF, true); });   // row_ror:8
+    v = row(v, [](int x) { return __builtin_amdgcn_mov_dpp(x, 0x124, 0xF, 0xF, true); });   // row_ror:4
+    v = row(v, [](int x) { return __builtin_amdgcn_mov_dpp(x, 0x4E, 0xF, 0xF, true); });    // quad_perm 2301
+    return row(v, [](int x) { return __builtin_amdgcn_mov_dpp(x, 0xB1, 0xF, 0xF, true); }); // quad_perm 1032
+}
+
 // Step 1 by every lane of a workgroup: the series for size parameter x and relative
 // index m.  The two recurrences are serial and run at once on lanes of two
 // different waves: D_n(mx) downward from n_start and psi_n(x), chi_n(x)
@@ -122,57 +315,27 @@ struct MieArgs {
 // added per lane, per wave and over the waves in a fixed order.  On return
 // (after a barrier) s_sums holds Q_ext, Q_sca and g for every lane.
 __device__ __forceinline__ void mie_series_block(double x, double m_re, double m_im, int N, int n_start, cplx *s_a, cplx *s_b,
-                                 double *s_psi, double *s_chi, double *s_red, double *s_sums)
+                                                 double2 *s_rec, double2 *s_fac, double *s_red, double *s_sums)
 {
     const int tid = threadIdx.x;
     const cplx m = {m_re, m_im};
-    if (tid == 0) {
+    const bool real = m_im == 0.0;
+    if (tid < 64) {
         const cplx mx = x * m;
         const cplx inv_mx = cplx{1.0, 0.0} / mx;
-        cplx P = {0.0, 0.0}, Q = {1.0, 0.0};   // D_{n_start} = 0
-        auto step = [&](int n) {
-            const cplx k = (double)n * inv_mx;
-            const cplx Q1 = {fma(k.re, Q.re, fma(-k.im, Q.im, P.re)), fma(k.re, Q.im, fma(k.im, Q.re, P.im))};
-            P = {fma(k.re, Q1.re, fma(-k.im, Q1.im, -Q.re)), fma(k.re, Q1.im, fma(k.im, Q1.re, -Q.im))};
-            Q = Q1;
-            if ((n & 7) == 0) {
-                int e;
-                (void)frexp(fmax(fmax(fabs(P.re), fabs(P.im)), fmax(fabs(Q.re), fabs(Q.im))), &e);
-                P = {ldexp(P.re, -e), ldexp(P.im, -e)};
-                Q = {ldexp(Q.re, -e), ldexp(Q.im, -e)};
-            }
-        };
-        int n = n_start;
-        for (; n > N; --n) step(n);
-        for (; n >= 1; --n) {   // keep D_n = P_n / Q_n for n <= N
-            s_a[n - 1] = P;
-            s_b[n - 1] = Q;
-            step(n);
-        }
-    } else if (tid == 64) {
-        double psi_prev = cos(x), psi = sin(x);        // psi_{-1}, psi_0
-        double chi_prev = -sin(x), chi = cos(x);       // chi_{-1}, chi_0
-        s_psi[0] = psi;
-        s_chi[0] = chi;
-        for (int n = 1; n <= N; ++n) {
-            const double f = (2.0 * n - 1.0) / x;
-            const double psi_n = f * psi - psi_prev;
-            const double chi_n = f * chi - chi_prev;
-            s_psi[n] = psi_n;
-            s_chi[n] = chi_n;
-            psi_prev = psi;
-            psi = psi_n;
-            chi_prev = chi;
-            chi = chi_n;
-        }
+        if (real) downward<true>(inv_mx, N, n_start, s_fac, s_a, s_b);
+        else downward<false>(inv_mx, N, n_start, s_fac, s_a, s_b);
+    } else if (tid < 128) {
+        upward(x, N, (double *)(s_fac + kAhead + kChunk), s_rec);
     }
     __syncthreads();
     const cplx inv_m = cplx{1.0, 0.0} / m;
     for (int n = tid + 1; n <= N; n += blockDim.x) {
-        const double psi_n = s_psi[n], psi = s_psi[n - 1];
-        const cplx xi_n = {psi_n, -s_chi[n]};
-        const cplx xi_nm1 = {psi, -s_chi[n - 1]};
-        const cplx Dn = s_a[n - 1] / s_b[n - 1];
+        const double psi_n = s_rec[n].x, psi = s_rec[n - 1].x;
+        const cplx xi_n = {psi_n, -s_rec[n].y};
+        const cplx xi_nm1 = {psi, -s_rec[n - 1].y};
+        const cplx Pn = s_a[n - 1];
+        const cplx Dn = real ? cplx{Pn.re / Pn.im, 0.0} : Pn / s_b[n - 1];
         const double nx = (double)n / x;
         const cplx da = Dn * inv_m + nx;
         const cplx db = m * Dn + nx;
@@ -194,12 +357,9 @@ __device__ __forceinline__ void mie_series_block(double x, double m_re, double m
         }
         sum_g += w / ((double)n * (n + 1)) * (an.re * bn.re + an.im * bn.im);
     }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        sum_ext += __shfl_xor(sum_ext, off, 64);
-        sum_sca += __shfl_xor(sum_sca, off, 64);
-        sum_g += __shfl_xor(sum_g, off, 64);
-    }
+    sum_ext = wave_sum(sum_ext);
+    sum_sca = wave_sum(sum_sca);
+    sum_g = wave_sum(sum_g);
     const int waves = blockDim.x >> 6;
     if ((tid & 63) == 0) {
         s_red[3 * (tid >> 6) + 0] = sum_ext;
@@ -239,42 +399,124 @@ __device__ void prepare_angular(int N, cplx *s_a, cplx *s_b, double2 *s_pi)
     __syncthreads();
 }
 
-// Step 2 at one angle: |S1|^2 + |S2|^2 (Eqs. 5-6) with the angular functions
-// upward, pi_n = ((2n - 1) mu pi_{n-1} - n pi_{n-2}) / (n - 1) from pi_0 = 0,
-// pi_1 = 1, and tau_n = n mu pi_n - (n + 1) pi_{n-1}, on the coefficients
-// prepared above.
-__device__ double mie_intensity(double th, int N, const cplx *s_a, const cplx *s_b, const double2 *s_pi)
+// Step 2 at an angle of cosine mu: S1 and S2 (Eqs. 5-6) with the angular functions
+// upward, pi_n = ((2n - 1) mu pi_{n-1} - n pi_{n-2}) / (n - 1) from pi_0 = 0, pi_1
+// = 1, and tau_n = n mu pi_n - (n + 1) pi_{n-1}, on the coefficients prepared
+// above.  PART says what the lane adds up: kAll both sums, S[0..3] = Re S1, Im S1,
+// Re S2, Im S2; kFirst or kSecond only the real part (im = 0) or imaginary part
+// (1) of S1 or S2, S[0].  The loop runs a single wave on its SIMD and each sum
+// takes two dependent fma a term, about 33 cycles each; the next terms'
+// coefficients are read while four are worked on.
+enum SumPart { kAll, kFirst, kSecond };
+template <SumPart PART>
+__device__ __forceinline__ void mie_sums(double mu, int N, const cplx *s_a, const cplx *s_b, const double2 *s_pi, int im,
+                                         double *S)
 {
-    const double mu = cos_0_pi(th);
+    struct Term {
+        double2 c;
+        cplx a, b;
+    };
+    auto read = [&](int i) -> Term {
+        if (PART == kAll) return {s_pi[i], s_a[i], s_b[i]};
+        return {s_pi[i], {((const double *)(s_a + i))[im], 0.0}, {((const double *)(s_b + i))[im], 0.0}};
+    };
     double pi_prev = 0.0, pi_n = 1.0;              // pi_0, pi_1
-    // n = 1: tau_1 = mu
-    cplx S1 = pi_n * s_a[0] + mu * s_b[0];
-    cplx S2 = mu * s_a[0] + pi_n * s_b[0];
-    double dn = 1.0;
-    for (int n = 2; n <= N; ++n) {
-        dn += 1.0;
-        const double2 c = s_pi[n - 1];
-        const double p = fma(c.x * mu, pi_n, -c.y * pi_prev);
+    {   // n = 1: tau_1 = mu
+        const Term t = read(0);
+        if (PART == kAll) {
+            S[0] = fma(mu, t.b.re, t.a.re); S[1] = fma(mu, t.b.im, t.a.im);
+            S[2] = fma(mu, t.a.re, t.b.re); S[3] = fma(mu, t.a.im, t.b.im);
+        } else {
+            S[0] = PART == kFirst ? fma(mu, t.b.re, t.a.re) : fma(mu, t.a.re, t.b.re);
+        }
+    }
+    double dn = 2.0;
+    auto add = [&](const Term &t) {
+        const double p = fma(t.c.x * mu, pi_n, -t.c.y * pi_prev);
         pi_prev = pi_n;
         pi_n = p;
-        const double tau_n = fma(dn * mu, pi_n, -(dn + 1.0) * pi_prev);
-        const cplx an = s_a[n - 1], bn = s_b[n - 1];
-        S1 = {fma(pi_n, an.re, fma(tau_n, bn.re, S1.re)), fma(pi_n, an.im, fma(tau_n, bn.im, S1.im))};
-        S2 = {fma(tau_n, an.re, fma(pi_n, bn.re, S2.re)), fma(tau_n, an.im, fma(pi_n, bn.im, S2.im))};
+        const double dmu = dn * mu;
+        dn += 1.0;
+        const double tau_n = fma(dmu, pi_n, -dn * pi_prev);
+        if (PART == kAll) {
+            S[0] = fma(pi_n, t.a.re, fma(tau_n, t.b.re, S[0]));
+            S[1] = fma(pi_n, t.a.im, fma(tau_n, t.b.im, S[1]));
+            S[2] = fma(tau_n, t.a.re, fma(pi_n, t.b.re, S[2]));
+            S[3] = fma(tau_n, t.a.im, fma(pi_n, t.b.im, S[3]));
+        } else if (PART == kFirst) {
+            S[0] = fma(pi_n, t.a.re, fma(tau_n, t.b.re, S[0]));
+        } else {
+            S[0] = fma(tau_n, t.a.re, fma(pi_n, t.b.re, S[0]));
+        }
+    };
+    constexpr int G = 4;
+    struct Four {
+        Term t[G];
+    };
+    auto four = [&](int n) {   // (terms beyond N are read but not used)
+        Four f;
+#pragma unroll
+        for (int u = 0; u < G; ++u) f.t[u] = read(min(n, MC_MAX_TERMS - G + 1) + u - 1);
+        return f;
+    };
+    int n = 2;
+    Four f = four(n);
+    for (; n + 2 * G <= N + 1; n += 2 * G) {
+        const Four g = four(n + G);
+#pragma unroll
+        for (int u = 0; u < G; ++u) add(f.t[u]);
+        f = four(n + 2 * G);
+#pragma unroll
+        for (int u = 0; u < G; ++u) add(g.t[u]);
     }
-    return norm2(S1) + norm2(S2);
+    for (; n <= N; ++n) add(read(n - 1));
+}
+
+// |S1|^2 + |S2|^2 and its halves, rounded the same way wherever the sums come from.
+__device__ __forceinline__ double square(double re, double im) { return fma(re, re, im * im); }
+__device__ __forceinline__ double plus(double x, double y)
+{
+#pragma clang fp contract(off)
+    return x + y;
 }
 
 // Step 2 at angle j of the na-point grid: scale x (|S1|^2 + |S2|^2) to
 // phase_out[j] and, times sin(theta_j), to ang[j] (each if given).
-__device__ void phase_at(int j, int na, int N, double scale, const cplx *s_a, const cplx *s_b, const double2 *s_pi,
-                         double *phase_out, double *ang)
+__device__ __forceinline__ void put_phase(int j, double th, double P, double *phase_out, double *ang)
 {
-    const double dth = M_PI / (double)(na - 1);
-    const double th = (double)j * dth;
-    const double P = scale * mie_intensity(th, N, s_a, s_b, s_pi);
     if (phase_out) phase_out[j] = P;
     if (ang) ang[j] = P * sin_0_pi(th);
+}
+
+// One lane per angle.
+__device__ __forceinline__ void phase_at(int j, int na, int N, double scale, const cplx *s_a, const cplx *s_b,
+                                         const double2 *s_pi, double *phase_out, double *ang)
+{
+    const double th = (double)j * (M_PI / (double)(na - 1));
+    double S[4];
+    mie_sums<kAll>(cos_0_pi(th), N, s_a, s_b, s_pi, 0, S);
+    put_phase(j, th, scale * plus(square(S[0], S[1]), square(S[2], S[3])), phase_out, ang);
+}
+
+// Four lanes per angle, one for each sum: waves 0 and 1 take S1, 2 and 3 S2, of the
+// workgroup's kAngles angles; even lanes the real part, odd ones the imaginary.
+// s_half holds kAngles doubles.
+__device__ __forceinline__ void phase_split(int na, int N, double scale, const cplx *s_a, const cplx *s_b,
+                                            const double2 *s_pi, double *s_half, double *phase_out, double *ang)
+{
+    const int tid = threadIdx.x, at = (tid & (kPhaseThreads / 2 - 1)) >> 1, j = blockIdx.x * kAngles + at;
+    const double th = (double)j * (M_PI / (double)(na - 1));
+    const bool first = tid < kPhaseThreads / 2;
+    double S;
+    if (first) mie_sums<kFirst>(cos_0_pi(th), N, s_a, s_b, s_pi, tid & 1, &S);
+    else mie_sums<kSecond>(cos_0_pi(th), N, s_a, s_b, s_pi, tid & 1, &S);
+    const int2 x = __builtin_bit_cast(int2, S);   // the neighbour's part (quad_perm 1032)
+    const double im = __builtin_bit_cast(double, int2{__builtin_amdgcn_mov_dpp(x.x, 0xB1, 0xF, 0xF, true),
+                                                      __builtin_amdgcn_mov_dpp(x.y, 0xB1, 0xF, 0xF, true)});
+    const double half = square(S, im);
+    if (!first && !(tid & 1)) s_half[at] = half;
+    __syncthreads();
+    if (first && !(tid & 1) && j < na) put_phase(j, th, scale * plus(half, s_half[at]), phase_out, ang);
 }
 
 // Steps 1-2 for one size: workgroup b runs the series, workgroup 0 writes the
@@ -284,15 +526,17 @@ __global__ __launch_bounds__(kPhaseThreads) void mie_phase_kernel(MieArgs a)
 {
     __shared__ cplx s_a[MC_MAX_TERMS];
     __shared__ cplx s_b[MC_MAX_TERMS];
-    __shared__ double s_rec[2 * (MC_MAX_TERMS + 1)];   // psi_n, chi_n
+    __shared__ double2 s_rec[MC_MAX_TERMS + 1];         // psi_n, chi_n
+    __shared__ double2 s_fac[kAhead + kChunk + kChunk / 2];   // factors of the recurrences
     __shared__ double2 s_pi[MC_MAX_TERMS];              // pi_n recurrence coefficients
     __shared__ double s_red[3 * (kPhaseThreads / 64)];
     __shared__ double s_sums[3];                       // Q_ext, Q_sca, g
+    __shared__ double s_half[kAngles];                 // |S2|^2
 
     const int tid = threadIdx.x;
     const int N = a.n_terms;
     const double x = a.x;
-    mie_series_block(x, a.m_re, a.m_im, N, a.n_start, s_a, s_b, s_rec, s_rec + MC_MAX_TERMS + 1, s_red, s_sums);
+    mie_series_block(x, a.m_re, a.m_im, N, a.n_start, s_a, s_b, s_rec, s_fac, s_red, s_sums);
     if (blockIdx.x == 0) {
         if (tid == 0) {
             a.result[0] = s_sums[0];
@@ -312,8 +556,7 @@ __global__ __launch_bounds__(kPhaseThreads) void mie_phase_kernel(MieArgs a)
     __syncthreads();
     prepare_angular(N, s_a, s_b, s_pi);
     // Phase function normalised as Eq. 10: P = 2 (|S1|^2 + |S2|^2) / (x^2 Q_sca).
-    const int j = blockIdx.x * kPhaseThreads + tid;
-    if (j < a.n_angles) phase_at(j, a.n_angles, N, 2.0 / (x * x * s_sums[1]), s_a, s_b, s_pi, a.phase, a.work);
+    phase_split(a.n_angles, N, 2.0 / (x * x * s_sums[1]), s_a, s_b, s_pi, s_half, a.phase, a.work);
 }
 
 __device__ int first_at_least(const double *f, int l, int r, double u)
@@ -426,14 +669,15 @@ __global__ __launch_bounds__(kPhaseThreads) void mie_bin_kernel(PolyArgs a)
 {
     __shared__ cplx s_a[MC_MAX_TERMS];
     __shared__ cplx s_b[MC_MAX_TERMS];
-    __shared__ double s_rec[2 * (MC_MAX_TERMS + 1)];   // psi_n, chi_n
+    __shared__ double2 s_rec[MC_MAX_TERMS + 1];         // psi_n, chi_n
+    __shared__ double2 s_fac[kAhead + kChunk + kChunk / 2];   // factors of the recurrences
     __shared__ double2 s_pi[MC_MAX_TERMS];              // pi_n recurrence coefficients
     __shared__ double s_red[3 * (kPhaseThreads / 64)];
     __shared__ double s_sums[3];
     const int k = blockIdx.y, tid = threadIdx.x;
     const double x = a.x[k];
     const int N = a.n_terms[k];
-    mie_series_block(x, a.m_re, a.m_im, N, a.n_start[k], s_a, s_b, s_rec, s_rec + MC_MAX_TERMS + 1, s_red, s_sums);
+    mie_series_block(x, a.m_re, a.m_im, N, a.n_start[k], s_a, s_b, s_rec, s_fac, s_red, s_sums);
     if (blockIdx.x == 0 && tid == 0) {
         a.bins[4 * k + 0] = s_sums[0];
         a.bins[4 * k + 1] = s_sums[1];
@@ -546,7 +790,7 @@ int launch_table(MieArgs args, mie_table_t *table, hipStream_t st, double *resul
 {
     args.result = result;
     args.work = work;
-    const int g_phase = (args.n_angles + kPhaseThreads - 1) / kPhaseThreads;
+    const int g_phase = (args.n_angles + kAngles - 1) / kAngles;
     const int g_inv = (args.n_cdf + kInvThreads - 1) / kInvThreads;
     hipLaunchKernelGGL(mie_phase_kernel, dim3(g_phase), dim3(kPhaseThreads), 0, st, args);
     hipLaunchKernelGGL(mie_inverse_kernel, dim3(g_inv), dim3(kInvThreads), 0, st, (const double *)work, args.n_angles,
