@@ -1,6 +1,8 @@
 // Error reporting and version entry points of the C ABI.
 #include "common.hpp"
 
+#include <atomic>
+#include <cstring>
 #include <mutex>
 
 namespace mcmie {
@@ -33,6 +35,51 @@ int device_cu_count(int *out)
     }
     *out = cached[dev];
     return MC_OK;
+}
+
+static std::atomic<uint64_t> g_free{~0ull};   // free slots of g_pinned
+static double *g_pinned = nullptr;            // 64 x kHostResult doubles
+static std::once_flag g_pinned_once;
+
+HostResult::HostResult() : slot_(-1)
+{
+    std::call_once(g_pinned_once, [] {
+        void *p = nullptr, *dev = nullptr;
+        const size_t bytes = 64 * kHostResult * sizeof(double);
+        if (hipHostMalloc(&p, bytes, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess ||
+            hipHostGetDevicePointer(&dev, p, 0) != hipSuccess || dev != p) {
+            (void)hipGetLastError();
+            return;
+        }
+        g_pinned = (double *)p;
+    });
+    if (!g_pinned) return;
+    uint64_t free = g_free.load(std::memory_order_relaxed);
+    while (free != 0) {
+        const int i = __builtin_ctzll(free);
+        if (g_free.compare_exchange_weak(free, free & ~(1ull << i), std::memory_order_acquire)) {
+            slot_ = i;
+            return;
+        }
+    }
+}
+
+HostResult::~HostResult()
+{
+    if (slot_ >= 0) g_free.fetch_or(1ull << slot_, std::memory_order_release);
+}
+
+double *HostResult::data() const { return g_pinned + slot_ * kHostResult; }
+
+hipError_t wait_result(double *out, int n, const double *result, const HostResult &host, hipStream_t st)
+{
+    if (!host) {
+        const hipError_t e = hipMemcpyAsync(out, result, n * sizeof(double), hipMemcpyDeviceToHost, st);
+        if (e != hipSuccess) return e;
+    }
+    const hipError_t e = hipStreamSynchronize(st);
+    if (e == hipSuccess && host) std::memcpy(out, host.data(), n * sizeof(double));
+    return e;
 }
 
 }  // namespace mcmie

@@ -23,13 +23,14 @@
 // memory.  One lane that walked over the blocks' sums and the annuli took 200
 // of the 263 us the call took; now the kernels take 4.6 and 19.4 us (about 5 of
 // them the annulus adds in LDS, 6 the last block's part) and the call 57, the
-// rest of which is launches and the wait.
+// rest of which is launches and the wait (48 since the results need no copy).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
 #include <cstdint>
 
 #include "common.hpp"
+#include "wave.hpp"
 
 namespace mcmie {
 namespace {
@@ -53,29 +54,10 @@ struct MetricsArgs {
     double *blk_sum;                 // grid x kPix
     unsigned long long *rad;         // n_r x 4: pixels, a, b, c (fixed point)
     unsigned long long *done;        // blocks that have finished their sums (the word of out[11], written last)
-    double *out;                     // MC_METRICS_N
+    double *out;                     // MC_METRICS_N (device)
+    double *result;                  // where the measures go: out, or pinned host memory
     double *profiles;                // optional: 4 x n_r (a, b, c profiles, pixel counts)
 };
-
-// v with its lanes permuted within rows of 16 (a DPP control).
-template <int CTRL>
-__device__ __forceinline__ double row_move(double v)
-{
-    const int2 x = __builtin_bit_cast(int2, v);
-    return __builtin_bit_cast(double, int2{__builtin_amdgcn_mov_dpp(x.x, CTRL, 0xF, 0xF, true),
-                                           __builtin_amdgcn_mov_dpp(x.y, CTRL, 0xF, 0xF, true)});
-}
-// op over each row of 16 lanes, in every lane: exchanges between neighbours,
-// pairs, the halves of 8 and of 16 (quad_perm 1032 and 2301, row_half_mirror,
-// row_mirror).
-template <class Op>
-__device__ __forceinline__ double row_reduce(double v, Op op)
-{
-    v = op(v, row_move<0xB1>(v));
-    v = op(v, row_move<0x4E>(v));
-    v = op(v, row_move<0x141>(v));
-    return op(v, row_move<0x140>(v));
-}
 
 // op over N <= kWaves values of every lane of the block, in a fixed order: over
 // the rows of each wave without touching LDS, then wave i over the 64 rows of
@@ -138,7 +120,7 @@ __global__ __launch_bounds__(kThreads) void metrics_max(MetricsArgs m)
 }
 
 // The totals, profiles and measures, by all lanes of one block.
-__device__ void metrics_final(const MetricsArgs &m, double *s, double *s_prof)
+__device__ void metrics_final(const MetricsArgs &m, const double (&top)[3], double *s, double *s_prof)
 {
     const int tid = threadIdx.x;
     // Radial profiles and the measures over non-empty annuli: squared errors
@@ -189,17 +171,18 @@ __device__ void metrics_final(const MetricsArgs &m, double *s, double *s_prof)
     block_sum(c, s);
     if (tid != 0) return;
     const double n = (double)m.n_pix;
-    m.out[0] = sqrt(t[5] / n);
+    m.result[0] = sqrt(t[5] / n);
     const double cov = t[4] - t[0] * t[1] / n, vx = t[2] - t[0] * t[0] / n, vy = t[3] - t[1] * t[1] / n;
     const double den = sqrt(vx * vy);
-    m.out[1] = den > 0.0 ? cov / den : NAN;
+    m.result[1] = den > 0.0 ? cov / den : NAN;
 #pragma unroll
-    for (int z = 0; z < 3; ++z) m.out[2 + z] = q[3 + z] > 0 ? sqrt(q[z] / q[3 + z]) : 0.0;
+    for (int z = 0; z < 3; ++z) m.result[2 + z] = q[3 + z] > 0 ? sqrt(q[z] / q[3 + z]) : 0.0;
     const double rden = sqrt(c[1] * c[2]);
-    m.out[5] = rden > 0.0 ? c[0] / rden : NAN;
-    m.out[6] = (double)m.n_r;
-    m.out[10] = m.c ? (used > 0 ? q[9] / used : NAN) : NAN;
-    m.out[11] = n;
+    m.result[5] = rden > 0.0 ? c[0] / rden : NAN;
+    m.result[6] = (double)m.n_r;
+    for (int i = 0; i < 3; ++i) m.result[7 + i] = top[i];
+    m.result[10] = m.c ? (used > 0 ? q[9] / used : NAN) : NAN;
+    m.result[11] = n;
 }
 
 __global__ __launch_bounds__(kThreads) void metrics_sums(MetricsArgs m)
@@ -213,11 +196,6 @@ __global__ __launch_bounds__(kThreads) void metrics_sums(MetricsArgs m)
         for (int j = 0; j < 3; ++j) top[j] = fmax(top[j], m.blk_max[3 * g + j]);
     for (int i = tid; i < 4 * m.n_r; i += kThreads) s_rad[i] = 0ull;
     block_max(top, s);   // (also the barrier after the clearing)
-    if (blockIdx.x == 0 && tid == 0) {
-        m.out[7] = top[0];
-        m.out[8] = top[1];
-        m.out[9] = top[2];
-    }
     const double ia = top[0] > 0.0 ? 1.0 / top[0] : 0.0, ib = top[1] > 0.0 ? 1.0 / top[1] : 0.0;
     const double ic = top[2] > 0.0 ? 1.0 / top[2] : 0.0;
     double acc[kPix] = {};
@@ -279,7 +257,7 @@ __global__ __launch_bounds__(kThreads) void metrics_sums(MetricsArgs m)
     __syncthreads();
     if (!s_last) return;
     __threadfence();
-    metrics_final(m, s, (double *)s_rad);
+    metrics_final(m, top, s, (double *)s_rad);
 }
 
 uint64_t grid_for(uint64_t n_pix)
@@ -339,6 +317,8 @@ extern "C" int mc_image_metrics(const double *a, const double *b, const double *
     m.rad = (unsigned long long *)(w + 3 * g + kPix * g);
     m.out = w + 3 * g + kPix * g + 4ull * n_r;
     m.done = (unsigned long long *)(m.out + 11);
+    HostResult host;
+    m.result = host ? host.data() : m.out;
     m.profiles = profiles;
     while (m.tile_bits < (uint32_t)kTileBits && (1 << m.tile_bits) < nx) ++m.tile_bits;
     const uint32_t tile_h = (uint32_t)kTileRows * (kThreads >> m.tile_bits);
@@ -351,7 +331,6 @@ extern "C" int mc_image_metrics(const double *a, const double *b, const double *
     hipLaunchKernelGGL(metrics_max, dim3((unsigned)g), dim3(kThreads), 0, st, m);
     hipLaunchKernelGGL(metrics_sums, dim3((unsigned)g), dim3(kThreads), lds, st, m);
     MC_HIP_CHECK(hipGetLastError());
-    MC_HIP_CHECK(hipMemcpyAsync(out, m.out, MC_METRICS_N * sizeof(double), hipMemcpyDeviceToHost, st));
-    MC_HIP_CHECK(hipStreamSynchronize(st));
+    MC_HIP_CHECK(wait_result(out, MC_METRICS_N, m.result, host, st));
     return MC_OK;
 }

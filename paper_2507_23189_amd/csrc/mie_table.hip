@@ -107,6 +107,7 @@ struct MieArgs {
     float *inv_cdf;
     double *phase, *cdf, *coef;
     double *result;          // q_ext, q_sca, g, n_terms
+    double *host_result;     // the same again, pinned host memory (optional)
     double *work;            // n_angles: P(theta_j) sin(theta_j), from the phase kernel to the inverse kernel
 };
 
@@ -519,6 +520,15 @@ __device__ __forceinline__ void phase_split(int na, int N, double scale, const c
     if (first && !(tid & 1) && j < na) put_phase(j, th, scale * plus(half, s_half[at]), phase_out, ang);
 }
 
+__device__ __forceinline__ void put_result(double *to, double q_ext, double q_sca, double g, double n_terms)
+{
+    if (!to) return;
+    to[0] = q_ext;
+    to[1] = q_sca;
+    to[2] = g;
+    to[3] = n_terms;
+}
+
 // Steps 1-2 for one size: workgroup b runs the series, workgroup 0 writes the
 // scalar results (and the coefficients if asked), and lane t evaluates angle
 // j = 256 b + t into work[j] = P sin(theta_j) (and phase[j] = P if asked).
@@ -539,10 +549,8 @@ __global__ __launch_bounds__(kPhaseThreads) void mie_phase_kernel(MieArgs a)
     mie_series_block(x, a.m_re, a.m_im, N, a.n_start, s_a, s_b, s_rec, s_fac, s_red, s_sums);
     if (blockIdx.x == 0) {
         if (tid == 0) {
-            a.result[0] = s_sums[0];
-            a.result[1] = s_sums[1];
-            a.result[2] = s_sums[2];
-            a.result[3] = (double)N;
+            put_result(a.result, s_sums[0], s_sums[1], s_sums[2], (double)N);
+            put_result(a.host_result, s_sums[0], s_sums[1], s_sums[2], (double)N);
         }
         if (a.coef) {
             for (int n = tid; n < N; n += kPhaseThreads) {
@@ -661,6 +669,7 @@ struct PolyArgs {
     double *ang;                   // n_angles: P(theta_j) sin(theta_j) of the mixture
     double *phase;
     double *result;                // q_ext, q_sca (over geo_median), g, max N
+    double *host_result;           // the same again, pinned host memory (optional)
 };
 
 // Workgroup (s, k) runs bin k's series (workgroup (0, k) writes its scalars to
@@ -697,44 +706,55 @@ __global__ __launch_bounds__(kPhaseThreads) void mie_bin_kernel(PolyArgs a)
 // bin order, and workgroup 0 writes the scalar results.
 __global__ __launch_bounds__(kPhaseThreads) void mie_mix_kernel(PolyArgs a)
 {
-    __shared__ double s_sca;
+    __shared__ double s_sca, s_bins[4 * MC_MAX_BINS], s_c[MC_MAX_BINS];
     const int tid = threadIdx.x;
+    static_assert(4 * MC_MAX_BINS <= kPhaseThreads, "a lane per bin value");
+    if (tid < 4 * a.n_bins) s_bins[tid] = a.bins[tid];
+    if (tid < a.n_bins) s_c[tid] = a.c[tid];
+    const int na = a.n_angles;
+    const int j = blockIdx.x * kPhaseThreads + tid;
+    const bool in = j < na;
+    const double *row = a.rows + (in ? j : 0);
+    // The rows added in bin order, their loads issued 32 at a time (8 at a time,
+    // and bins read by the lane that adds them, took 10.4 us at 64 bins).
+    constexpr int kRows = 32;
+    double v[kRows];
+    auto read = [&](int k0) {
+#pragma unroll
+        for (int u = 0; u < kRows; ++u) v[u] = row[(uint64_t)min(k0 + u, a.n_bins - 1) * na];
+    };
+    read(0);
+    __syncthreads();
     if (tid == 0) {
         // Number-averaged cross-sections and the C_sca-weighted asymmetry, in bin order.
         double ext = 0.0, sca = 0.0, gs = 0.0, nmax = 0.0;
 #pragma unroll 8
         for (int k = 0; k < a.n_bins; ++k) {
-            const double q_ext = a.bins[4 * k + 0], q_sca = a.bins[4 * k + 1];
-            const double g = a.bins[4 * k + 2], n = a.bins[4 * k + 3];
-            ext += a.c[k] * q_ext;
-            sca += a.c[k] * q_sca;
-            gs += a.c[k] * q_sca * g;
+            const double q_ext = s_bins[4 * k + 0], q_sca = s_bins[4 * k + 1];
+            const double g = s_bins[4 * k + 2], n = s_bins[4 * k + 3];
+            ext += s_c[k] * q_ext;
+            sca += s_c[k] * q_sca;
+            gs += s_c[k] * q_sca * g;
             nmax = fmax(nmax, n);
         }
         s_sca = sca;
         if (blockIdx.x == 0) {
-            a.result[0] = ext / a.geo_median;
-            a.result[1] = sca / a.geo_median;
-            a.result[2] = gs / sca;
-            a.result[3] = nmax;
+            put_result(a.result, ext / a.geo_median, sca / a.geo_median, gs / sca, nmax);
+            put_result(a.host_result, ext / a.geo_median, sca / a.geo_median, gs / sca, nmax);
         }
     }
-    __syncthreads();
-    const int na = a.n_angles;
-    const int j = blockIdx.x * kPhaseThreads + tid;
-    if (j >= na) return;
-    const double dth = M_PI / (double)(na - 1);
-    // The rows added in bin order, their loads issued eight at a time.
     double mix = 0.0;
-    int k = 0;
-    for (; k + 8 <= a.n_bins; k += 8) {
-        double v[8];
+    for (int k0 = 0;;) {
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = a.rows[(uint64_t)(k + u) * na + j];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) mix += v[u];
+        for (int u = 0; u < kRows; ++u)
+            if (k0 + u < a.n_bins) mix += v[u];
+        k0 += kRows;
+        if (k0 >= a.n_bins) break;
+        read(k0);
     }
-    for (; k < a.n_bins; ++k) mix += a.rows[(uint64_t)k * na + j];
+    __syncthreads();
+    if (!in) return;
+    const double dth = M_PI / (double)(na - 1);
     const double P = mix * (1.0 / s_sca);
     if (a.phase) a.phase[j] = P;
     a.ang[j] = P * sin_0_pi((double)j * dth);
@@ -780,15 +800,17 @@ int prepare_table(const mie_spec_t *spec, const mie_table_t *table, MieArgs *arg
                         (int)std::ceil(8.0 * std::cbrt(mx_abs));
 
     *args = MieArgs{x, m_re, m_im, n_terms, n_start, s.n_angles, s.n_cdf,
-                    table->inv_cdf, table->phase, table->cdf, table->coef, nullptr, nullptr};
+                    table->inv_cdf, table->phase, table->cdf, table->coef, nullptr, nullptr, nullptr};
     return MC_OK;
 }
 
 // Launch the prepared table kernels on `st`: scalar results to `result`,
 // the angle grid through `work` (both device).
-int launch_table(MieArgs args, mie_table_t *table, hipStream_t st, double *result, double *work)
+int launch_table(MieArgs args, mie_table_t *table, hipStream_t st, double *result, double *work,
+                 double *host_result = nullptr)
 {
     args.result = result;
+    args.host_result = host_result;
     args.work = work;
     const int g_phase = (args.n_angles + kAngles - 1) / kAngles;
     const int g_inv = (args.n_cdf + kInvThreads - 1) / kInvThreads;
@@ -844,26 +866,59 @@ int scratch_buffers(const mie_table_t *table, std::unique_lock<std::mutex> &lock
 // three-term recurrence h_{j+1} = sqrt(2/(j+1)) t h_j - sqrt(j/(j+1)) h_{j-1}
 // from h_0 = pi^(-1/4), together with sum_{j<n} h_j(t)^2.
 struct HermiteCoef {
+    double h0;                               // pi^(-1/4)
     double a[MC_MAX_BINS], b[MC_MAX_BINS];   // sqrt(2 / (j + 1)), sqrt(j / (j + 1))
 };
 
-void hermite_orthonormal(const HermiteCoef &c, int n, double t, double *h_n, double *sum_sq)
+// kLanes arguments at once, as independent chains that fill the vector units
+// (one argument's chain of n steps leaves them idle).
+constexpr int kLanes = 8;
+struct Lanes {
+    double v[kLanes];
+};
+
+template <bool SUM>
+Lanes hermite_lanes(const HermiteCoef &c, int n, const Lanes &t, Lanes *sum_sq, Lanes *h_last)
 {
-    double h_prev = 0.0, h = std::pow(M_PI, -0.25), s = 0.0;
-    for (int j = 0; j < n; ++j) {
-        s += h * h;
-        const double h_next = c.a[j] * t * h - c.b[j] * h_prev;
-        h_prev = h;
-        h = h_next;
+    typedef double Pair __attribute__((vector_size(16)));
+    constexpr int kPairs = kLanes / 2;
+    Pair x[kPairs], h_prev[kPairs], h[kPairs], s[kPairs];
+    for (int l = 0; l < kPairs; ++l) {
+        x[l] = Pair{t.v[2 * l], t.v[2 * l + 1]};
+        h_prev[l] = s[l] = Pair{0.0, 0.0};
+        h[l] = Pair{c.h0, c.h0};
     }
-    *h_n = h;
-    *sum_sq = s;
+    for (int j = 0; j < n; ++j) {
+        const Pair a = {c.a[j], c.a[j]}, b = {c.b[j], c.b[j]};
+#pragma unroll
+        for (int l = 0; l < kPairs; ++l) {
+            if (SUM) s[l] += h[l] * h[l];
+            const Pair h_next = a * x[l] * h[l] - b * h_prev[l];
+            h_prev[l] = h[l];
+            h[l] = h_next;
+        }
+    }
+    Lanes out;
+    for (int l = 0; l < kLanes; ++l) {
+        out.v[l] = h[l / 2][l & 1];
+        if (SUM) sum_sq->v[l] = s[l / 2][l & 1];
+        if (h_last) h_last->v[l] = h_prev[l / 2][l & 1];   // h_{n-1}
+    }
+    return out;
+}
+Lanes hermite_orthonormal(const HermiteCoef &c, int n, const Lanes &t, Lanes *sum_sq, Lanes *h_last = nullptr)
+{
+    return sum_sq ? hermite_lanes<true>(c, n, t, sum_sq, h_last) : hermite_lanes<false>(c, n, t, sum_sq, h_last);
 }
 
 // Gauss-Hermite rule for the weight exp(-t^2): the nodes are the n roots of
 // h_n, all inside (-sqrt(2n+1), sqrt(2n+1)); each is bracketed by a sign
 // change on a grid far finer than the root spacing and bisected to machine
 // precision.  The weights are the Christoffel numbers 1 / sum_{j<n} h_j(t)^2.
+//
+// The grid's cells are found from every kStride-th point, then by halving, and
+// kLanes roots are refined at a time: 64 nodes from the whole grid and one by one
+// took 370 of the 430 us of mie_table_build_poly; this takes about 40 of its 84.
 int gauss_hermite(int n, double *t, double *w)
 {
     if (n == 1) {
@@ -872,49 +927,122 @@ int gauss_hermite(int n, double *t, double *w)
         return MC_OK;
     }
     HermiteCoef c;
+    c.h0 = std::pow(M_PI, -0.25);
     for (int j = 0; j < n; ++j) {
         c.a[j] = std::sqrt(2.0 / (j + 1));
         c.b[j] = std::sqrt((double)j / (j + 1));
     }
-    // Grid step 2R / (40 n) < 0.04 for n <= 64, well below the smallest
-    // spacing of neighbouring roots (about pi / sqrt(2n + 1) > 0.27).
+    // The grid step 2R / (40 n) is below a seventeenth of the smallest spacing
+    // of neighbouring roots (about pi / sqrt(2n + 1)): no kStride cells hold two.
+    constexpr int kStride = 8;
     const double R = std::sqrt(2.0 * n + 1.0) + 1.0;
     const int steps = 40 * n;
+    auto grid = [&](int i) { return -R + 2.0 * R * (double)i / steps; };
+    auto at_grid = [&](const int *i, double *h) {   // h_n at kLanes grid points
+        Lanes x;
+        for (int l = 0; l < kLanes; ++l) x.v[l] = i[l] == 0 ? -R : grid(i[l]);
+        const Lanes v = hermite_orthonormal(c, n, x, nullptr);
+        for (int l = 0; l < kLanes; ++l) h[l] = v.v[l];
+    };
+    // Strides (at[k] - kStride, at[k]] with a root: the sign of h_n changes over
+    // them, or h_n is 0 at their end (it then has the other sign after it).
+    static_assert(40 % kStride == 0, "whole strides");
+    int at[MC_MAX_BINS + kLanes] = {0};
+    bool neg[MC_MAX_BINS + kLanes] = {false};   // h_n < 0 before the root
     int found = 0;
-    double t_prev = -R, h_prev, s;
-    hermite_orthonormal(c, n, t_prev, &h_prev, &s);
-    for (int i = 1; i <= steps && found < n; ++i) {
-        const double ti = -R + 2.0 * R * (double)i / steps;
-        double hi;
-        hermite_orthonormal(c, n, ti, &hi, &s);
-        if ((h_prev < 0.0) != (hi < 0.0) || hi == 0.0) {
-            double lo = t_prev, up = ti, h_lo = h_prev;
-            for (int it = 0; it < 200 && hi != 0.0; ++it) {
-                const double mid = 0.5 * (lo + up);
-                if (mid <= lo || mid >= up) break;
-                double hm;
-                hermite_orthonormal(c, n, mid, &hm, &s);
-                if ((hm < 0.0) == (h_lo < 0.0)) {
-                    lo = mid;
-                    h_lo = hm;
-                } else {
-                    up = mid;
-                }
+    bool before = false;
+    for (int i0 = 0; i0 <= steps && found < n; i0 += kLanes * kStride) {
+        int i[kLanes];
+        double h[kLanes];
+        for (int l = 0; l < kLanes; ++l) i[l] = std::min(i0 + l * kStride, steps);
+        at_grid(i, h);
+        for (int l = 0; l < kLanes && i0 + l * kStride <= steps && found < n; ++l) {
+            if (i[l] == 0) {
+                before = h[l] < 0.0;
+                continue;
             }
-            const double root = hi == 0.0 ? ti : 0.5 * (lo + up);
-            double hr;
-            hermite_orthonormal(c, n, root, &hr, &s);
-            t[found] = root;
-            w[found] = 1.0 / s;
-            ++found;
-            // Step past an exact zero so it is not found twice.
-            hermite_orthonormal(c, n, ti, &hi, &s);
-            if (hi == 0.0) hi = -h_prev;
+            if ((h[l] < 0.0) != before || h[l] == 0.0) {
+                at[found] = i[l];
+                neg[found] = before;
+                ++found;
+                before = !before;
+            }
         }
-        t_prev = ti;
-        h_prev = hi;
     }
-    return found == n ? MC_OK : fail(MC_EINVAL, "Gauss-Hermite: found %d of %d nodes", found, n);
+    if (found != n) return fail(MC_EINVAL, "Gauss-Hermite: found %d of %d nodes", found, n);
+    for (int r0 = 0; r0 < n; r0 += kLanes) {
+        // The stride's first point at or past the root, by halving.  (Selects, not
+        // branches: which half holds a root cannot be predicted.)
+        int lo_i[kLanes], up_i[kLanes];
+        bool minus[kLanes];
+        double h[kLanes], h_up[kLanes];
+        for (int l = 0; l < kLanes; ++l) {
+            const int r = std::min(r0 + l, n - 1);
+            lo_i[l] = at[r] - kStride;
+            up_i[l] = at[r];
+            minus[l] = neg[r];
+        }
+        at_grid(up_i, h_up);
+        for (int width = kStride; width > 1; width /= 2) {
+            int mid[kLanes];
+            for (int l = 0; l < kLanes; ++l) mid[l] = (lo_i[l] + up_i[l]) / 2;
+            at_grid(mid, h);
+            for (int l = 0; l < kLanes; ++l) {
+                const bool past = ((h[l] < 0.0) != minus[l]) | (h[l] == 0.0);
+                up_i[l] = past ? mid[l] : up_i[l];
+                h_up[l] = past ? h[l] : h_up[l];
+                lo_i[l] = past ? lo_i[l] : mid[l];
+            }
+        }
+        // The cell, by halving to neighbouring doubles (a root on the grid is one).
+        // Newton's steps (h_n' = sqrt(2n) h_{n-1}; from a cell's middle the error
+        // falls as 3e-4, 8e-7, 7e-12, rounding) say where the root is, so that
+        // h_n itself is needed only within 1e-12 of it: beyond, |h_n| is a hundred
+        // times what its recurrence rounds and has the sign of its side.
+        Lanes lo, up, mid, near;
+        for (int l = 0; l < kLanes; ++l) {
+            lo.v[l] = h_up[l] == 0.0 ? grid(up_i[l]) : (lo_i[l] == 0 ? -R : grid(lo_i[l]));
+            up.v[l] = grid(up_i[l]);
+            near.v[l] = 0.5 * (lo.v[l] + up.v[l]);
+        }
+        const double slope = std::sqrt(2.0 * n);
+        for (int it = 0; it < 4; ++it) {
+            Lanes last;
+            const Lanes hn = hermite_orthonormal(c, n, near, nullptr, &last);
+            for (int l = 0; l < kLanes; ++l) near.v[l] -= hn.v[l] / (slope * last.v[l]);
+        }
+        // (A step that left the cell would be no guide: every sign is then taken
+        // from h_n.)
+        double margin[kLanes];
+        for (int l = 0; l < kLanes; ++l)
+            margin[l] = near.v[l] > lo.v[l] && near.v[l] < up.v[l] ? 1e-12 * std::max(1.0, std::fabs(near.v[l])) : INFINITY;
+        for (int it = 0; it < 200; ++it) {
+            int open = 0, ask = 0;
+            bool inside[kLanes];
+            for (int l = 0; l < kLanes; ++l) {
+                mid.v[l] = 0.5 * (lo.v[l] + up.v[l]);
+                inside[l] = (mid.v[l] > lo.v[l]) & (mid.v[l] < up.v[l]);
+                open |= inside[l];
+                ask |= inside[l] & !(std::fabs(mid.v[l] - near.v[l]) > margin[l]);
+            }
+            if (!open) break;
+            Lanes hm{};
+            if (ask) hm = hermite_orthonormal(c, n, mid, nullptr);
+            for (int l = 0; l < kLanes; ++l) {
+                const bool below = ask ? (hm.v[l] < 0.0) == minus[l] : mid.v[l] < near.v[l];
+                lo.v[l] = (inside[l] & below) ? mid.v[l] : lo.v[l];
+                up.v[l] = (inside[l] & !below) ? mid.v[l] : up.v[l];
+            }
+        }
+        Lanes root, sum;
+        for (int l = 0; l < kLanes; ++l) root.v[l] = h_up[l] == 0.0 ? up.v[l] : 0.5 * (lo.v[l] + up.v[l]);
+        (void)hermite_orthonormal(c, n, root, &sum);
+        for (int l = 0; l < kLanes && r0 + l < n; ++l) {
+            t[r0 + l] = root.v[l];
+            w[r0 + l] = 1.0 / sum.v[l];
+        }
+    }
+    return MC_OK;
 }
 
 int lognormal_bins(double median_um, double sigma_ln, int n, double *d, double *p)
@@ -994,6 +1122,8 @@ extern "C" int mie_table_build_poly(const mie_spec_t *spec, const mie_poly_t *po
     a.phase = table->phase;
     std::unique_lock<std::mutex> lock(g_scratch_mu, std::defer_lock);
     if (int rc = scratch_buffers(table, lock, &a.result, nullptr, who)) return rc;
+    const HostResult host;
+    a.host_result = host ? host.data() : nullptr;
     hipStream_t st = (hipStream_t)stream;
     const int slices = (s.n_angles + kPhaseThreads - 1) / kPhaseThreads;
     hipLaunchKernelGGL(mie_bin_kernel, dim3(slices, q.n_bins), dim3(kPhaseThreads), 0, st, a);
@@ -1002,8 +1132,7 @@ extern "C" int mie_table_build_poly(const mie_spec_t *spec, const mie_poly_t *po
                        (const double *)a.ang, s.n_angles, s.n_cdf, table->inv_cdf, table->cdf);
     MC_HIP_CHECK(hipGetLastError());
     double res[4];
-    MC_HIP_CHECK(hipMemcpyAsync(res, a.result, sizeof res, hipMemcpyDeviceToHost, st));
-    MC_HIP_CHECK(hipStreamSynchronize(st));
+    MC_HIP_CHECK(wait_result(res, 4, a.result, host, st));
     table->x = med.x;
     table->m_rel_re = med.m_re;
     table->m_rel_im = med.m_im;
@@ -1023,10 +1152,10 @@ extern "C" int mie_table_build(const mie_spec_t *spec, mie_table_t *table, void 
     double *result = nullptr, *work = nullptr;
     std::unique_lock<std::mutex> lock(g_scratch_mu, std::defer_lock);
     if (int rc = scratch_buffers(table, lock, &result, &work, "mie_table_build")) return rc;
-    if (int rc = launch_table(args, table, st, result, work)) return rc;
+    const HostResult host;
+    if (int rc = launch_table(args, table, st, result, work, host ? host.data() : nullptr)) return rc;
     double res[4];
-    MC_HIP_CHECK(hipMemcpyAsync(res, result, sizeof res, hipMemcpyDeviceToHost, st));
-    MC_HIP_CHECK(hipStreamSynchronize(st));
+    MC_HIP_CHECK(wait_result(res, 4, result, host, st));
     set_scalars(table, *spec, res);
     return MC_OK;
 }

@@ -2213,7 +2213,8 @@ extern "C" int mc_grad(const mc_medium_t *medium, const mc_geometry_t *geometry,
                     (unsigned long long)((kWsScalarWords + 4) * 8));
     const double mu_s = coef.mu_sca;
     hipStream_t st = (hipStream_t)stream;
-    double *dots = (double *)t.workspace + 24;    // scalar words 24..27
+    const HostResult host;
+    double *dots = host ? host.data() : (double *)t.workspace + 24;    // scalar words 24..27
     const uint64_t n = (uint64_t)det.side_nx * det.side_ny;
     // The blocks' partials go after the scalar words, where mc_simulate keeps
     // its image copies (consumed by then): one block per 8192 pixels, at most
@@ -2228,8 +2229,7 @@ extern "C" int mc_grad(const mc_medium_t *medium, const mc_geometry_t *geometry,
                        d2loss_dside2 != nullptr, d2loss_uniform, (const double *)t.scalars, dots);
     MC_HIP_CHECK(hipGetLastError());
     double d[4];
-    MC_HIP_CHECK(hipMemcpyAsync(d, dots, sizeof d, hipMemcpyDeviceToHost, st));
-    MC_HIP_CHECK(hipStreamSynchronize(st));
+    MC_HIP_CHECK(wait_result(d, 4, dots, host, st));
     // D = M_k / mu_s - M_L (mu_sca), -M_L (mu_abs); Q likewise from the w^2 moments.
     const double gq_s = d[2] / mu_s - d[3], gq_a = -d[3];
     out_grad[0] = (d[0] / mu_s - d[1]) - gq_s;
