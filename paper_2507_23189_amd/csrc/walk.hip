@@ -982,38 +982,28 @@ void walk_kernel(WalkArgs a)
             a.log_count[i * gridDim.x + blockIdx.x] = min(s_lcnt[i], a.log_cap);
 }
 
-// Zero the workspace words [0, n_ws) and [ws2, ws2 + n_ws2), and the outputs
-// unless accumulating.  (Fill kernels,
-// not memset, so the sequence stays valid under stream capture.)
-__global__ void init_kernel(unsigned long long *ws, size_t n_ws, unsigned long long *ws2, size_t n_ws2,
-                            unsigned long long *side, unsigned long long *trans,
-                            unsigned long long *side_w2, unsigned long long *trans_w2, size_t n_side, size_t n_trans,
-                            double *scalars, size_t n_scalars, int32_t *rec_i, float *rec_f, size_t n_rec,
-                            double *side_wk,
-                            double *side_wl, double *side_w2k, double *side_w2l, int zero_all)
+// Zero the workspace words [0, n_ws) and [ws2, ws2 + n_ws2) and, unless
+// accumulating, the outputs that the walk itself writes (path moments, records);
+// the finalize writes the others whole.  (A fill kernel, not memset, so the
+// sequence stays valid under stream capture.)
+__global__ void init_kernel(unsigned long long *ws, size_t n_ws, unsigned long long *ws2, size_t n_ws2, size_t n_side,
+                            int32_t *rec_i, float *rec_f, size_t n_rec, double *side_wk, double *side_wl,
+                            double *side_w2k, double *side_w2l, int zero_all)
 {
     const size_t stride = (size_t)gridDim.x * blockDim.x;
     const size_t t0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     for (size_t i = t0; i < n_ws; i += stride) ws[i] = 0ull;
     for (size_t i = t0; i < n_ws2; i += stride) ws2[i] = 0ull;
     if (!zero_all) return;
-    for (size_t i = t0; i < n_side; i += stride) {
-        side[i] = 0ull;                 // +0.0 and int64 0 share the bit pattern
-        if (side_w2) side_w2[i] = 0ull;
-        if (side_wk) {
+    if (side_wk)
+        for (size_t i = t0; i < n_side; i += stride) {
             side_wk[i] = 0.0;
             side_wl[i] = 0.0;
+            if (side_w2k) {
+                side_w2k[i] = 0.0;
+                side_w2l[i] = 0.0;
+            }
         }
-        if (side_w2k) {
-            side_w2k[i] = 0.0;
-            side_w2l[i] = 0.0;
-        }
-    }
-    for (size_t i = t0; i < n_trans; i += stride) {
-        trans[i] = 0ull;
-        if (trans_w2) trans_w2[i] = 0ull;
-    }
-    for (size_t i = t0; i < n_scalars; i += stride) scalars[i] = 0.0;
     for (size_t i = t0; i < (size_t)MC_REC_I_N * n_rec; i += stride) rec_i[i] = (i / n_rec == MC_REC_I_FACE) ? -1 : 0;
     for (size_t i = t0; i < (size_t)MC_REC_F_N * n_rec; i += stride) rec_f[i] = 0.f;
 }
@@ -1101,110 +1091,120 @@ __global__ __launch_bounds__(1024) void log_bin(const unsigned long long *log, c
 }
 
 // Sum the n_copies fixed-point copies of every pixel (integer adds, so the
-// order is immaterial) and add them to the caller's images, as int64 (FIX) or
-// converted to double.  Weight sums of the +x and +z images also give those
-// faces' totals.
+// order is immaterial) and write them to the caller's images, or add them
+// (ADD), as int64 (FIX) or converted to double.
 // One medium per blockIdx.y: its pixels are keys [y * n_pix, (y + 1) * n_pix)
 // of copies that hold n_total keys each; its images start at y * n_side and
-// y * (n_pix - n_side) in the outputs and its face totals are at
-// face_side / face_trans + y * face_stride.
+// y * (n_pix - n_side) in the outputs.  blockIdx.z = 1 takes the squared
+// weights.
 //
 // Unscattered first-step exits were only counted (workspace word kWsBallistic
 // of each medium); the beam pixel (word kWsBeamKey) gets count x ball_w.
-template <bool FIX>
-__global__ __launch_bounds__(256) void finalize_images(const unsigned long long *copies, int n_copies, uint64_t n_total,
-                                                       uint64_t n_pix, uint32_t n_side, void *side, void *trans,
-                                                       unsigned long long *face_side, unsigned long long *face_trans,
-                                                       uint64_t face_stride, const unsigned long long *ws_scal,
-                                                       unsigned long long ball_w)
+//
+// A block takes kFinBlock pixels of one image.  Their weights' sum, its share of
+// the +x or +z face's total, replaces its first pixel in copy 0 (which no other
+// block reads) for finalize_scalars to add up: an atomic per block on one word
+// took 12 ns each, one after the other, 12 of the 21 us at 512 x 512.
+constexpr int kFinThreads = 256, kFinPix = 4, kFinBlock = kFinThreads * kFinPix;
+struct FinArgs {
+    unsigned long long *copies[2];     // of the weights and of their squares
+    void *side[2], *trans[2];
+    unsigned long long ball_w[2];
+    int n_copies;
+    uint64_t n_total;
+    uint32_t n_pix, n_side;
+    const unsigned long long *ws_scal;
+    double *scalars;
+};
+
+template <bool FIX, bool ADD>
+__global__ __launch_bounds__(kFinThreads) void finalize_images(FinArgs a)
 {
     const uint64_t inst = blockIdx.y;
-    const uint64_t key0 = inst * n_pix;
-    side = FIX ? (void *)((long long *)side + inst * n_side) : (void *)((double *)side + inst * n_side);
-    trans = FIX ? (void *)((long long *)trans + inst * (n_pix - n_side))
-                : (void *)((double *)trans + inst * (n_pix - n_side));
-    if (face_side) {
-        face_side += inst * face_stride;
-        face_trans += inst * face_stride;
+    const int z = blockIdx.z;
+    const uint32_t side_blocks = (a.n_side + kFinBlock - 1) / kFinBlock;
+    const bool is_side = blockIdx.x < side_blocks;
+    const uint32_t first = is_side ? blockIdx.x * kFinBlock : a.n_side + (blockIdx.x - side_blocks) * kFinBlock;
+    // (differences, which stay below 2^32 where an index past the end may not)
+    const uint32_t n_here = min((is_side ? a.n_side : a.n_pix) - first, (uint32_t)kFinBlock);
+    unsigned long long *copies = a.copies[z] + inst * a.n_pix;
+    long long *out = (long long *)(is_side ? a.side[z] : a.trans[z]) +
+                     (is_side ? inst * a.n_side : inst * (a.n_pix - a.n_side) - a.n_side);
+    const unsigned long long beam_key = a.ws_scal[kWsBeamKey];
+    const unsigned long long beam_v = a.ws_scal[inst * kWsScalarWords + kWsBallistic] * a.ball_w[z];
+    // The loads of all copies and outputs are issued before any is used.
+    unsigned long long part[kFinPix][kCopies];
+    long long prev[kFinPix];
+#pragma unroll
+    for (int u = 0; u < kFinPix; ++u) {
+        const uint32_t k = u * kFinThreads + threadIdx.x, i = first + k;
+        const bool in = k < n_here;
+#pragma unroll
+        for (int c = 0; c < kCopies; ++c) part[u][c] = in && c < a.n_copies ? copies[(uint64_t)c * a.n_total + i] : 0ull;
+        prev[u] = ADD && in ? out[i] : 0ll;   // the output's bits (int64, or a double's)
     }
-    unsigned long long sum_side = 0ull, sum_trans = 0ull;
-    const unsigned long long beam_key = ws_scal[kWsBeamKey];
-    const unsigned long long beam_v = ws_scal[inst * kWsScalarWords + kWsBallistic] * ball_w;
-    // Each thread takes kFinPix pixels a grid-stride apart per pass and issues
-    // the loads of all their copies and outputs before using any.
-    constexpr int kFinPix = 4;
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t i0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i0 < n_pix; i0 += kFinPix * stride) {
-        unsigned long long part[kFinPix][kCopies];
-        long long prev[kFinPix];
+    unsigned long long sum = 0ull;
 #pragma unroll
-        for (int u = 0; u < kFinPix; ++u) {
-            const uint64_t i = i0 + u * stride;
-            const bool in = i < n_pix, is_side = i < n_side;
-            const uint64_t j = is_side ? i : i - n_side;
-            long long *out = (long long *)(is_side ? side : trans);
+    for (int u = 0; u < kFinPix; ++u) {
+        const uint32_t k = u * kFinThreads + threadIdx.x, i = first + k;
+        if (k >= n_here) break;
+        unsigned long long v = 0ull;
 #pragma unroll
-            for (int c = 0; c < kCopies; ++c)
-                part[u][c] = in && c < n_copies ? copies[(uint64_t)c * n_total + key0 + i] : 0ull;
-            prev[u] = in ? out[j] : 0ll;   // the output's bits (int64, or a double's)
-        }
-#pragma unroll
-        for (int u = 0; u < kFinPix; ++u) {
-            const uint64_t i = i0 + u * stride;
-            if (i >= n_pix) break;
-            unsigned long long v = 0ull;
-#pragma unroll
-            for (int c = 0; c < kCopies; ++c) v += part[u][c];
-            if (beam_key == i + 1) v += beam_v;
-            const bool is_side = i < n_side;
-            const uint64_t j = is_side ? i : i - n_side;
-            if (FIX) ((long long *)(is_side ? side : trans))[j] = prev[u] + (long long)v;
-            else ((double *)(is_side ? side : trans))[j] =
-                __longlong_as_double(prev[u]) + (double)(long long)v * (1.0 / kFix);
-            if (is_side) sum_side += v; else sum_trans += v;
-        }
+        for (int c = 0; c < kCopies; ++c) v += part[u][c];
+        if (beam_key == (uint64_t)i + 1) v += beam_v;
+        if (FIX) out[i] = prev[u] + (long long)v;
+        else ((double *)out)[i] = __longlong_as_double(prev[u]) + (double)(long long)v * (1.0 / kFix);
+        sum += v;
     }
-    if (face_side) {
-        // One atomic per block and face: same-address global atomics serialise.
-        __shared__ unsigned long long s_part[2][4];
-        sum_side = wave_sum(sum_side);
-        sum_trans = wave_sum(sum_trans);
-        const int wave = threadIdx.x >> 6;
-        if (__lane_id() == 0) {
-            s_part[0][wave] = sum_side;
-            s_part[1][wave] = sum_trans;
-        }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            const unsigned long long a0 = s_part[0][0] + s_part[0][1] + s_part[0][2] + s_part[0][3];
-            const unsigned long long a1 = s_part[1][0] + s_part[1][1] + s_part[1][2] + s_part[1][3];
-            if (a0) atomicAdd(face_side, a0);
-            if (a1) atomicAdd(face_trans, a1);
-        }
-    }
+    if (z != 0) return;
+    __shared__ unsigned long long s_part[kFinThreads / 64];
+    sum = wave_sum(sum);
+    if (__lane_id() == 0) s_part[threadIdx.x >> 6] = sum;
+    __syncthreads();   // (every pixel of the block has been read)
+    if (threadIdx.x == 0) copies[first] = s_part[0] + s_part[1] + s_part[2] + s_part[3];
 }
 
 // Fixed-point scalar sums to the caller's doubles (weights scaled back by
 // 2^-32, counts as they are); the second-order side moments are FP64 sums.
-// One medium per block.
-__global__ void finalize_scalars(const unsigned long long *ws_scal, double *scalars)
+// The +x and +z faces' totals are those of their images, added up from the
+// blocks of finalize_images.  One medium per block.
+template <bool ADD>
+__global__ __launch_bounds__(kFinThreads) void finalize_scalars(FinArgs a)
 {
-    ws_scal += (uint64_t)blockIdx.x * kWsScalarWords;
-    scalars += (uint64_t)blockIdx.x * MC_N_SCALARS;
+    const uint64_t inst = blockIdx.x;
+    const unsigned long long *ws_scal = a.ws_scal + inst * kWsScalarWords;
+    const unsigned long long *copies = a.copies[0] + inst * a.n_pix;
+    double *scalars = a.scalars + inst * MC_N_SCALARS;
     const int t = threadIdx.x;
+    unsigned long long face[2] = {0ull, 0ull};
+    for (uint64_t i = t * kFinBlock; i < a.n_side; i += kFinThreads * kFinBlock) face[0] += copies[i];
+    for (uint64_t i = (uint64_t)a.n_side + t * kFinBlock; i < a.n_pix; i += kFinThreads * kFinBlock) face[1] += copies[i];
+    __shared__ unsigned long long s_face[2][kFinThreads / 64];
+    for (int f = 0; f < 2; ++f) {
+        const unsigned long long v = wave_sum(face[f]);
+        if (__lane_id() == 0) s_face[f][t >> 6] = v;
+    }
+    __syncthreads();
+    if (t >= MC_N_SCALARS) return;
+    double v = 0.0;
     if (t < MC_S_RESERVED) {
         const bool weight = t <= MC_S_CAPPED_W;
-        long long v = (long long)ws_scal[t];
+        long long n = (long long)ws_scal[t];
+        if (t == MC_S_FACE + 1 || t == MC_S_FACE + 5) {
+            const unsigned long long *f = s_face[t == MC_S_FACE + 1 ? 0 : 1];
+            n = (long long)(f[0] + f[1] + f[2] + f[3]);
+        }
         // Reflections are not counted by the walk: every step interacts or
         // reaches a wall, and a wall step reflects unless the photon leaves,
         // which every photon not killed by roulette or capped does once.
         if (t == MC_S_REFLECTIONS)
-            v = (long long)(ws_scal[MC_S_STEPS] - ws_scal[MC_S_EVENTS] -
+            n = (long long)(ws_scal[MC_S_STEPS] - ws_scal[MC_S_EVENTS] -
                             (ws_scal[MC_S_PHOTONS] - ws_scal[MC_S_ROULETTE_KILLS] - ws_scal[MC_S_CAPPED]));
-        scalars[t] += weight ? (double)v * (1.0 / kFix) : (double)v;
+        v = weight ? (double)n * (1.0 / kFix) : (double)n;
     } else if (t >= MC_S_SIDE_W2 && t <= MC_S_SIDE_W2L) {
-        scalars[t] += __longlong_as_double((long long)ws_scal[t]);
+        v = __longlong_as_double((long long)ws_scal[t]);
     }
+    scalars[t] = ADD ? scalars[t] + v : v;
 }
 
 __global__ void philox_blocks_kernel(uint32_t k0, uint32_t k1, uint32_t instance, const uint64_t *ids,
@@ -1738,12 +1738,8 @@ int launch_walk(WalkArgs &a, const mc_detector_t &det, const mc_run_t &rn, const
     // (hipExtLaunchKernel): a separate event record would put a barrier, and
     // several microseconds of idle device, between two kernels.
     hipExtLaunchKernelGGL(init_kernel, dim3(1024), dim3(256), 0, st, (hipEvent_t)rn.sim_events[0], nullptr, 0u, ws,
-                          (size_t)clear_words, clear2,
-                       (size_t)clear2_words, (unsigned long long *)t.side, (unsigned long long *)t.trans,
-                       sig ? (unsigned long long *)t.side_w2 : nullptr, sig ? (unsigned long long *)t.trans_w2 : nullptr,
-                       (size_t)(n_side * n_inst), (size_t)(n_trans * n_inst), t.scalars,
-                       (size_t)MC_N_SCALARS * n_inst, a.rec_i, a.rec_f, (size_t)a.rec_rows, a.side_wk, a.side_wl,
-                       a.side_w2k, a.side_w2l, zero_all);
+                          (size_t)clear_words, clear2, (size_t)clear2_words, (size_t)(n_side * n_inst), a.rec_i, a.rec_f,
+                          (size_t)a.rec_rows, a.side_wk, a.side_wl, a.side_w2k, a.side_w2l, zero_all);
     MC_HIP_CHECK(hipGetLastError());
 
     using Kern = void (*)(WalkArgs);
@@ -1822,22 +1818,28 @@ int launch_walk(WalkArgs &a, const mc_detector_t &det, const mc_run_t &rn, const
     }
     // ---- finalize: per-XCD copies to the caller's images, scalars to doubles ----
     const bool fix64 = (det.flags & MC_FIX64) != 0;
-    const unsigned fin_x = (unsigned)std::max<uint64_t>(1, std::min<uint64_t>(batch ? 64 : 512, (n_pix + 255) / 256));
-    auto fin = fix64 ? finalize_images<true> : finalize_images<false>;
+    FinArgs f{};
+    f.copies[0] = a.ws_img;
+    f.copies[1] = a.ws_img2;
+    f.side[0] = t.side; f.side[1] = t.side_w2;
+    f.trans[0] = t.trans; f.trans[1] = t.trans_w2;
     // The fixed-point weight (and squared weight, an FP32 product as in the
     // walk) of an unscattered first-step exit, as the walk's fix() rounds it.
     const float w0sq = a.w0 * a.w0;
-    const unsigned long long ball_w = (unsigned long long)std::llrint((double)a.w0 * kFix);
-    const unsigned long long ball_w2 = (unsigned long long)std::llrint((double)w0sq * kFix);
-    hipLaunchKernelGGL(fin, dim3(fin_x, n_inst), dim3(256), 0, st, a.ws_img, (int)copies, n_total, n_pix,
-                       (uint32_t)n_side, t.side, t.trans, ws + MC_S_FACE + 1, ws + MC_S_FACE + 5, kWsScalarWords,
-                       (const unsigned long long *)ws, ball_w);
-    if (sig)
-        hipLaunchKernelGGL(fin, dim3(fin_x, n_inst), dim3(256), 0, st, a.ws_img2, (int)copies, n_total, n_pix,
-                           (uint32_t)n_side, t.side_w2, t.trans_w2, (unsigned long long *)nullptr,
-                           (unsigned long long *)nullptr, kWsScalarWords, (const unsigned long long *)ws, ball_w2);
-    hipExtLaunchKernelGGL(finalize_scalars, dim3(n_inst), dim3(64), 0, st, nullptr, (hipEvent_t)rn.sim_events[1], 0u,
-                          (const unsigned long long *)ws, t.scalars);
+    f.ball_w[0] = (unsigned long long)std::llrint((double)a.w0 * kFix);
+    f.ball_w[1] = (unsigned long long)std::llrint((double)w0sq * kFix);
+    f.n_copies = (int)copies;
+    f.n_total = n_total;
+    f.n_pix = (uint32_t)n_pix;
+    f.n_side = (uint32_t)n_side;
+    f.ws_scal = ws;
+    f.scalars = t.scalars;
+    const unsigned fin_x = (unsigned)((n_side + kFinBlock - 1) / kFinBlock + (n_trans + kFinBlock - 1) / kFinBlock);
+    auto fin = zero_all ? (fix64 ? finalize_images<true, false> : finalize_images<false, false>)
+                        : (fix64 ? finalize_images<true, true> : finalize_images<false, true>);
+    hipLaunchKernelGGL(fin, dim3(fin_x, n_inst, sig ? 2 : 1), dim3(kFinThreads), 0, st, f);
+    hipExtLaunchKernelGGL(zero_all ? finalize_scalars<false> : finalize_scalars<true>, dim3(n_inst), dim3(kFinThreads), 0,
+                          st, nullptr, (hipEvent_t)rn.sim_events[1], 0u, f);
     MC_HIP_CHECK(hipGetLastError());
     return MC_OK;
 }

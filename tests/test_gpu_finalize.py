@@ -1,0 +1,92 @@
+"""From the summed copies to the caller's images (-m gpu): pixel counts at the
+edges of a block of 1024, images of one pixel, sums written and added, int64 and
+double, squared weights in the same launch, the copies of one medium or several.
+The oracle walks the same photons; sums of fixed-point weights are exact, so
+everything here is compared exactly with them or with each other."""
+import numpy as np
+import pytest
+
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+N = 20_000
+SHAPES = [(1, 1, 1, 1), (1, 1023, 32, 32), (1025, 1, 1, 1), (32, 32, 3, 683), (45, 91, 1, 1), (7, 3, 64, 32)]
+
+
+@pytest.fixture(scope="module")
+def mc():
+    import paper_2507_23189_amd as m
+    m.lib()
+    return m
+
+
+@pytest.fixture(scope="module")
+def table(mc, cuda_device):
+    return mc.mie_table_build(mc.args_from_workload(W.TINY)[0], cuda_device)
+
+
+def _args(mc, table, shape, flags=0, tau=1.0):
+    w = W.TINY.replace(tau=tau, n_photons=N, side_px=16, trans_px=16)
+    _, med, src, geo, det, run = mc.args_from_workload(w, table, flags=flags)
+    det.side_nx, det.side_ny, det.trans_nx, det.trans_ny = shape
+    return med, src, geo, det, run
+
+
+def _run(mc, args, tally, times=1):
+    import torch
+    for _ in range(times):
+        mc.mc_simulate(*args, tally)
+    torch.cuda.synchronize()
+    return {k: getattr(tally, k).cpu().numpy().ravel() for k in ("side", "trans", "scalars", "side_w2", "trans_w2")
+            if getattr(tally, k, None) is not None}
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=str)
+@pytest.mark.parametrize("log", [False, True], ids=["atomic", "log"])
+def test_images_and_totals_at_the_edges_of_a_block(mc, table, cuda_device, shape, log):
+    """int64, double, squared weights and added sums of one walk agree, and the
+    faces' totals are those of one-pixel images, which count every exit."""
+    extra = mc.MC_EXIT_LOG if log else 0
+    fixed = _args(mc, table, shape, mc.MC_FIX64 | extra)
+    got = _run(mc, fixed, mc.Tally.alloc(fixed[3], "cuda", fix64=True, log_photons=N))
+    one = _args(mc, table, (1, 1, 1, 1), mc.MC_FIX64)
+    ref = _run(mc, one, mc.Tally.alloc(one[3], "cuda", fix64=True))
+    assert got["scalars"][mc.MC_S_FACE + 1] == ref["side"][0] / 2.0**32 == got["side"].sum() / 2.0**32
+    assert got["scalars"][mc.MC_S_FACE + 5] == ref["trans"][0] / 2.0**32 == got["trans"].sum() / 2.0**32
+    assert np.array_equal(got["scalars"], ref["scalars"])
+
+    real = _args(mc, table, shape, mc.MC_SIGMA)
+    t = mc.Tally.alloc(real[3], "cuda", sigma=True)
+    for img in (t.side, t.trans, t.side_w2, t.trans_w2, t.scalars):
+        img.fill_(7.0)                       # written whole, not added to
+    dbl = _run(mc, real, t)
+    assert np.array_equal(dbl["scalars"], ref["scalars"])
+    for k in ("side", "trans"):
+        assert np.array_equal(dbl[k], got[k] / 2.0**32), k
+        assert 0.0 <= dbl[k + "_w2"].sum() <= dbl[k].sum()
+
+    for flags, base in ((mc.MC_FIX64, got), (0, dbl)):
+        acc = _args(mc, table, shape, flags | extra | mc.MC_ACCUMULATE)
+        t = mc.Tally.alloc(acc[3], "cuda", fix64=bool(flags), log_photons=N)
+        for img in (t.side, t.trans, t.scalars):
+            img.fill_(3)
+        two = _run(mc, acc, t, times=2)
+        for k in ("side", "trans", "scalars"):
+            assert np.array_equal(two[k], 3 + base[k] + base[k]), k
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=str)
+def test_media_of_a_batch_keep_their_own_images(mc, table, cuda_device, shape):
+    import torch
+    med, src, geo, det, run = _args(mc, table, shape, mc.MC_FIX64)
+    taus = (0.25, 1.0, 3.0)
+    items = [mc.BatchItem(tau=t, albedo=0.9999, inv_cdf=table.inv_cdf.data_ptr(), n_photons=N, instance=0) for t in taus]
+    tally = mc.Tally.alloc_batch(det, len(items), "cuda", fix64=True)
+    mc.mc_simulate_batch(items, W.TINY.n_cdf, src, geo, det, run, tally)
+    torch.cuda.synchronize()
+    for i, tau in enumerate(taus):
+        alone = _args(mc, table, shape, mc.MC_FIX64, tau=tau)
+        ref = _run(mc, alone, mc.Tally.alloc(det, "cuda", fix64=True))
+        for k in ("side", "trans", "scalars"):
+            assert np.array_equal(getattr(tally, k)[i].cpu().numpy().ravel(), ref[k]), (tau, k)
