@@ -337,7 +337,8 @@ void walk_kernel(WalkArgs a)
     const int slots = a.cache_bits ? 1 << a.cache_bits : 0;
     // The block's pool of photon ids (work units), see kPoolFilling.
     unsigned long long *s_pool = s_scal + n_scal;
-    unsigned long long *s_cw = s_pool + 1;
+    unsigned long long *s_full = s_pool + 1;   // exit log: exits that found their region full
+    unsigned long long *s_cw = s_full + 1;
     unsigned long long *s_cw2 = s_cw + (SIGMA ? slots : 0);
     uint32_t *s_key = (uint32_t *)(s_cw2 + slots);
     float *s_queue = (float *)(s_key + slots);
@@ -353,6 +354,7 @@ void walk_kernel(WalkArgs a)
         const uint64_t lo = min((uint64_t)blockIdx.x * a.claim0, (uint64_t)a.n_ids);
         const uint64_t hi = min(lo + a.claim0, (uint64_t)a.n_ids);
         *s_pool = lo < hi ? pool_range((uint32_t)lo, (uint32_t)hi) : 0ull;
+        *s_full = 0ull;
     }
     for (int i = threadIdx.x; i < slots; i += blockDim.x) {
         s_cw[i] = 0ull;
@@ -404,8 +406,11 @@ void walk_kernel(WalkArgs a)
     // Tally the first n queued exits, one per lane: pixel key, then the LDS
     // cache (claim or hit, up to four linear probes) or, when every probed
     // slot holds another pixel, a global atomic.  With the exit log the exits
-    // are appended to the log instead; a global atomic is then the fallback
-    // for a range whose region of the log is full.
+    // are appended to the log instead, until their range's region is full.
+    // What comes after that is mostly the few pixels that filled the region, so
+    // the cache takes nearly all of it (with global atomics alone, on pixels and
+    // a counter that all blocks share, 1e8 photons at optical depth 1 took
+    // 22.4 ms at 64 x 64 and 3.46 ms at 1024 x 1024; now 1.34 and 1.25).
     auto flush = [&](uint32_t n) {
         const ArgsPtr ra = reload_args();
         __builtin_amdgcn_wave_barrier();
@@ -430,31 +435,24 @@ void walk_kernel(WalkArgs a)
             key = key_base + (side ? 0u : ra->n_side) +
                   (uint32_t)(pixel_scaled(y, per_row, n_row) * n_col + pixel_scaled(b, per_col, n_col));
         }
-        if (act && !LOG) {
-            wq = fix(wf);
-            wq2 = SIGMA ? fix(wf * wf) : 0ull;
-        }
+        bool to_image = act;
         if (LOG) {
             // Append to the block's region of the key's range at the position
-            // the block's LDS counter hands out; past the region's end, the
-            // exit is added directly.
+            // the block's LDS counter hands out.
             const uint32_t bucket = log_bucket(key, ra->log_bits, ra->log_rbits);
-            bool direct = false;
             if (act) {
                 const uint32_t e = atomicAdd(&s_lcnt[bucket], 1u);
-                if (e < ra->log_cap)
+                if (e < ra->log_cap) {
                     ra->log[(uint64_t)(bucket * gridDim.x + blockIdx.x) * ra->log_cap + e] =
                         ((unsigned long long)key << 32) | __float_as_uint(wf);
-                else
-                    direct = true;
+                    to_image = false;
+                }
             }
-            if (direct) {
-                atomicAdd(my_img() + key, fix(wf));
-                if (SIGMA) atomicAdd(my_img2() + key, fix(wf * wf));
-            }
-            const uint64_t took = __ballot(direct);
-            if (took && lane == 0) atomicAdd(ra->ws_scal + kWsLogFallback, (unsigned long long)__popcll(took));
-        } else if (act) {
+        }
+        if (to_image) {
+            wq = fix(wf);
+            wq2 = SIGMA ? fix(wf * wf) : 0ull;
+            if (LOG) atomicAdd(s_full, 1ull);
             bool cached = false;
             if (slots) {
                 uint32_t slot = (key * 2654435761u) >> (32 - ra->cache_bits);
@@ -969,6 +967,7 @@ void walk_kernel(WalkArgs a)
             if (v != 0.0) atomicAdd((double *)&a.ws_scal[threadIdx.x], v);
         }
     }
+    if (LOG && threadIdx.x == 0 && *s_full != 0ull) atomicAdd(a.ws_scal + kWsLogFallback, *s_full);
     for (int i = threadIdx.x; i < slots; i += blockDim.x) {
         const uint32_t key = s_key[i];
         if (key == kEmpty) continue;
@@ -1013,18 +1012,19 @@ __global__ void init_kernel(unsigned long long *ws, size_t n_ws, unsigned long l
 // from block s, wrote (log_count entries each), adds the fixed-point weights (and
 // squared weights) of the entries whose index within the range lies in part
 // p into an LDS histogram of 2^kLogHistBits sums, then writes the sums into
-// copy s.  Copy 0 also holds the walk's fallback atomics (exits that found
-// their region full), so it was cleared and takes the non-zero sums as
-// adds; the other copies were not cleared and take every key's sum as a
-// store (the blocks of copy s cover each of its keys exactly once).  No
+// copy s.  The first n_cleared copies (copy 0, or all) also hold the walk's
+// fallback atomics (exits that found their region full), so they were cleared
+// and take the non-zero sums as adds; the other copies were not cleared and
+// take every key's sum as a store (the blocks of copy s cover each of its keys
+// exactly once).  No
 // other writer touches those keys now, so plain loads and stores do.  The
 // sums are of the same fix() values the walk would have added, so the
 // images equal those of the atomic path bit for bit.
 template <bool SIGMA>
 __global__ __launch_bounds__(1024) void log_bin(const unsigned long long *log, const uint32_t *count, uint32_t cap,
                                                 uint32_t walk_blocks, unsigned long long *copies,
-                                                unsigned long long *copies2, uint32_t n_copies, uint64_t n_total,
-                                                uint32_t parts, uint32_t bits, uint32_t rbits, uint32_t inv_mul)
+                                                unsigned long long *copies2, uint32_t n_copies, uint32_t n_cleared,
+                                                uint64_t n_total, uint32_t parts, uint32_t bits, uint32_t rbits, uint32_t inv_mul)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned long long s_hist[];
     constexpr uint32_t H = 1u << kLogHistBits;
@@ -1080,7 +1080,7 @@ __global__ __launch_bounds__(1024) void log_bin(const unsigned long long *log, c
         if (key >= n_total) continue;
         const unsigned long long v = s_hist[i];
         const unsigned long long v2 = SIGMA ? s_hist2[i] : 0ull;
-        if (s != 0) {
+        if (s >= n_cleared) {
             dst[key] = v;
             if (SIGMA) dst2[key] = v2;
         } else {
@@ -1668,7 +1668,7 @@ int launch_walk(WalkArgs &a, const mc_detector_t &det, const mc_run_t &rn, const
     // two per CU.
     const int block = rn.block_size ? rn.block_size : ((det.flags & MC_MOMENTS) ? 768 : 1024);
     const size_t table_bytes = batch ? 0 : (size_t)((a.n_cdf + 3) & ~3) * sizeof(float);
-    const size_t scal_bytes = ((batch ? (size_t)n_inst * kBatchScal : MC_N_SCALARS) + 1) * sizeof(double);
+    const size_t scal_bytes = ((batch ? (size_t)n_inst * kBatchScal : MC_N_SCALARS) + 2) * sizeof(double);
     const size_t queue_arrays = batch ? 4 : 3;
     const size_t slot_bytes = sizeof(uint32_t) + sizeof(double) * ((det.flags & MC_SIGMA) ? 2 : 1);
     const size_t lds_half_cu = 80 * 1024;
@@ -1678,7 +1678,7 @@ int launch_walk(WalkArgs &a, const mc_detector_t &det, const mc_run_t &rn, const
         const size_t lds_fixed = table_bytes + scal_bytes + (size_t)(block / 64) * queue_arrays * kQueue * sizeof(float) +
                                  (log ? ((size_t)4 << shape.rbits) : 0);
         a.cache_bits = 0;
-        for (int b = 10; b >= 4 && !log; --b)
+        for (int b = 10; b >= 4; --b)
             if (lds_fixed + (slot_bytes << b) <= lds_half_cu) { a.cache_bits = b; break; }
         lds = lds_fixed + (a.cache_bits ? (slot_bytes << a.cache_bits) : 0);
         const int blocks_per_cu = std::max(1, std::min((int)(160 * 1024 / lds), 32 / (block / 64)));
@@ -1693,8 +1693,15 @@ int launch_walk(WalkArgs &a, const mc_detector_t &det, const mc_run_t &rn, const
     }
     const uint64_t copies = copies_for(use_log);
     // With the exit log the walk's only image atomics are its fallback ones
-    // (an exit whose region is full): all of them go to copy 0.
-    a.copy_mask = use_log ? 0u : (uint32_t)(copies - 1);
+    // (an exit whose region is full and whose pixel has no slot in the cache):
+    // all of them go to copy 0, the only one to be cleared.  Many photons in
+    // small images leave so many that they take a copy per XCD as well (1e8 at
+    // optical depth 1, 128 x 128: 6.0 ms on copy 0, 1.44 spread; 1e7: 196.5 us
+    // and 199.4, of which clearing is the difference; 256 x 256 and 1e8: 1.26
+    // and 1.23 ms).
+    const bool spread = n_total <= (1u << 17) && total_photons >= (1u << 24);
+    const uint32_t n_cleared = use_log && !spread ? 1u : (uint32_t)copies;
+    a.copy_mask = n_cleared - 1;
     a.ws_img2 = (det.flags & MC_SIGMA) ? a.ws_img + copies * n_total : nullptr;
     if (lds > 160 * 1024) return fail(MC_EINVAL, "mc_simulate: %zu bytes of LDS per block do not fit a CU", lds);
     const uint64_t waves_total = (uint64_t)grid * (block / 64);
@@ -1716,9 +1723,9 @@ int launch_walk(WalkArgs &a, const mc_detector_t &det, const mc_run_t &rn, const
     // what the caller gave beyond the workspace words (the walk writes every
     // count, so nothing needs clearing) ----
     // What init clears: the scalar words and every image copy, except when
-    // log_bin will run (the exit log and some photons): then only copy 0 (and
-    // copy 0 of the squared weights), since log_bin stores into the others.
-    const bool bin_stores = use_log && total_photons > 0;
+    // log_bin will run (the exit log and some photons) and store into the
+    // copies other than 0: then only copy 0 (and copy 0 of the squared weights).
+    const bool bin_stores = use_log && !spread && total_photons > 0;
     const uint64_t clear_words = bin_stores ? kWsScalarWords * n_inst + n_total : workspace_words(det, n_inst, copies);
     unsigned long long *clear2 = bin_stores && (det.flags & MC_SIGMA) ? a.ws_img2 : nullptr;
     const uint64_t clear2_words = clear2 ? n_total : 0;
@@ -1812,8 +1819,8 @@ int launch_walk(WalkArgs &a, const mc_detector_t &det, const mc_run_t &rn, const
         MC_HIP_CHECK(hipFuncSetAttribute((const void *)bin, hipFuncAttributeMaxDynamicSharedMemorySize, (int)hist));
         hipLaunchKernelGGL(bin, dim3((1u << a.log_rbits) * parts * (uint32_t)copies), dim3(1024), hist, st,
                            (const unsigned long long *)a.log, (const uint32_t *)a.log_count, a.log_cap,
-                           (uint32_t)grid, a.ws_img, a.ws_img2, (uint32_t)copies, n_total, parts, a.log_bits,
-                           a.log_rbits, inv);
+                           (uint32_t)grid, a.ws_img, a.ws_img2, (uint32_t)copies, n_cleared, n_total, parts,
+                           a.log_bits, a.log_rbits, inv);
         MC_HIP_CHECK(hipGetLastError());
     }
     // ---- finalize: per-XCD copies to the caller's images, scalars to doubles ----
