@@ -1672,6 +1672,22 @@ int launch_walk(WalkArgs &a, const mc_detector_t &det, const mc_run_t &rn, const
     const size_t queue_arrays = batch ? 4 : 3;
     const size_t slot_bytes = sizeof(uint32_t) + sizeof(double) * ((det.flags & MC_SIGMA) ? 2 : 1);
     const size_t lds_half_cu = 80 * 1024;
+    // The optical depth along the beam axis (negative for a batch).
+    const double tau_z = !batch && a.neg_ln2_over_mu < 0.f && std::isfinite(a.neg_ln2_over_mu)
+                             ? -M_LN2 / (double)a.neg_ln2_over_mu * a.size[2]
+                             : -1.0;
+    // Few photons take one block per CU: half the tables to load, half the
+    // shares to finish, and the same lanes with twice the photons each.  Up to
+    // three photons per lane of such a launch, four from depth 3 and five from
+    // depth 6 (deep walks hide more of each photon's end); but below half a
+    // photon per lane at depth 12 and more two blocks spread the
+    // long walks over more waves.  Times in us of two blocks and of one: 1e5
+    // tau = 4 57.6 / 53.4, 3e5 tau = 2 63.2 / 58.2, 7e5 tau = 0.25 109.7 / 104.9, tau = 16
+    // 209 / 167; 1e6 tau = 1 73.9 / 76.0, tau = 4 88.7 / 83.9, tau = 16 219 / 194; 2e6
+    // tau = 4 117.5 / 118.5; 1e4 tau = 16 94.7 / 97.9.
+    const uint64_t lanes_one = (uint64_t)cus * block;
+    const bool few = !batch && total_photons <= lanes_one * (tau_z > 6.0 ? 5 : (tau_z > 3.0 ? 4 : 3)) &&
+                     !(tau_z > 12.0 && total_photons < lanes_one / 2);
     size_t lds = 0;
     int grid = 0;
     auto launch_shape = [&](bool log) {
@@ -1682,7 +1698,7 @@ int launch_walk(WalkArgs &a, const mc_detector_t &det, const mc_run_t &rn, const
             if (lds_fixed + (slot_bytes << b) <= lds_half_cu) { a.cache_bits = b; break; }
         lds = lds_fixed + (a.cache_bits ? (slot_bytes << a.cache_bits) : 0);
         const int blocks_per_cu = std::max(1, std::min((int)(160 * 1024 / lds), 32 / (block / 64)));
-        grid = rn.grid_blocks > 0 ? rn.grid_blocks : cus * blocks_per_cu;
+        grid = rn.grid_blocks > 0 ? rn.grid_blocks : cus * (few ? 1 : blocks_per_cu);
     };
     const uint64_t ws_words = workspace_words(det, n_inst, max_copies);
     bool use_log = (det.flags & MC_EXIT_LOG) != 0;
@@ -1705,10 +1721,6 @@ int launch_walk(WalkArgs &a, const mc_detector_t &det, const mc_run_t &rn, const
     a.ws_img2 = (det.flags & MC_SIGMA) ? a.ws_img + copies * n_total : nullptr;
     if (lds > 160 * 1024) return fail(MC_EINVAL, "mc_simulate: %zu bytes of LDS per block do not fit a CU", lds);
     const uint64_t waves_total = (uint64_t)grid * (block / 64);
-    // The optical depth along the beam axis (negative for a batch).
-    const double tau_z = !batch && a.neg_ln2_over_mu < 0.f && std::isfinite(a.neg_ln2_over_mu)
-                             ? -M_LN2 / (double)a.neg_ln2_over_mu * a.size[2]
-                             : -1.0;
     uint64_t chunk = rn.chunk;
     if (chunk == 0) chunk = chunk_for(total_photons, waves_total, batch);
     // Work units are counted in 31 bits.

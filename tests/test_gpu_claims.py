@@ -75,3 +75,16 @@ def test_batch_units_are_walked_once(mc, cuda_device, shape):
         one = _run(mc, table, n=n, tau=t)
         for k in NAMES:
             assert np.array_equal(getattr(tb, k)[i].cpu().numpy(), one[k]), (i, k)
+
+
+@pytest.mark.parametrize("tau, per_lane", [(0.5, 3), (4.0, 4), (8.0, 5), (16.0, 0.5), (16.0, 5)], ids=str)
+@pytest.mark.parametrize("extra", [-1, 0, 1])
+def test_one_block_per_cu_or_two(mc, table, cuda_device, tau, per_lane, extra):
+    """Around the photon counts where a launch takes two blocks per CU instead
+    of one (or one instead of two): the sums of a fixed grid."""
+    import torch
+    lanes = torch.cuda.get_device_properties(0).multi_processor_count * 1024
+    n = int(per_lane * lanes) + extra
+    got, ref = _run(mc, table, n=n, tau=tau), _run(mc, table, n=n, tau=tau, grid_blocks=300)
+    for k in NAMES:
+        assert np.array_equal(got[k], ref[k]), k
