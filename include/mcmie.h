@@ -64,7 +64,9 @@ extern "C" {
                                  the results are identical bit for bit.  The log fills the
                                  workspace beyond mc_workspace_bytes (size it with
                                  mc_workspace_bytes_log); exits that find their part of it full
-                                 are added directly, so any size is correct.  Not with
+                                 are added directly, so any size is correct, and so are
+                                 all exits of at most 2^20 photons (over all media of a
+                                 batch) unless the caller sets grid_blocks.  Not with
                                  MC_RECORD; batched launches size it with
                                  mc_workspace_bytes_batch_log. */
 

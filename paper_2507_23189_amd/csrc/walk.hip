@@ -148,6 +148,7 @@ struct WalkArgs {
 };
 
 constexpr int kCopies = 8;                 // per-XCD image copies in the workspace (at most)
+constexpr uint64_t kFewPhotons = 1 << 20;  // launches up to here take no exit log and fewer image copies
 constexpr uint64_t kLogBinBlocks = 512;    // log_bin blocks that fill the chip (two per CU)
 constexpr double kFix = 4294967296.0;      // fixed-point scale 2^32 per unit weight
 
@@ -1649,11 +1650,19 @@ int launch_walk(WalkArgs &a, const mc_detector_t &det, const mc_run_t &rn, const
     // With the exit log the image copies take log_bin's sums (and the rare
     // fallback atomics): as many copies as give it kLogBinBlocks blocks, so
     // that fine key ranges (large images, batches) leave fewer copies to clear
-    // and to sum.  Without it, one per XCD for the image atomics.  The
+    // and to sum.  Without it, one per XCD for the image atomics, or one or two
+    // in all where the atomics are too few to make up for clearing and summing
+    // the others, which takes about 3 ps per pixel and copy (a single copy costs
+    // up to 20 ps per photon in waiting).  1, 2 and 8 copies, us, tau = 1: 1e5
+    // photons, 512 x 512 49.2 / 51.3 / 66.5; 1e6, 256 x 256 80.9 / 70.6 / 74.5; 1e6, 1024 x
+    // 1024 91.5 / 91.7 / 111.9; 3e6, 512 x 512 196 / 197 / 150.  The
     // workspace layout keeps room for all of them either way (the schedule and
     // the log start at the same place); the copies in use come first.
     auto copies_for = [&](bool log) -> uint64_t {
-        if (!log) return max_copies;
+        if (!log) {
+            if (total_photons > std::max<uint64_t>(kFewPhotons, n_total)) return max_copies;
+            return std::min<uint64_t>(max_copies, total_photons > kFewPhotons / 2 ? 2 : 1);
+        }
         const uint64_t bin_blocks = ((uint64_t)1 << shape.rbits) * parts;
         uint64_t c = 1;
         while (c < max_copies && bin_blocks * c < kLogBinBlocks) c <<= 1;
@@ -1701,7 +1710,11 @@ int launch_walk(WalkArgs &a, const mc_detector_t &det, const mc_run_t &rn, const
         grid = rn.grid_blocks > 0 ? rn.grid_blocks : cus * (few ? 1 : blocks_per_cu);
     };
     const uint64_t ws_words = workspace_words(det, n_inst, max_copies);
-    bool use_log = (det.flags & MC_EXIT_LOG) != 0;
+    // So few exits are not worth the log's second pass over them (log and
+    // atomics, us, tau = 4: 1e5 photons, 512 x 512 74.9 / 53.8, 1024 x 1024 83.2 / 68.2;
+    // 1e6 103.4 / 85.6 and 116.4 / 97.6; 3e6, tau = 1, 512 x 512 134 / 150).  A
+    // caller that sets the grid keeps the log: these are times of full launches.
+    bool use_log = (det.flags & MC_EXIT_LOG) != 0 && (total_photons > kFewPhotons || rn.grid_blocks > 0);
     launch_shape(use_log);
     if (use_log && t.workspace_bytes / 8 < ws_words + sched_words + (((uint64_t)grid << shape.rbits) * 4 + 7) / 8) {
         use_log = false;

@@ -49,6 +49,7 @@ def test_images_and_totals_at_the_edges_of_a_block(mc, table, cuda_device, shape
     faces' totals are those of one-pixel images, which count every exit."""
     extra = mc.MC_EXIT_LOG if log else 0
     fixed = _args(mc, table, shape, mc.MC_FIX64 | extra)
+    fixed[4].grid_blocks = 256 if log else 0    # (a launch this small takes the log only if the grid is set)
     got = _run(mc, fixed, mc.Tally.alloc(fixed[3], "cuda", fix64=True, log_photons=N))
     one = _args(mc, table, (1, 1, 1, 1), mc.MC_FIX64)
     ref = _run(mc, one, mc.Tally.alloc(one[3], "cuda", fix64=True))
@@ -68,6 +69,7 @@ def test_images_and_totals_at_the_edges_of_a_block(mc, table, cuda_device, shape
 
     for flags, base in ((mc.MC_FIX64, got), (0, dbl)):
         acc = _args(mc, table, shape, flags | extra | mc.MC_ACCUMULATE)
+        acc[4].grid_blocks = fixed[4].grid_blocks
         t = mc.Tally.alloc(acc[3], "cuda", fix64=bool(flags), log_photons=N)
         for img in (t.side, t.trans, t.scalars):
             img.fill_(3)

@@ -62,3 +62,44 @@ def test_overflow_of_added_launches(mc, table, cuda_device, n):
     assert (full > 0) == (n > SMALL)
     for k in one:
         assert np.array_equal(two[k], 2 * one[k]), k
+
+
+@pytest.mark.parametrize("shape", [(37, 23, 61, 19), (1, 1, 1, 1), (5, 300, 700, 3), (512, 512, 1024, 1024)], ids=str)
+@pytest.mark.parametrize("n, grid", [(1 << 20, 0), ((1 << 20) + 1, 0), (1 << 19, 0), ((1 << 19) + 1, 0), (200_000, 300),
+                                     (200_000, 2)], ids=str)
+def test_few_photons_with_and_without_the_log(mc, table, cuda_device, shape, n, grid):
+    """Around the counts up to which a launch takes no log, and one or two image
+    copies: the sums of a log that the caller's grid asks for."""
+    import torch
+    w = W.TINY.replace(tau=2.0, n_photons=n, side_px=16, trans_px=16)
+    out = []
+    for flags, blocks in ((mc.MC_EXIT_LOG, grid), (mc.MC_EXIT_LOG, 256), (0, grid)):
+        _, med, src, geo, det, run = mc.args_from_workload(w, table, flags=flags | mc.MC_FIX64 | mc.MC_SIGMA)
+        det.side_nx, det.side_ny, det.trans_nx, det.trans_ny = shape
+        run.grid_blocks = blocks
+        t = mc.Tally.alloc(det, "cuda", sigma=True, fix64=True, log_photons=n)
+        mc.mc_simulate(med, src, geo, det, run, t)
+        torch.cuda.synchronize()
+        out.append([getattr(t, k).cpu().numpy() for k in ("side", "trans", "scalars", "side_w2", "trans_w2")])
+    for other in out[1:]:
+        for x, y in zip(out[0], other):
+            assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("n", [1 << 12, 1 << 13, 1 << 14], ids=str)
+def test_few_photons_of_a_batch(mc, table, cuda_device, n):
+    """64 media of n photons: one copy, two, and all of them (or the log)."""
+    import torch
+    _, _, src, geo, det, run = mc.args_from_workload(W.TINY.replace(side_px=16, trans_px=16), table, flags=mc.MC_FIX64)
+    out = []
+    for flags, blocks, extra in ((0, 0, 0), (mc.MC_EXIT_LOG, 0, 0), (mc.MC_EXIT_LOG, 256, 0), (0, 0, 1)):
+        det.flags, run.grid_blocks = mc.MC_FIX64 | flags, blocks
+        items = [mc.BatchItem(tau=0.1 * (i + 1), albedo=0.9999, inv_cdf=table.inv_cdf.data_ptr(),
+                              n_photons=n + (extra if i == 63 else 0), instance=i) for i in range(64)]
+        t = mc.Tally.alloc_batch(det, 64, "cuda", fix64=True, log_photons=64 * n)
+        mc.mc_simulate_batch(items, W.TINY.n_cdf, src, geo, det, run, t)
+        torch.cuda.synchronize()
+        out.append([getattr(t, k)[:63].cpu().numpy() for k in ("side", "trans", "scalars")])
+    for other in out[1:]:
+        for x, y in zip(out[0], other):
+            assert np.array_equal(x, y)
