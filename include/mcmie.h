@@ -366,7 +366,7 @@ int mc_simulate(const mc_medium_t *medium, const mc_source_t *source, const mc_g
  * captured into a HIP graph, tight serving loops, harnesses that forbid
  * hipMalloc.  Same arguments and results as mc_simulate, except that
  * tally->workspace and tally->workspace_bytes are ignored: the images are
- * tallied in one fixed-point copy (instead of eight per-XCD copies) held in a
+ * tallied in as many fixed-point copies as fit (of the eight, one per XCD) in a
  * device array of MC_NOALLOC_SCRATCH_BYTES that the library keeps on every
  * GPU it runs on until the process ends.  The call allocates nothing (no
  * hipMalloc, no hipFree, no allocating library routine); the caller still

@@ -103,3 +103,29 @@ def test_few_photons_of_a_batch(mc, table, cuda_device, n):
     for other in out[1:]:
         for x, y in zip(out[0], other):
             assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("pixels", [1 << 21, 1 << 20, (1 << 20) + 1, 1 << 18, (1 << 18) + 1], ids=str)
+@pytest.mark.parametrize("sigma", [False, True], ids=["", "sigma"])
+def test_copies_in_the_library_scratch(mc, table, cuda_device, pixels, sigma):
+    """One, two, four and eight copies in the library's own scratch: the sums of
+    a caller's workspace; a pixel more than it holds is refused."""
+    import torch
+    n = (1 << 21) + 1 if pixels == 1 << 21 else (1 << 20) + 2
+    if sigma:
+        pixels = pixels // 2
+    w = W.TINY.replace(tau=1.0, n_photons=n, side_px=16, trans_px=16)
+    flags = mc.MC_FIX64 | (mc.MC_SIGMA if sigma else 0)
+    _, med, src, geo, det, run = mc.args_from_workload(w, table, flags=flags)
+    det.side_nx, det.side_ny, det.trans_nx, det.trans_ny = pixels - 48 * 64, 1, 64, 48
+    ref, got = (mc.Tally.alloc(det, "cuda", sigma=sigma, fix64=True) for _ in range(2))
+    mc.mc_simulate(med, src, geo, det, run, ref)
+    mc.mc_simulate_noalloc(med, src, geo, det, run, got)
+    torch.cuda.synchronize()
+    for k in ("side", "trans", "scalars") + (("side_w2", "trans_w2") if sigma else ()):
+        assert torch.equal(getattr(got, k), getattr(ref, k)), k
+    if pixels == (1 << 21 if not sigma else 1 << 20):
+        det.side_nx += 1
+        big = mc.Tally.alloc(det, "cuda", sigma=sigma, fix64=True)
+        with pytest.raises(mc.McError):
+            mc.mc_simulate_noalloc(med, src, geo, det, run, big)
