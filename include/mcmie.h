@@ -477,6 +477,16 @@ int mc_grad(const mc_medium_t *medium, const mc_geometry_t *geometry, const mc_d
             double d2loss_uniform, double out_grad[3], void *stream);
 
 /*
+ * The variance-corrected L2 loss of a side image filled by mc_simulate with
+ * MC_MOMENTS: *loss (device) = sum_p (I_p - T_p)^2 - sum w^2, and its g for
+ * mc_grad, dloss_dside (device, side-image shape) = 2 (I - T), with target
+ * (device, the same shape).  Sums in a fixed order, in the tally's workspace
+ * as mc_grad's.  MC_EINVAL with MC_FIX64.  Asynchronous.
+ */
+int mc_side_l2(const mc_detector_t *detector, const mc_tally_t *tally, const double *target,
+               double *dloss_dside, double *loss, void *stream);
+
+/*
  * The random numbers the walk draws: for each of n_ids photon ids (device
  * array) and steps step0 .. step0 + n_steps - 1, write the four 32-bit
  * Philox4x32-10 words to out (device, n_ids * n_steps * 4 uint32, photon-major).

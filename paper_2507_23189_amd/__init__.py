@@ -11,7 +11,7 @@ from ._capi import (MC_ACCUMULATE, MC_EDEVICE, MC_EINVAL, MC_ENOMEM, MC_EUNSUPPO
                     MC_S_CAPPED, MC_S_REFLECTIONS, MC_S_STEPS,
                     MC_MAX_N_CDF, MC_MAX_TERMS, MC_N_SCALARS, MC_OK, MC_PHASE_HG, MC_PHASE_MIE, MC_RECORD,
                     MC_SIGMA, Detector, Geometry, McError, Medium, MieSpec, MieTable, Run, Source, Tally, lib,
-                    mc_grad, mc_philox_blocks, mc_simulate, mc_version, mc_workspace_bytes, mie_table_build,
+                    mc_grad, mc_side_l2, mc_philox_blocks, mc_simulate, mc_version, mc_workspace_bytes, mie_table_build,
                     mc_workspace_bytes_log,
                     BatchItem, MC_MAX_BATCH, AUTOTUNE_BLOCKS, AUTOTUNE_CHUNKS, mc_simulate_batch,
                     mc_autotune_batch, mc_workspace_bytes_batch, mc_workspace_bytes_batch_log, MiePoly, MC_MAX_BINS, mie_table_build_poly,

@@ -149,6 +149,8 @@ def lib():
                                           C.POINTER(Detector), C.POINTER(Run), C.POINTER(_TallyC), C.c_void_p]
         L.mc_grad.argtypes = [C.POINTER(Medium), C.POINTER(Geometry), C.POINTER(Detector), C.POINTER(_TallyC),
                               C.c_void_p, C.c_void_p, C.c_double, C.POINTER(C.c_double), C.c_void_p]
+        L.mc_side_l2.argtypes = [C.POINTER(Detector), C.POINTER(_TallyC), C.c_void_p, C.c_void_p, C.c_void_p,
+                                 C.c_void_p]
         L.mc_philox_blocks.argtypes = [C.c_uint64, C.c_uint32, C.c_void_p, C.c_uint64, C.c_uint32, C.c_uint32,
                                        C.c_void_p, C.c_void_p]
         L.mie_table_build_poly.argtypes = [C.POINTER(MieSpec), C.POINTER(MiePoly), C.POINTER(_MieTableC),
@@ -177,7 +179,7 @@ def lib():
                                                       C.POINTER(C.c_double), C.POINTER(C.c_double), C.c_void_p]
         L.mc_last_error.restype = C.c_char_p
         L.mc_version.restype = C.c_int
-        for f in ("mie_table_build", "mie_table_enqueue", "mc_simulate", "mc_simulate_noalloc", "mc_grad", "mc_philox_blocks",
+        for f in ("mie_table_build", "mie_table_enqueue", "mc_simulate", "mc_simulate_noalloc", "mc_grad", "mc_side_l2", "mc_philox_blocks",
                   "mc_simulate_batch", "mc_autotune_batch", "mie_table_build_poly", "mc_lognormal_bins",
                   "mc_image_metrics", "mc_medium_coefficients"):
             getattr(L, f).restype = C.c_int
@@ -531,6 +533,21 @@ def mc_grad(medium: Medium, geometry: Geometry, detector: Detector, tally: Tally
     _check(lib().mc_grad(C.byref(medium), C.byref(geometry), C.byref(detector), C.byref(tc),
                          _ptr(dloss_dside), _ptr(d2loss_dside2), float(d2loss_uniform), out, _stream(stream)))
     return tuple(out)
+
+
+def mc_side_l2(detector: Detector, tally: Tally, target, stream=None):
+    """(loss, dLoss/dI) of the variance-corrected L2 loss of `tally`'s side
+    image (filled by mc_simulate with MC_MOMENTS) against `target` (float64
+    device tensor): a 0-d tensor and an image, both enqueued."""
+    import torch
+    n = detector.side_ny * detector.side_nx
+    target = _require(target, "target", torch.float64, numel=n)
+    tally.validate(detector, target=target)
+    g = torch.empty_like(tally.side)
+    loss = torch.empty((), dtype=torch.float64, device=g.device)
+    tc = tally._c()
+    _check(lib().mc_side_l2(C.byref(detector), C.byref(tc), _ptr(target), _ptr(g), _ptr(loss), _stream(stream)))
+    return loss, g
 
 
 def _batch_items(items) -> "C.Array":

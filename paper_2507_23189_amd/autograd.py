@@ -17,7 +17,7 @@ side_l2_loss(mu_sca, mu_abs, target, sim)
 from __future__ import annotations
 
 from ._capi import (MC_EXIT_LOG, MC_MEDIUM_MU, MC_MOMENTS, MC_S_SIDE_W2, Detector, Geometry, Medium, Run, Source, Tally, mc_grad,
-                    mc_simulate)
+                    mc_side_l2, mc_simulate)
 
 
 class SideImage:
@@ -86,10 +86,16 @@ def _functions():
         @staticmethod
         def forward(ctx, mu_sca, mu_abs, target, sim):
             med, tally = sim.run_walk(float(mu_sca), float(mu_abs))
-            diff = tally.side - target
-            loss = (diff * diff).sum() - tally.scalars[MC_S_SIDE_W2]
+            # The library's pass reads a target laid out as the image; another
+            # (broadcast, strided, float32) goes through tensor operations.
+            if (type(target) is torch.Tensor and target.dtype == torch.float64 and target.shape == tally.side.shape
+                    and target.is_contiguous() and target.device == tally.side.device):
+                loss, ctx.g = mc_side_l2(sim.detector, tally, target)
+            else:
+                diff = tally.side - target
+                loss = (diff * diff).sum() - tally.scalars[MC_S_SIDE_W2]
+                ctx.g = (2.0 * diff).contiguous()
             ctx.sim, ctx.med, ctx.tally = sim, med, tally
-            ctx.g = (2.0 * diff).contiguous()
             ctx.dtypes = (mu_sca.dtype, mu_sca.device, mu_abs.dtype, mu_abs.device)
             return loss
 

@@ -1223,46 +1223,116 @@ __global__ void philox_blocks_kernel(uint32_t k0, uint32_t k1, uint32_t instance
     out[4 * t + 3] = r.r3;
 }
 
-// sum_p g_p M_k[p], sum_p g_p M_L[p] and, with per-pixel h, sum_p h_p M2_k[p]
-// and sum_p h_p M2_L[p], in two passes with a fixed order (deterministic):
-// block b of grad_partial sums pixels b x 1024 + t + j x (gridDim x 1024) per
-// lane t, then over the block by a fixed tree, into part[4 b .. 4 b + 3];
-// grad_final adds the blocks' partials in block order.  With a uniform h
-// instead, h times the image-wide second moments.
-__global__ __launch_bounds__(1024) void grad_partial(const double *g, const double *h, const double *wk,
-                                                     const double *wl, const double *w2k, const double *w2l,
-                                                     uint64_t n, double *part)
+// Sums over an image in two kernels and a fixed order (deterministic): block b
+// of the first takes pixels b x 1024 + t + j x (gridDim x 1024) in lane t, adds
+// over its waves by a fixed tree and over the waves in order, and leaves N
+// partials in part[N b ...]; sum_parts adds those of up to kSumBlocks blocks,
+// one per lane of a block of that size, in the same way.  They are bound by
+// launch and latency, not by the bytes (512 x 512: 6 MB, 1.3 us at the card's
+// copy rate): 2048 pixels per block and the partials added side by side take
+// 8.9 us for mc_grad's two kernels where 8192 per block and one chain took 11.9.
+constexpr uint32_t kSumThreads = 1024, kSumBlocks = 256;
+template <int N>
+__device__ __forceinline__ void block_sum(double (&acc)[N], double (&s_part)[N][kSumThreads / 64])
 {
-    __shared__ double s_red[4][1024];
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+    const uint32_t wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+#pragma unroll
+    for (int c = 0; c < N; ++c) {
+        acc[c] = wave_sum(acc[c]);
+        if (__lane_id() == 0) s_part[c][wave] = acc[c];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < N; ++c) {
+        acc[c] = 0.0;
+        for (uint32_t w = 0; w < waves; ++w) acc[c] += s_part[c][w];
+    }
+}
+
+template <int N>
+__device__ __forceinline__ void sum_parts(const double *part, uint32_t n_blocks, double (&acc)[N])
+{
+    __shared__ double s_part[N][kSumThreads / 64];
+#pragma unroll
+    for (int c = 0; c < N; ++c) acc[c] = threadIdx.x < n_blocks ? part[N * threadIdx.x + c] : 0.0;
+    block_sum(acc, s_part);
+}
+
+// The blocks such a sum over n pixels takes, N partials each, with room for
+// `room` doubles.
+template <int N>
+uint32_t sum_blocks(uint64_t n, uint64_t room)
+{
+    return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>({kSumBlocks, (n + 2047) / 2048, room / N}));
+}
+
+// sum_p g_p M_k[p], sum_p g_p M_L[p] and, with per-pixel h (H), sum_p h_p
+// M2_k[p] and sum_p h_p M2_L[p].
+template <bool H>
+__global__ __launch_bounds__(kSumThreads) void grad_partial(const double *g, const double *h, const double *wk,
+                                                            const double *wl, const double *w2k, const double *w2l,
+                                                            uint64_t n, double *part)
+{
+    constexpr int N = H ? 4 : 2;
+    __shared__ double s_part[N][kSumThreads / 64];
+    double acc[N] = {};
+    const uint64_t stride = (uint64_t)gridDim.x * kSumThreads;
+    for (uint64_t i = (uint64_t)blockIdx.x * kSumThreads + threadIdx.x; i < n; i += stride) {
         acc[0] = fma(g[i], wk[i], acc[0]);
         acc[1] = fma(g[i], wl[i], acc[1]);
-        if (h) {
+        if constexpr (H) {
             acc[2] = fma(h[i], w2k[i], acc[2]);
             acc[3] = fma(h[i], w2l[i], acc[3]);
         }
     }
-    for (int c = 0; c < 4; ++c) s_red[c][threadIdx.x] = acc[c];
-    __syncthreads();
-    for (int off = blockDim.x / 2; off > 0; off >>= 1) {
-        if ((int)threadIdx.x < off)
-            for (int c = 0; c < 4; ++c) s_red[c][threadIdx.x] += s_red[c][threadIdx.x + off];
-        __syncthreads();
-    }
-    if (threadIdx.x < 4) part[4 * (uint64_t)blockIdx.x + threadIdx.x] = s_red[threadIdx.x][0];
+    block_sum(acc, s_part);
+    if (threadIdx.x == 0)
+        for (int c = 0; c < N; ++c) part[N * blockIdx.x + c] = acc[c];
 }
 
-__global__ void grad_final(const double *part, uint32_t n_blocks, bool per_pixel_h, double h_uniform,
-                           const double *scalars, double *out)
+// With a uniform h instead, h times the image-wide second moments.
+template <bool H>
+__global__ __launch_bounds__(kSumBlocks) void grad_final(const double *part, uint32_t n_blocks, double h_uniform,
+                                                         const double *scalars, double *out)
 {
-    if (threadIdx.x >= 4) return;
-    double v = 0.0;
-    for (uint32_t b = 0; b < n_blocks; ++b) v += part[4 * (uint64_t)b + threadIdx.x];
-    if (!per_pixel_h && threadIdx.x >= 2)
-        v = h_uniform != 0.0 ? h_uniform * scalars[threadIdx.x == 2 ? MC_S_SIDE_W2K : MC_S_SIDE_W2L] : 0.0;
-    out[threadIdx.x] = v;
+    double acc[H ? 4 : 2];
+    sum_parts(part, n_blocks, acc);
+    if (threadIdx.x != 0) return;
+    out[0] = acc[0];
+    out[1] = acc[1];
+    if constexpr (H) {
+        out[2] = acc[2];
+        out[3] = acc[3];
+    } else {
+        out[2] = h_uniform != 0.0 ? h_uniform * scalars[MC_S_SIDE_W2K] : 0.0;
+        out[3] = h_uniform != 0.0 ? h_uniform * scalars[MC_S_SIDE_W2L] : 0.0;
+    }
+}
+
+// The side image's squared distance from a target less sum w^2, and its
+// derivative 2 (I - T), in one pass over the images where tensor operations
+// take five.
+__global__ __launch_bounds__(kSumThreads) void l2_partial(const double *side, const double *target, uint64_t n,
+                                                          double *g, double *part)
+{
+    __shared__ double s_part[1][kSumThreads / 64];
+    double acc[1] = {0.0};
+    const uint64_t stride = (uint64_t)gridDim.x * kSumThreads;
+    for (uint64_t i = (uint64_t)blockIdx.x * kSumThreads + threadIdx.x; i < n; i += stride) {
+        const double d = side[i] - target[i];
+        g[i] = 2.0 * d;
+        acc[0] = fma(d, d, acc[0]);
+    }
+    block_sum(acc, s_part);
+    if (threadIdx.x == 0) part[blockIdx.x] = acc[0];
+}
+
+__global__ __launch_bounds__(kSumBlocks) void l2_final(const double *part, uint32_t n_blocks, const double *scalars,
+                                                       double *loss)
+{
+    double acc[1];
+    sum_parts(part, n_blocks, acc);
+    if (threadIdx.x == 0) *loss = acc[0] - scalars[MC_S_SIDE_W2];
 }
 
 bool finite_pos(double v) { return std::isfinite(v) && v > 0.0; }
@@ -2255,16 +2325,15 @@ extern "C" int mc_grad(const mc_medium_t *medium, const mc_geometry_t *geometry,
     double *dots = host ? host.data() : (double *)t.workspace + 24;    // scalar words 24..27
     const uint64_t n = (uint64_t)det.side_nx * det.side_ny;
     // The blocks' partials go after the scalar words, where mc_simulate keeps
-    // its image copies (consumed by then): one block per 8192 pixels, at most
-    // 256, and no more than the workspace holds.
+    // its image copies (consumed by then), as many as the workspace holds.
     double *part = (double *)t.workspace + kWsScalarWords;
     const uint64_t room = t.workspace_bytes / 8 - kWsScalarWords;
-    const uint32_t n_blocks = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>({256, (n + 8191) / 8192, room / 4}));
-    hipLaunchKernelGGL(grad_partial, dim3(n_blocks), dim3(1024), 0, st, dloss_dside, d2loss_dside2,
-                       (const double *)t.side_wk, (const double *)t.side_wl, (const double *)t.side_w2k,
-                       (const double *)t.side_w2l, n, part);
-    hipLaunchKernelGGL(grad_final, dim3(1), dim3(64), 0, st, (const double *)part, n_blocks,
-                       d2loss_dside2 != nullptr, d2loss_uniform, (const double *)t.scalars, dots);
+    const uint32_t n_blocks = d2loss_dside2 ? sum_blocks<4>(n, room) : sum_blocks<2>(n, room);
+    hipLaunchKernelGGL(d2loss_dside2 ? grad_partial<true> : grad_partial<false>, dim3(n_blocks), dim3(kSumThreads), 0,
+                       st, dloss_dside, d2loss_dside2, (const double *)t.side_wk, (const double *)t.side_wl,
+                       (const double *)t.side_w2k, (const double *)t.side_w2l, n, part);
+    hipLaunchKernelGGL(d2loss_dside2 ? grad_final<true> : grad_final<false>, dim3(1), dim3(kSumBlocks), 0, st,
+                       (const double *)part, n_blocks, d2loss_uniform, (const double *)t.scalars, dots);
     MC_HIP_CHECK(hipGetLastError());
     double d[4];
     MC_HIP_CHECK(wait_result(d, 4, dots, host, st));
@@ -2274,6 +2343,32 @@ extern "C" int mc_grad(const mc_medium_t *medium, const mc_geometry_t *geometry,
     out_grad[1] = -d[1] - gq_a;
     const bool have_sigma = m.sigma_sca_mm2 != 0.0 || m.sigma_abs_mm2 != 0.0;
     out_grad[2] = have_sigma ? m.sigma_sca_mm2 * out_grad[0] + m.sigma_abs_mm2 * out_grad[1] : NAN;
+    return MC_OK;
+}
+
+extern "C" int mc_side_l2(const mc_detector_t *detector, const mc_tally_t *tally, const double *target,
+                          double *dloss_dside, double *loss, void *stream)
+{
+    using namespace mcmie;
+    clear_error();
+    if (!detector || !tally || !target || !dloss_dside || !loss) return fail(MC_EINVAL, "mc_side_l2: null argument");
+    const mc_detector_t det = *detector;
+    const mc_tally_t t = *tally;
+    if (det.side_nx < 1 || det.side_ny < 1) return fail(MC_EINVAL, "mc_side_l2: side image dimensions must be >= 1");
+    if (det.flags & MC_FIX64) return fail(MC_EINVAL, "mc_side_l2: needs a double side image (no MC_FIX64)");
+    if (!t.side || !t.scalars) return fail(MC_EINVAL, "mc_side_l2: the tally has no side image or scalars");
+    if (!t.workspace || ((uintptr_t)t.workspace & 7) || t.workspace_bytes < (kWsScalarWords + 1) * 8)
+        return fail(MC_EINVAL, "mc_side_l2: workspace of at least %llu bytes required",
+                    (unsigned long long)((kWsScalarWords + 1) * 8));
+    hipStream_t st = (hipStream_t)stream;
+    const uint64_t n = (uint64_t)det.side_nx * det.side_ny;
+    double *part = (double *)t.workspace + kWsScalarWords;   // as mc_grad's
+    const uint32_t n_blocks = sum_blocks<1>(n, t.workspace_bytes / 8 - kWsScalarWords);
+    hipLaunchKernelGGL(l2_partial, dim3(n_blocks), dim3(kSumThreads), 0, st, (const double *)t.side, target, n,
+                       dloss_dside, part);
+    hipLaunchKernelGGL(l2_final, dim3(1), dim3(kSumBlocks), 0, st, (const double *)part, n_blocks,
+                       (const double *)t.scalars, loss);
+    MC_HIP_CHECK(hipGetLastError());
     return MC_OK;
 }
 
