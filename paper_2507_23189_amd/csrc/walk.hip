@@ -128,6 +128,7 @@ struct WalkArgs {
     unsigned long long *ws_img;    // workspace: kCopies x n_pix fixed-point weight sums
     unsigned long long *ws_img2;   // workspace (MC_SIGMA): kCopies x n_pix squared-weight sums
     uint64_t n_pix;
+    uint32_t spread;          // the image copies are permuted (spread_pixel); without the exit log
     uint32_t copy_mask;       // image copy of a wave: XCC_ID & copy_mask (kCopies - 1, or 0 for one copy)
     int32_t *rec_i;
     float *rec_f;
@@ -233,6 +234,22 @@ __device__ __forceinline__ double wave_sum(double v)
 }
 
 
+// Where the copies of an image of n pixels hold pixel p: every whole block of
+// 4096 is permuted, so that neighbours lie 265 words apart.  Exits crowd around
+// the beam, and atomics on one 64-byte line, or on lines of few L2 channels,
+// wait for each other (83 million a second on one word; 24 thousand million on
+// the whole card, at best and for any number of copies).  1e9 atomics around
+// the centre, spread as a normal distribution of 2, 5, 10 and 40 pixels, mean
+// over images of 64 x 64 to 1024 x 1024, ms: in order 146 / 79 / 69 / 55, so
+// 106 / 58 / 49 / 48, blocks of 1024 116 / 60 / 49 / 48.
+constexpr uint32_t kSpreadBits = 12, kSpreadMul = 265, kSpreadShift = 37;
+__device__ __forceinline__ uint32_t spread_pixel(uint32_t p, uint32_t n)
+{
+    const uint32_t block = p >> kSpreadBits;
+    const uint32_t at = (p * kSpreadMul + block * kSpreadShift) & ((1u << kSpreadBits) - 1u);
+    return block < n >> kSpreadBits ? (block << kSpreadBits) | at : p;
+}
+
 constexpr int kQueue = 64;                 // queued image exits per wave
 constexpr uint32_t kEmpty = 0xFFFFFFFFu;   // free tally-cache slot
 // Steps a wave takes at most before it looks again whether any of its photons
@@ -274,6 +291,12 @@ constexpr int kOptSigma = 1, kOptRecord = 2, kOptMoments = 4, kOptBatch = 8, kOp
 // LDS allows (one binning block per range and copy).
 constexpr uint32_t kLogMinRangeBits = 6;
 constexpr uint32_t kLogHistBits = 13;      // keys per binning block: 2^13 (64 KB of int64 sums)
+constexpr uint32_t inverse_mod_2_32(uint32_t m)   // of an odd m (Newton: x <- x (2 - m x))
+{
+    uint32_t x = m;
+    for (int i = 0; i < 5; ++i) x *= 2u - m * x;
+    return x;
+}
 constexpr uint32_t kLogHashMul = 0x9E3779B1u;
 __device__ __forceinline__ uint32_t log_scramble(uint32_t key, uint32_t bits)
 {
@@ -433,8 +456,10 @@ void walk_kernel(WalkArgs a)
             asm volatile("" : "+s"(dim[0]), "+s"(dim[1]), "+s"(dim[2]), "+s"(dim[3]));
             const float per_row = side ? scale[0] : scale[2], per_col = side ? scale[1] : scale[3];
             const int n_row = side ? dim[0] : dim[2], n_col = side ? dim[1] : dim[3];
-            key = key_base + (side ? 0u : ra->n_side) +
-                  (uint32_t)(pixel_scaled(y, per_row, n_row) * n_col + pixel_scaled(b, per_col, n_col));
+            const uint32_t pix = (uint32_t)(pixel_scaled(y, per_row, n_row) * n_col + pixel_scaled(b, per_col, n_col));
+            key = key_base + (side ? 0u : ra->n_side);
+            if (LOG) key += pix;
+            else key += spread_pixel(pix, ra->spread ? (side ? ra->n_side : ra->n_pix_inst - ra->n_side) : 0u);
         }
         bool to_image = act;
         if (LOG) {
@@ -1102,11 +1127,17 @@ __global__ __launch_bounds__(1024) void log_bin(const unsigned long long *log, c
 // Unscattered first-step exits were only counted (workspace word kWsBallistic
 // of each medium); the beam pixel (word kWsBeamKey) gets count x ball_w.
 //
-// A block takes kFinBlock pixels of one image.  Their weights' sum, its share of
-// the +x or +z face's total, replaces its first pixel in copy 0 (which no other
-// block reads) for finalize_scalars to add up: an atomic per block on one word
-// took 12 ns each, one after the other, 12 of the 21 us at 512 x 512.
-constexpr int kFinThreads = 256, kFinPix = 4, kFinBlock = kFinThreads * kFinPix;
+// A block takes kFinPix pixels per thread of one image; with SPREAD they are a
+// block of spread_pixel, which it undoes through LDS.  Their weights' sum, its
+// share of the +x or +z face's total, replaces its first word in copy 0 (which
+// no other block reads) for finalize_scalars to add up: an atomic per block on
+// one word took 12 ns each, one after the other, 12 of the 21 us at 512 x 512.
+constexpr int kFinPix = 4;
+template <bool SPREAD>
+constexpr int fin_threads() { return SPREAD ? 1024 : 256; }
+template <bool SPREAD>
+constexpr int fin_block() { return fin_threads<SPREAD>() * kFinPix; }
+static_assert(fin_block<true>() == 1 << kSpreadBits, "a block undoes one permutation");
 struct FinArgs {
     unsigned long long *copies[2];     // of the weights and of their squares
     void *side[2], *trans[2];
@@ -1116,18 +1147,22 @@ struct FinArgs {
     uint32_t n_pix, n_side;
     const unsigned long long *ws_scal;
     double *scalars;
+    int fix, add;                      // int64 images; add to the outputs
+    uint32_t block;                    // pixels per block of finalize_images
 };
 
-template <bool FIX, bool ADD>
-__global__ __launch_bounds__(kFinThreads) void finalize_images(FinArgs a)
+template <bool SPREAD>
+__global__ __launch_bounds__(fin_threads<SPREAD>()) void finalize_images(FinArgs a)
 {
+    constexpr int kThreads = fin_threads<SPREAD>(), kBlock = fin_block<SPREAD>();
     const uint64_t inst = blockIdx.y;
     const int z = blockIdx.z;
-    const uint32_t side_blocks = (a.n_side + kFinBlock - 1) / kFinBlock;
+    const uint32_t side_blocks = (a.n_side + kBlock - 1) / kBlock;
     const bool is_side = blockIdx.x < side_blocks;
-    const uint32_t first = is_side ? blockIdx.x * kFinBlock : a.n_side + (blockIdx.x - side_blocks) * kFinBlock;
+    const uint32_t nth = is_side ? blockIdx.x : blockIdx.x - side_blocks;
+    const uint32_t first = (is_side ? 0u : a.n_side) + nth * kBlock;
     // (differences, which stay below 2^32 where an index past the end may not)
-    const uint32_t n_here = min((is_side ? a.n_side : a.n_pix) - first, (uint32_t)kFinBlock);
+    const uint32_t n_here = min((is_side ? a.n_side : a.n_pix) - first, (uint32_t)kBlock);
     unsigned long long *copies = a.copies[z] + inst * a.n_pix;
     long long *out = (long long *)(is_side ? a.side[z] : a.trans[z]) +
                      (is_side ? inst * a.n_side : inst * (a.n_pix - a.n_side) - a.n_side);
@@ -1138,39 +1173,59 @@ __global__ __launch_bounds__(kFinThreads) void finalize_images(FinArgs a)
     long long prev[kFinPix];
 #pragma unroll
     for (int u = 0; u < kFinPix; ++u) {
-        const uint32_t k = u * kFinThreads + threadIdx.x, i = first + k;
+        const uint32_t k = u * kThreads + threadIdx.x, i = first + k;
         const bool in = k < n_here;
 #pragma unroll
         for (int c = 0; c < kCopies; ++c) part[u][c] = in && c < a.n_copies ? copies[(uint64_t)c * a.n_total + i] : 0ull;
-        prev[u] = ADD && in ? out[i] : 0ll;   // the output's bits (int64, or a double's)
+        prev[u] = a.add && in ? out[i] : 0ll;   // the output's bits (int64, or a double's)
+    }
+    unsigned long long v[kFinPix];
+#pragma unroll
+    for (int u = 0; u < kFinPix; ++u) {
+        v[u] = 0ull;
+#pragma unroll
+        for (int c = 0; c < kCopies; ++c) v[u] += part[u][c];
+    }
+    if (SPREAD) {
+        // The word at k is that of pixel (k - shift) / kSpreadMul in a whole block.
+        constexpr uint32_t inv = inverse_mod_2_32(kSpreadMul);
+        __shared__ unsigned long long s_pix[kBlock];
+#pragma unroll
+        for (int u = 0; u < kFinPix; ++u) {
+            const uint32_t k = u * kThreads + threadIdx.x;
+            s_pix[n_here == (uint32_t)kBlock ? ((k - nth * kSpreadShift) * inv) & (kBlock - 1) : k] = v[u];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kFinPix; ++u) v[u] = s_pix[u * kThreads + threadIdx.x];
     }
     unsigned long long sum = 0ull;
 #pragma unroll
     for (int u = 0; u < kFinPix; ++u) {
-        const uint32_t k = u * kFinThreads + threadIdx.x, i = first + k;
+        const uint32_t k = u * kThreads + threadIdx.x, i = first + k;
         if (k >= n_here) break;
-        unsigned long long v = 0ull;
-#pragma unroll
-        for (int c = 0; c < kCopies; ++c) v += part[u][c];
-        if (beam_key == (uint64_t)i + 1) v += beam_v;
-        if (FIX) out[i] = prev[u] + (long long)v;
-        else ((double *)out)[i] = __longlong_as_double(prev[u]) + (double)(long long)v * (1.0 / kFix);
-        sum += v;
+        if (beam_key == (uint64_t)i + 1) v[u] += beam_v;
+        if (a.fix) out[i] = prev[u] + (long long)v[u];
+        else ((double *)out)[i] = __longlong_as_double(prev[u]) + (double)(long long)v[u] * (1.0 / kFix);
+        sum += v[u];
     }
     if (z != 0) return;
-    __shared__ unsigned long long s_part[kFinThreads / 64];
+    __shared__ unsigned long long s_part[kThreads / 64];
     sum = wave_sum(sum);
     if (__lane_id() == 0) s_part[threadIdx.x >> 6] = sum;
-    __syncthreads();   // (every pixel of the block has been read)
-    if (threadIdx.x == 0) copies[first] = s_part[0] + s_part[1] + s_part[2] + s_part[3];
+    __syncthreads();   // (every word of the block has been read)
+    if (threadIdx.x < 64) {
+        sum = wave_sum(threadIdx.x < kThreads / 64 ? s_part[threadIdx.x] : 0ull);
+        if (threadIdx.x == 0) copies[first] = sum;
+    }
 }
 
 // Fixed-point scalar sums to the caller's doubles (weights scaled back by
 // 2^-32, counts as they are); the second-order side moments are FP64 sums.
 // The +x and +z faces' totals are those of their images, added up from the
 // blocks of finalize_images.  One medium per block.
-template <bool ADD>
-__global__ __launch_bounds__(kFinThreads) void finalize_scalars(FinArgs a)
+constexpr int kScalThreads = 256;
+__global__ __launch_bounds__(kScalThreads) void finalize_scalars(FinArgs a)
 {
     const uint64_t inst = blockIdx.x;
     const unsigned long long *ws_scal = a.ws_scal + inst * kWsScalarWords;
@@ -1178,9 +1233,9 @@ __global__ __launch_bounds__(kFinThreads) void finalize_scalars(FinArgs a)
     double *scalars = a.scalars + inst * MC_N_SCALARS;
     const int t = threadIdx.x;
     unsigned long long face[2] = {0ull, 0ull};
-    for (uint64_t i = t * kFinBlock; i < a.n_side; i += kFinThreads * kFinBlock) face[0] += copies[i];
-    for (uint64_t i = (uint64_t)a.n_side + t * kFinBlock; i < a.n_pix; i += kFinThreads * kFinBlock) face[1] += copies[i];
-    __shared__ unsigned long long s_face[2][kFinThreads / 64];
+    for (uint64_t i = t * a.block; i < a.n_side; i += kScalThreads * a.block) face[0] += copies[i];
+    for (uint64_t i = (uint64_t)a.n_side + t * a.block; i < a.n_pix; i += kScalThreads * a.block) face[1] += copies[i];
+    __shared__ unsigned long long s_face[2][kScalThreads / 64];
     for (int f = 0; f < 2; ++f) {
         const unsigned long long v = wave_sum(face[f]);
         if (__lane_id() == 0) s_face[f][t >> 6] = v;
@@ -1205,7 +1260,7 @@ __global__ __launch_bounds__(kFinThreads) void finalize_scalars(FinArgs a)
     } else if (t >= MC_S_SIDE_W2 && t <= MC_S_SIDE_W2L) {
         v = __longlong_as_double((long long)ws_scal[t]);
     }
-    scalars[t] = ADD ? scalars[t] + v : v;
+    scalars[t] = a.add ? scalars[t] + v : v;
 }
 
 __global__ void philox_blocks_kernel(uint32_t k0, uint32_t k1, uint32_t instance, const uint64_t *ids,
@@ -1801,6 +1856,11 @@ int launch_walk(WalkArgs &a, const mc_detector_t &det, const mc_run_t &rn, const
     const bool spread = n_total <= (1u << 17) && total_photons >= (1u << 24);
     const uint32_t n_cleared = use_log && !spread ? 1u : (uint32_t)copies;
     a.copy_mask = n_cleared - 1;
+    // Permuted copies pay where many exits meet (one medium, tau = 1, in order and
+    // permuted, us: 1e7 photons, 150 x 150 295 / 230, 512 x 512 335 / 303, 700 x 700
+    // 384 / 332, but 1024 x 1024 340 / 346; 1e8 2505 / 1847, 2523 / 2317, 3208 / 2540, 2585 /
+    // 2434; 3e6, 150 x 150 122 / 127, 700 x 700 154 / 155).
+    a.spread = !use_log && !batch && total_photons > std::max<uint64_t>(1u << 22, 8 * n_pix);
     a.ws_img2 = (det.flags & MC_SIGMA) ? a.ws_img + copies * n_total : nullptr;
     if (lds > 160 * 1024) return fail(MC_EINVAL, "mc_simulate: %zu bytes of LDS per block do not fit a CU", lds);
     const uint64_t waves_total = (uint64_t)grid * (block / 64);
@@ -1907,15 +1967,13 @@ int launch_walk(WalkArgs &a, const mc_detector_t &det, const mc_run_t &rn, const
         if (rn.walk_events[1]) MC_HIP_CHECK(hipEventRecord((hipEvent_t)rn.walk_events[1], st));
     }
     if (use_log && units > 0) {
-        uint32_t inv = kLogHashMul;   // inverse of the odd multiplier mod 2^32 (Newton: x <- x (2 - m x))
-        for (int i = 0; i < 5; ++i) inv *= 2u - kLogHashMul * inv;
         const size_t hist = ((size_t)8 << kLogHistBits) * (sig ? 2 : 1);
         auto bin = sig ? log_bin<true> : log_bin<false>;
         MC_HIP_CHECK(hipFuncSetAttribute((const void *)bin, hipFuncAttributeMaxDynamicSharedMemorySize, (int)hist));
         hipLaunchKernelGGL(bin, dim3((1u << a.log_rbits) * parts * (uint32_t)copies), dim3(1024), hist, st,
                            (const unsigned long long *)a.log, (const uint32_t *)a.log_count, a.log_cap,
                            (uint32_t)grid, a.ws_img, a.ws_img2, (uint32_t)copies, n_cleared, n_total, parts,
-                           a.log_bits, a.log_rbits, inv);
+                           a.log_bits, a.log_rbits, inverse_mod_2_32(kLogHashMul));
         MC_HIP_CHECK(hipGetLastError());
     }
     // ---- finalize: per-XCD copies to the caller's images, scalars to doubles ----
@@ -1936,12 +1994,14 @@ int launch_walk(WalkArgs &a, const mc_detector_t &det, const mc_run_t &rn, const
     f.n_side = (uint32_t)n_side;
     f.ws_scal = ws;
     f.scalars = t.scalars;
-    const unsigned fin_x = (unsigned)((n_side + kFinBlock - 1) / kFinBlock + (n_trans + kFinBlock - 1) / kFinBlock);
-    auto fin = zero_all ? (fix64 ? finalize_images<true, false> : finalize_images<false, false>)
-                        : (fix64 ? finalize_images<true, true> : finalize_images<false, true>);
-    hipLaunchKernelGGL(fin, dim3(fin_x, n_inst, sig ? 2 : 1), dim3(kFinThreads), 0, st, f);
-    hipExtLaunchKernelGGL(zero_all ? finalize_scalars<false> : finalize_scalars<true>, dim3(n_inst), dim3(kFinThreads), 0,
-                          st, nullptr, (hipEvent_t)rn.sim_events[1], 0u, f);
+    f.fix = fix64;
+    f.add = !zero_all;
+    f.block = a.spread ? fin_block<true>() : fin_block<false>();
+    const unsigned fin_x = (unsigned)((n_side + f.block - 1) / f.block + (n_trans + f.block - 1) / f.block);
+    hipLaunchKernelGGL(a.spread ? finalize_images<true> : finalize_images<false>, dim3(fin_x, n_inst, sig ? 2 : 1),
+                       dim3(a.spread ? fin_threads<true>() : fin_threads<false>()), 0, st, f);
+    hipExtLaunchKernelGGL(finalize_scalars, dim3(n_inst), dim3(kScalThreads), 0, st, nullptr,
+                          (hipEvent_t)rn.sim_events[1], 0u, f);
     MC_HIP_CHECK(hipGetLastError());
     return MC_OK;
 }

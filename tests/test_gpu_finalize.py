@@ -1,5 +1,5 @@
 """From the summed copies to the caller's images (-m gpu): pixel counts at the
-edges of a block of 1024, images of one pixel, sums written and added, int64 and
+edges of a block, images of one pixel, sums written and added, int64 and
 double, squared weights in the same launch, the copies of one medium or several.
 The oracle walks the same photons; sums of fixed-point weights are exact, so
 everything here is compared exactly with them or with each other."""
@@ -11,7 +11,8 @@ import workloads as W
 pytestmark = pytest.mark.gpu
 
 N = 20_000
-SHAPES = [(1, 1, 1, 1), (1, 1023, 32, 32), (1025, 1, 1, 1), (32, 32, 3, 683), (45, 91, 1, 1), (7, 3, 64, 32)]
+SHAPES = [(1, 1, 1, 1), (1, 1023, 32, 32), (1025, 1, 1, 1), (32, 32, 3, 683), (45, 91, 1, 1), (7, 3, 64, 32),
+          (64, 64, 4095, 1), (17, 241, 64, 128), (63, 65, 3, 2731), (200, 123, 256, 80)]    # and of 4096
 
 
 @pytest.fixture(scope="module")
@@ -92,3 +93,46 @@ def test_media_of_a_batch_keep_their_own_images(mc, table, cuda_device, shape):
         ref = _run(mc, alone, mc.Tally.alloc(det, "cuda", fix64=True))
         for k in ("side", "trans", "scalars"):
             assert np.array_equal(getattr(tally, k)[i].cpu().numpy().ravel(), ref[k]), (tau, k)
+
+
+@pytest.mark.parametrize("shape", [(64, 64, 100, 100), (200, 123, 256, 80)], ids=str)
+def test_pixels_keep_their_places(mc, table, cuda_device, shape):
+    """The exits of recorded photons, put into pixels here, give the images."""
+    import torch
+    med, src, geo, det, run = _args(mc, table, shape, mc.MC_RECORD)
+    t = mc.Tally.alloc(det, "cuda", record_rows=N)
+    mc.mc_simulate(med, src, geo, det, run, t)
+    torch.cuda.synchronize()
+    face, (x, y, z), w = t.rec_i[0].cpu().numpy(), t.rec_f[:3].cpu().numpy(), t.rec_f[6].cpu().numpy()
+    sx, sy, sz = geo.size_mm
+
+    def index(v, size, n):
+        return np.clip((v.astype(np.float32) * np.float32(n / size)).astype(int), 0, n - 1)
+    for f, img, row, col in ((1, t.side, index(y, sy, shape[1]), index(z, sz, shape[0])),
+                             (5, t.trans, index(y, sy, shape[3]), index(x, sx, shape[2]))):
+        ref = np.zeros(img.shape)
+        on = face == f
+        np.add.at(ref, (row[on], col[on]), w[on])
+        # A photon on a pixel's edge may round into the next one.
+        moved = np.abs(img.cpu().numpy() - ref).sum()
+        assert on.sum() > 100 and moved <= 2e-3 * ref.sum()
+
+
+@pytest.mark.parametrize("flags", [0, 1], ids=["double", "int64"])
+@pytest.mark.parametrize("shape", [(1, 1, 4096, 1), (1, 4095, 64, 65), (200, 123, 256, 80), (181, 181, 5, 3)], ids=str)
+def test_copies_in_another_order(mc, table, cuda_device, shape, flags):
+    """Past 2^22 photons the copies hold the pixels of each whole block of 4096
+    in another order (the exit log does not): written and added images."""
+    flags = mc.MC_FIX64 if flags else 0
+    out = []
+    for extra, times, n in ((mc.MC_EXIT_LOG, 1, (1 << 22) + 1), (0, 1, (1 << 22) + 1),
+                            (mc.MC_ACCUMULATE, 2, (1 << 22) + 1), (0, 1, 1 << 22), (mc.MC_EXIT_LOG, 1, 1 << 22)):
+        args = _args(mc, table, shape, flags | extra, tau=0.5)
+        args[4].n_photons = n
+        t = mc.Tally.alloc(args[3], "cuda", fix64=bool(flags), log_photons=n)
+        for img in (t.side, t.trans, t.scalars):
+            img.fill_(0)
+        out.append(_run(mc, args, t, times))
+    for k in ("side", "trans", "scalars"):
+        assert np.array_equal(out[0][k], out[1][k]) and np.array_equal(2 * out[0][k], out[2][k]), k
+        assert np.array_equal(out[3][k], out[4][k]), k
