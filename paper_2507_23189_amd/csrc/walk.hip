@@ -1856,11 +1856,12 @@ int launch_walk(WalkArgs &a, const mc_detector_t &det, const mc_run_t &rn, const
     const bool spread = n_total <= (1u << 17) && total_photons >= (1u << 24);
     const uint32_t n_cleared = use_log && !spread ? 1u : (uint32_t)copies;
     a.copy_mask = n_cleared - 1;
-    // Permuted copies pay where many exits meet (one medium, tau = 1, in order and
+    // Permuted copies pay where many exits meet (tau = 1, in order and
     // permuted, us: 1e7 photons, 150 x 150 295 / 230, 512 x 512 335 / 303, 700 x 700
     // 384 / 332, but 1024 x 1024 340 / 346; 1e8 2505 / 1847, 2523 / 2317, 3208 / 2540, 2585 /
-    // 2434; 3e6, 150 x 150 122 / 127, 700 x 700 154 / 155).
-    a.spread = !use_log && !batch && total_photons > std::max<uint64_t>(1u << 22, 8 * n_pix);
+    // 2434; 3e6, 150 x 150 122 / 127, 700 x 700 154 / 155; batches of 37 to 250 media 2
+    // to 9 % less).
+    a.spread = !use_log && total_photons > std::max<uint64_t>(1u << 22, 8 * n_total);
     a.ws_img2 = (det.flags & MC_SIGMA) ? a.ws_img + copies * n_total : nullptr;
     if (lds > 160 * 1024) return fail(MC_EINVAL, "mc_simulate: %zu bytes of LDS per block do not fit a CU", lds);
     const uint64_t waves_total = (uint64_t)grid * (block / 64);

@@ -136,3 +136,20 @@ def test_copies_in_another_order(mc, table, cuda_device, shape, flags):
     for k in ("side", "trans", "scalars"):
         assert np.array_equal(out[0][k], out[1][k]) and np.array_equal(2 * out[0][k], out[2][k]), k
         assert np.array_equal(out[3][k], out[4][k]), k
+
+
+@pytest.mark.parametrize("shape", [(45, 91, 1, 1), (64, 65, 64, 64)], ids=str)
+def test_copies_of_a_batch_in_another_order(mc, table, cuda_device, shape):
+    import torch
+    med, src, geo, det, run = _args(mc, table, shape, mc.MC_FIX64)
+    out = []
+    for flags in (mc.MC_FIX64, mc.MC_FIX64 | mc.MC_EXIT_LOG):
+        det.flags = flags
+        items = [mc.BatchItem(tau=0.3 * (i + 1), albedo=0.9999, inv_cdf=table.inv_cdf.data_ptr(), n_photons=2_000_000,
+                              instance=i) for i in range(3)]
+        t = mc.Tally.alloc_batch(det, 3, "cuda", fix64=True, log_photons=6_000_000)
+        mc.mc_simulate_batch(items, W.TINY.n_cdf, src, geo, det, run, t)
+        torch.cuda.synchronize()
+        out.append(t)
+    for k in ("side", "trans", "scalars"):
+        assert torch.equal(getattr(out[0], k), getattr(out[1], k)), k
