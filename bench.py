@@ -84,7 +84,11 @@ METRIC = "Mie MC scatter events/s (τ=4, 1e8 photons); fwd+adjoint vs fwd-only t
 # bench/issue_cost_probe.hip at 2.3-2.6, 3.7-4.4 and 8.0-8.2 cycles.  A slot
 # is one full-rate lane-instruction, so a unit costs full + 2 half + 4 trans
 # slots.  A uniform is one funnel shift (23 random bits under the exponent of
-# 1.0) and one subtraction: 1 full, 1 half.
+# 1.0) and one subtraction: 1 full, 1 half.  The census prices the method as
+# written, with wall distances in every step and each random block whole; the
+# walk keeps a photon's part of the block and looks for walls only near them,
+# which at tau = 4 needs 994 slots a photon where the census counts 1172, so
+# frac compares kernels over time and is not the share of busy issue slots.
 #   step         Philox4x32-10 (20 products, 20 three-input XORs: 40 half);
 #                the free-path uniform (1 full, 1 half), its log and the
 #                product by -1/mu (1 full, 1 trans); three wall distances
@@ -142,8 +146,8 @@ PEAK_SLOTS_PER_S = 256 * 4 * 32 * 2.4e9
 # WRITE_SIZE x 1.0); valid only for the tally path and kernel code it was
 # measured on (profiles/walk_tau4_counters.md): the digest covers the walk
 # sources without comments and whitespace, so a comment edit keeps it.
-TRAFFIC = {"tally": "log", "sources_sha256": "38c308aadf57ff13455a2aed5542f66d0dec4c300fd06419b7cc5937b107dc34",
-           "fetch_kib": 374.3, "write_kib": 558765.0, "fetch_factor": 2.0, "write_factor": 1.0}
+TRAFFIC = {"tally": "log", "sources_sha256": "d9e9100ba6c5c590c42bd1572d9c7f1f7eedb876c3de372b0256e93e4e88101c",
+           "fetch_kib": 386.2, "write_kib": 554687.7, "fetch_factor": 2.0, "write_factor": 1.0}
 WALK_SOURCES = ("paper_2507_23189_amd/csrc/walk.hip", "paper_2507_23189_amd/csrc/philox.hpp")
 
 

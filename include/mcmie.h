@@ -146,7 +146,7 @@ typedef struct {
  * Q_ext/Q_sca/g (Eqs. 12-13), S1/S2 (Eqs. 5-6) and the normalised phase
  * function (Eqs. 9-10) on n_angles angles, its CDF in theta, and the inverse
  * table sampled at n_cdf equally spaced probabilities.  It runs as two FP64
- * kernels on `stream` (one lane per angle, then one lane per inverse-table
+ * kernels on `stream` (four lanes per angle, then one lane per inverse-table
  * entry); the call then waits for the stream so the host scalars of `table`
  * are valid on return.  The device buffers of `table` must hold the sizes
  * stated above; without result or work it uses per-device library scratch,
@@ -293,8 +293,9 @@ typedef struct {
     double roulette_p;     /* survival probability in (0, 1]; survivors' weight / p */
     uint64_t record_stride;/* MC_RECORD: photon offset + r * stride goes to row r (>= 1) */
     int32_t block_size;    /* threads per block, multiple of 64 in 64..1024; 0 = library choice */
-    int32_t grid_blocks;   /* blocks; 0 = library choice (enough to fill every CU) */
-    uint32_t chunk;        /* photons a wave claims at a time, 1..65536; 0 = library choice */
+    int32_t grid_blocks;   /* blocks; 0 = library choice (one or two per CU) */
+    uint32_t chunk;        /* photons a wave takes from its block's at a time, 1..65536; 0 = library
+                              choice */
     uint32_t reserved;     /* set to 0 */
     void *walk_events[2];  /* optional hipEvent_t pair (NULL: none): set to the start and the end of
                               the walk kernel, so the caller can time that kernel alone

@@ -36,7 +36,7 @@
 // to the rounds, about 400 cycles each, that run when refill_min lanes wait.
 // Resolving walls in every step, with the distances for all lanes, took 2.69
 // ms at tau = 4 and 8.6 at tau = 16 for 1e8 photons (mc_simulate, 512 x 512,
-// exit log); this takes 2.40 and 6.6.
+// exit log); this takes 2.30 and 6.5.
 //
 // Transport runs in FP32.  Weights are tallied in 64-bit fixed point
 // (weight * 2^32, rounded to nearest): integer sums do not depend on the order
@@ -49,13 +49,16 @@
 //     of every key range and appends at the position an LDS counter of the
 //     block hands out (one LDS add and one store per exit); a second kernel
 //     (log_bin) sums each range in an LDS histogram and writes the sums into
-//     image copies with plain loads and stores; or
+//     image copies with plain loads and stores.  Exits that find their region
+//     full are added as in the other path; or
 //   * adds them into a per-block LDS tally cache (direct-mapped pixel ids
 //     claimed with an LDS compare-and-swap) whose sums go to the images once
-//     per block, with a global atomic into one of eight per-XCD copies of the
-//     images for the pixels that miss the cache.
-// On gfx950 every global image atomic is performed at the memory side, so the
-// log, which needs none, is the faster path.  Unscattered photons all leave
+//     per block, with a global atomic into one of at most eight per-XCD copies
+//     of the images for the pixels that miss the cache.
+// The card performs 24 thousand million global atomics a second at best,
+// whatever the number of copies, so the log, which needs none, is the faster
+// path from a few million photons up; below, the second pass costs more than
+// the atomics, and both paths add directly.  Unscattered photons all leave
 // through one pixel with one weight and are only counted.  A finalize pass
 // sums the copies in integer arithmetic and converts to the caller's images.
 // Scalar tallies use LDS atomics and lane accumulators, flushed once per
