@@ -5,8 +5,8 @@
 //   1. every workgroup runs the Bohren-Huffman series (Sec. 2.5) for itself:
 //      one lane runs the logarithmic derivative D_n(mx) by downward
 //      recurrence (in homogeneous form, D_n = P_n / Q_n, so the serial chain
-//      holds no division) while a lane of another wave runs psi_n(x) and
-//      chi_n(x) upward; then every lane forms a_n and b_n for its n (Eqs. 7-8
+//      holds no division; from 256 steps all lanes of its wave share them)
+//      while a lane of another wave runs psi_n(x) and chi_n(x) upward; then every lane forms a_n and b_n for its n (Eqs. 7-8
 //      divided through by psi_n(mx)), and Q_ext (Eq. 13), Q_sca and the
 //      asymmetry sums (Eq. 12) are added in a fixed order;
 //   2. four lanes evaluate S1, S2 (Eqs. 5-6) at an angle, one each of their real
@@ -27,11 +27,13 @@
 //
 // All of it is bound by the serial chains: a dependent FP64 fma takes about 33
 // cycles on a lone wave, four of them a downward step (two for a real index),
-// two a term of a sum.  The 100 um absorbing sphere (x = 785) takes 57 us of
-// downward steps, hidden behind them 18 of upward ones (33 with a division in
-// each), and 30 of sums; the 5 um one 4.7 and 2.9 of the kernel's 12.6.  Before
-// (one lane per angle, factors formed in the steps, eight fma in every downward
-// step) mie_phase_kernel took 14.4 us at 5 um and 133 at 100 um, the 64 bins 26.5.
+// two a term of a sum.  The 100 um absorbing sphere (x = 785) took 57 us of
+// downward steps one after the other, hidden behind them 18 of upward ones (33
+// with a division in each), and 30 of sums; with the downward steps shared it is
+// the upward ones and the sums, 57 us for the kernel from 105.  The 5 um sphere
+// takes 4.7 and 2.9 of the kernel's 12.  Before (one lane per angle, factors
+// formed in the steps, eight fma in every downward step) mie_phase_kernel took
+// 14.4 us at 5 um and 133 at 100 um, the 64 bins 26.5.
 // Arrays live in LDS (coefficients 32 KB, pi_n recurrence coefficients 16 KB,
 // psi and chi 16 KB, factors 6 KB, angle grid 24 KB at the limits; gfx950 gives
 // a workgroup up to 160 KB).
@@ -117,7 +119,141 @@ struct MieArgs {
 // steps into LDS, and the lane's steps are the recurrence's own fma, a store,
 // and a read of two factors ahead of their use, in groups of eight without
 // branches.
+// Downward recurrences of this many steps and more are taken by all lanes of the
+// wave (downward_scan): below, the steps one after the other end at most a few
+// us after the upward recurrence beside them (whole call, us, one after the other
+// / shared, 1801 angles: x = 190 real 49.1 / 42.2, absorbing 56.9 / 42.3; x = 440
+// 70.1 / 57.1 and 85.9 / 57.8; x = 785 101.7 / 78.4 and 127.9 / 79.4).
+constexpr int kScanFrom = 256;
 constexpr int kChunk = 256, kAhead = 16;   // kAhead: entries before the first that reading ahead may touch
+
+// A vector (P, Q) of the downward recurrence, its step from n to n - 1 with
+// k = n/(mx), and its scaling by a power of two (see mie_series_block).  With a
+// real index the imaginary parts are zero and left out.
+struct Ratio {
+    cplx P, Q;
+};
+template <bool REAL>
+__device__ __forceinline__ void down_step(Ratio &v, cplx k)
+{
+    if (REAL) {
+        const double Q1 = fma(k.re, v.Q.re, v.P.re);
+        v.P.re = fma(k.re, Q1, -v.Q.re);
+        v.Q.re = Q1;
+    } else {
+        const cplx Q1 = {fma(k.re, v.Q.re, fma(-k.im, v.Q.im, v.P.re)), fma(k.re, v.Q.im, fma(k.im, v.Q.re, v.P.im))};
+        v.P = {fma(k.re, Q1.re, fma(-k.im, Q1.im, -v.Q.re)), fma(k.re, Q1.im, fma(k.im, Q1.re, -v.Q.im))};
+        v.Q = Q1;
+    }
+}
+template <bool REAL>
+__device__ __forceinline__ double largest(const Ratio &v)
+{
+    const double top = fmax(fabs(v.P.re), fabs(v.Q.re));
+    return REAL ? top : fmax(fmax(top, fabs(v.P.im)), fabs(v.Q.im));
+}
+template <bool REAL>
+__device__ __forceinline__ void scale_by(Ratio &v, int e)
+{
+    v.P.re = ldexp(v.P.re, e);
+    v.Q.re = ldexp(v.Q.re, e);
+    if (!REAL) {
+        v.P.im = ldexp(v.P.im, e);
+        v.Q.im = ldexp(v.Q.im, e);
+    }
+}
+
+// The downward recurrence (see downward, below) by all lanes of a wave, for long
+// series: its steps are matrices of determinant 1, so each lane multiplies
+// those of its 64th of the steps (both columns at once), a scan over the lanes
+// joins the products, and each lane takes its steps again from the vector that
+// reaches them.  The chain is 2/64 of the steps and six products.  Errors of a_n
+// and b_n against an 80-bit evaluation, 70 spheres of x = 165 to 801 with real
+// and absorbing indices of 1.4 to 2.4: 1.5e-13 root mean square, 8e-13 at most
+// (1.8e-13 and 1.1e-12 one after the other), two thirds of those in the geometric
+// mean.
+template <bool REAL>
+__device__ __forceinline__ void downward_scan(double x, cplx m, int N, int n_start, cplx *s_a, cplx *s_b)
+{
+    const int lane = threadIdx.x & 63;
+    const int len = (n_start + 63) / 64, top = n_start - lane * len;   // this lane's steps: n = top, top - 1, .. (n >= 1)
+    const int steps = min(max(top, 0), len);
+    // 1/(mx) as a sum of two doubles: its rounding would turn every step the same
+    // way.  1 - mx h is exact up to the second order: its products are split by
+    // fma, and the differences of their near-equal leading parts are exact.
+    const cplx mx = {x * m.re, x * m.im};
+    const cplx h = REAL ? cplx{1.0 / mx.re, 0.0} : cplx{1.0, 0.0} / mx;
+    cplx l;
+    {
+        const double lr = fma(x, m.re, -mx.re), li = fma(x, m.im, -mx.im);
+        const double p1 = mx.re * h.re, p2 = mx.im * h.im, p3 = mx.re * h.im, p4 = mx.im * h.re;
+        const double e1 = fma(mx.re, h.re, -p1), e2 = fma(mx.im, h.im, -p2);
+        const double e3 = fma(mx.re, h.im, -p3), e4 = fma(mx.im, h.re, -p4);
+        const cplx r = {((1.0 - p1) + p2) + ((e2 - e1) + (li * h.im - lr * h.re)),
+                        (-p3 - p4) - ((e3 + e4) + (lr * h.im + li * h.re))};
+        l = REAL ? cplx{r.re * h.re, 0.0} : r * h;
+    }
+    auto factor = [&](int n) {
+        const double d = n;
+        return cplx{fma(d, h.re, d * l.re), REAL ? 0.0 : fma(d, h.im, d * l.im)};
+    };
+    // Columns of the product: where the steps take (1, 0) and (0, 1).
+    Ratio c0 = {{1.0, 0.0}, {0.0, 0.0}}, c1 = {{0.0, 0.0}, {1.0, 0.0}};
+    auto rescale = [&]() {
+        int e;
+        (void)frexp(fmax(largest<REAL>(c0), largest<REAL>(c1)), &e);
+        scale_by<REAL>(c0, -e);
+        scale_by<REAL>(c1, -e);
+    };
+    for (int i = 0; i < steps; ++i) {
+        const cplx k = factor(top - i);
+        down_step<REAL>(c0, k);
+        down_step<REAL>(c1, k);
+        if ((i & 7) == 7) rescale();
+    }
+    rescale();
+    auto shifted = [&](const Ratio &v, int by) {
+        Ratio r = {{__shfl_up(v.P.re, by), 0.0}, {__shfl_up(v.Q.re, by), 0.0}};
+        if (!REAL) {
+            r.P.im = __shfl_up(v.P.im, by);
+            r.Q.im = __shfl_up(v.Q.im, by);
+        }
+        return r;
+    };
+    auto apply = [&](const Ratio &v) {   // (c0 c1) v
+        if (REAL)
+            return Ratio{{fma(c0.P.re, v.P.re, c1.P.re * v.Q.re), 0.0}, {fma(c0.Q.re, v.P.re, c1.Q.re * v.Q.re), 0.0}};
+        auto dot = [](cplx a, cplx x, cplx b, cplx y) {
+            return cplx{fma(a.re, x.re, fma(-a.im, x.im, fma(b.re, y.re, -b.im * y.im))),
+                        fma(a.re, x.im, fma(a.im, x.re, fma(b.re, y.im, b.im * y.re)))};
+        };
+        return Ratio{dot(c0.P, v.P, c1.P, v.Q), dot(c0.Q, v.P, c1.Q, v.Q)};
+    };
+    for (int by = 1; by < 64; by *= 2) {
+        const Ratio b0 = shifted(c0, by), b1 = shifted(c1, by);
+        if (lane >= by) {
+            const Ratio n0 = apply(b0), n1 = apply(b1);
+            c0 = n0;
+            c1 = n1;
+            rescale();
+        }
+    }
+    Ratio v = shifted(c1, 1);   // of D_{n_start} = 0: (0, 1)
+    if (lane == 0) v = Ratio{{0.0, 0.0}, {1.0, 0.0}};
+    for (int i = 0; i < steps; ++i) {
+        const int n = top - i;
+        if (n <= N) {
+            s_a[n - 1] = REAL ? cplx{v.P.re, v.Q.re} : v.P;
+            if (!REAL) s_b[n - 1] = v.Q;
+        }
+        down_step<REAL>(v, factor(n));
+        if ((i & 7) == 7) {
+            int e;
+            (void)frexp(largest<REAL>(v), &e);
+            scale_by<REAL>(v, -e);
+        }
+    }
+}
 
 // One wave's downward recurrence of D_n(mx) = P_n / Q_n from n_start (see
 // mie_series_block): P_n to s_a and Q_n to s_b, index n - 1, for n = N..1.  For a
@@ -128,36 +264,19 @@ template <bool REAL>
 __device__ __forceinline__ void downward(cplx inv_mx, int N, int n_start, double2 *s_k, cplx *s_a, cplx *s_b)
 {
     const int lane = threadIdx.x & 63;
-    cplx P = {0.0, 0.0}, Q = {1.0, 0.0};   // D_{n_start} = 0
-    auto step = [&](cplx k) {
-        if (REAL) {
-            const double Q1 = fma(k.re, Q.re, P.re);
-            P.re = fma(k.re, Q1, -Q.re);
-            Q.re = Q1;
-        } else {
-            const cplx Q1 = {fma(k.re, Q.re, fma(-k.im, Q.im, P.re)), fma(k.re, Q.im, fma(k.im, Q.re, P.im))};
-            P = {fma(k.re, Q1.re, fma(-k.im, Q1.im, -Q.re)), fma(k.re, Q1.im, fma(k.im, Q1.re, -Q.im))};
-            Q = Q1;
-        }
-    };
+    Ratio v = {{0.0, 0.0}, {1.0, 0.0}};   // D_{n_start} = 0
+    auto step = [&](cplx k) { down_step<REAL>(v, k); };
     auto rescale = [&]() {   // after each step from a multiple of 8
-        double top = fmax(fabs(P.re), fabs(Q.re));
-        if (!REAL) top = fmax(fmax(fabs(P.re), fabs(P.im)), fmax(fabs(Q.re), fabs(Q.im)));
         int e;
-        (void)frexp(top, &e);
-        P.re = ldexp(P.re, -e);
-        Q.re = ldexp(Q.re, -e);
-        if (!REAL) {
-            P.im = ldexp(P.im, -e);
-            Q.im = ldexp(Q.im, -e);
-        }
+        (void)frexp(largest<REAL>(v), &e);
+        scale_by<REAL>(v, -e);
     };
     auto keep = [&](int n) {   // D_n = P_n / Q_n
         if (REAL) {
-            s_a[n - 1] = cplx{P.re, Q.re};
+            s_a[n - 1] = cplx{v.P.re, v.Q.re};
         } else {
-            s_a[n - 1] = P;
-            s_b[n - 1] = Q;
+            s_a[n - 1] = v.P;
+            s_b[n - 1] = v.Q;
         }
     };
     struct Eight {
@@ -324,8 +443,13 @@ __device__ __forceinline__ void mie_series_block(double x, double m_re, double m
     if (tid < 64) {
         const cplx mx = x * m;
         const cplx inv_mx = cplx{1.0, 0.0} / mx;
-        if (real) downward<true>(inv_mx, N, n_start, s_fac, s_a, s_b);
-        else downward<false>(inv_mx, N, n_start, s_fac, s_a, s_b);
+        if (n_start >= kScanFrom) {
+            if (real) downward_scan<true>(x, m, N, n_start, s_a, s_b);
+            else downward_scan<false>(x, m, N, n_start, s_a, s_b);
+        } else {
+            if (real) downward<true>(inv_mx, N, n_start, s_fac, s_a, s_b);
+            else downward<false>(inv_mx, N, n_start, s_fac, s_a, s_b);
+        }
     } else if (tid < 128) {
         upward(x, N, (double *)(s_fac + kAhead + kChunk), s_rec);
     }

@@ -43,3 +43,12 @@ def test_tables_match_the_oracle(cuda_device, x, m_re, n_angles, m_im):
     P = t.phase.cpu().numpy()
     assert np.abs(P - o.P).max() <= 1e2 * tol * o.P.max()
     assert np.abs(t.cdf.cpu().numpy() - o.F).max() <= 1e2 * tol
+
+
+@pytest.mark.parametrize("m_im", [0.0, 0.001, 0.02])
+@pytest.mark.parametrize("x, m_re", [(153.0, 1.59), (195.0, 1.59), (196.0, 1.59), (197.0, 1.59), (232.0, 1.59), (255.0, 1.35),
+                                     (268.0, 1.59), (520.0, 1.4), (700.0, 1.59), (850.0, 1.4), (20.0, 17.0), (20.1, 18.0)])
+def test_shared_downward_steps(cuda_device, x, m_re, m_im):
+    """From 256 downward steps all lanes of a wave share them: starts around that
+    and around multiples of 64, and |m| x above the number of terms."""
+    test_tables_match_the_oracle(cuda_device, x, m_re, 181, m_im)
