@@ -66,8 +66,10 @@ extern "C" {
                                  mc_workspace_bytes_log); exits that find their part of it full
                                  are added directly, so any size is correct, and so are
                                  all exits of at most 2^20 photons (over all media of a
-                                 batch) unless the caller sets grid_blocks.  Not with
-                                 MC_RECORD; batched launches size it with
+                                 batch) unless the caller sets grid_blocks.  (Without the
+                                 flag, launches whose mc_workspace_bytes have room for
+                                 enough of a log beside the image copies in use keep one
+                                 there.)  Not with MC_RECORD; batched launches size it with
                                  mc_workspace_bytes_batch_log. */
 
 /* Scalar tallies: mc_tally_t.scalars holds MC_N_SCALARS doubles. */

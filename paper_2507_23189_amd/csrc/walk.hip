@@ -45,7 +45,8 @@
 // per wave in LDS and handled 64 at a time by the whole wave, so the pixel
 // arithmetic runs with full lanes instead of on the few lanes that exit in
 // any one step.  A flush then either
-//   * appends them to the exit log (MC_EXIT_LOG): each block owns a region
+//   * appends them to the exit log (MC_EXIT_LOG, or room for it among the image
+//     copies): each block owns a region
 //     of every key range and appends at the position an LDS counter of the
 //     block hands out (one LDS add and one store per exit); a second kernel
 //     (log_bin) sums each range in an LDS histogram and writes the sums into
@@ -1848,6 +1849,29 @@ int launch_walk(WalkArgs &a, const mc_detector_t &det, const mc_run_t &rn, const
         use_log = false;
         launch_shape(false);
     }
+    // The log's place: words [log_at, log_end) of the workspace, what the caller
+    // gave beyond the scalar words, the copies and the schedule.
+    uint64_t log_at = ws_words + sched_words, log_end = t.workspace_bytes / 8;
+    // Without the flag, large images and batches leave most of their eight copies
+    // unused if the exits go through a log: where that room takes three exits of
+    // five or more, they do (us with atomics / so: 1e7 photons, tau = 1, 1024 x 1024
+    // 335 / 221, 850 x 850 386 / 225, tau = 4 408 / 340; 223 media of 191 x 294 and
+    // 5.8e7 photons with squares 5015 / 3080; room for two of three 6540 / 5560, for
+    // two of five 1470 / 1795).  Below 2^21 photons it is even, or loses up to 6 %
+    // (1.5e6, 725 x 725, tau = 0.5 124 / 129, tau = 1 117 / 111; 3e6 165 / 148).
+    if (!(det.flags & (MC_EXIT_LOG | MC_RECORD)) && rn.grid_blocks <= 0 &&
+        total_photons > std::max<uint64_t>(1u << 21, n_total)) {
+        const uint64_t at = kWsScalarWords * n_inst + copies_for(true) * n_total * ((det.flags & MC_SIGMA) ? 2 : 1);
+        launch_shape(true);
+        const uint64_t regions = ((uint64_t)1 << shape.rbits) * grid;
+        use_log = at < ws_words && 5 * regions * log_cap_for((ws_words - at) * 8, regions) >= 3 * total_photons;
+        if (use_log) {
+            log_at = at;
+            log_end = ws_words;
+        } else {
+            launch_shape(false);
+        }
+    }
     const uint64_t copies = copies_for(use_log);
     // With the exit log the walk's only image atomics are its fallback ones
     // (an exit whose region is full and whose pixel has no slot in the cache):
@@ -1890,8 +1914,7 @@ int launch_walk(WalkArgs &a, const mc_detector_t &det, const mc_run_t &rn, const
     const uint64_t clear2_words = clear2 ? n_total : 0;
     if (use_log) {
         const uint64_t regions = ((uint64_t)1 << shape.rbits) * grid;
-        const uint64_t log_at = ws_words + sched_words;
-        a.log_cap = t.workspace_bytes > log_at * 8 ? log_cap_for(t.workspace_bytes - log_at * 8, regions) : 0;
+        a.log_cap = log_end > log_at ? log_cap_for((log_end - log_at) * 8, regions) : 0;
         a.log_count = (uint32_t *)(ws + log_at);
         a.log = ws + log_at + (regions * 4 + 7) / 8;
         a.log_bits = shape.bits;

@@ -129,3 +129,52 @@ def test_copies_in_the_library_scratch(mc, table, cuda_device, pixels, sigma):
         big = mc.Tally.alloc(det, "cuda", sigma=sigma, fix64=True)
         with pytest.raises(mc.McError):
             mc.mc_simulate_noalloc(med, src, geo, det, run, big)
+
+
+@pytest.mark.parametrize("sigma", [False, True], ids=["", "sigma"])
+@pytest.mark.parametrize("n, shape, overflows", [
+    (1 << 21, (1000, 900, 1000, 900), None), ((1 << 21) + 1, (1000, 900, 1000, 900), None),
+    (3_000_000, (1024, 1024, 1024, 1024), None), (12_000_000, (1024, 1024, 1024, 1024), True),
+    (20_000_000, (1024, 1024, 1024, 1024), None), (5_000_000, (700, 701, 702, 703), None), (9_000_000, (1500, 1200, 64, 48), True),
+], ids=str)
+def test_a_log_beside_the_copies(mc, table, cuda_device, n, shape, overflows, sigma):
+    """Without the flag, a log in the room of unused image copies (not with a grid
+    of the caller's): around the counts where it starts and where it no longer
+    fits, with and without exits that find it full."""
+    import torch
+    w = W.TINY.replace(tau=1.0, n_photons=n, side_px=16, trans_px=16)
+    out = []
+    for blocks in (0, 512):
+        _, med, src, geo, det, run = mc.args_from_workload(w, table, flags=mc.MC_FIX64 | (mc.MC_SIGMA if sigma else 0))
+        det.side_nx, det.side_ny, det.trans_nx, det.trans_ny = shape
+        run.grid_blocks = blocks
+        t = mc.Tally.alloc(det, "cuda", sigma=sigma, fix64=True)
+        t.workspace.fill_(-1)
+        mc.mc_simulate(med, src, geo, det, run, t)
+        torch.cuda.synchronize()
+        out.append(t)
+    full = int(out[0].workspace[21].item())
+    if overflows and not sigma:      # (with squares there is twice the room)
+        assert full > 0
+    for k in ("side", "trans", "scalars") + (("side_w2", "trans_w2") if sigma else ()):
+        assert torch.equal(getattr(out[0], k), getattr(out[1], k)), k
+
+
+@pytest.mark.parametrize("sigma", [False, True], ids=["", "sigma"])
+@pytest.mark.parametrize("n_each", [60_000, 400_000])
+def test_a_log_beside_the_copies_of_a_batch(mc, table, cuda_device, n_each, sigma):
+    import torch
+    flags = mc.MC_FIX64 | (mc.MC_SIGMA if sigma else 0)
+    _, _, src, geo, det, run = mc.args_from_workload(W.TINY.replace(side_px=150, trans_px=130), table, flags=flags)
+    items = [mc.BatchItem(tau=0.1 * (i + 1), albedo=0.9999, inv_cdf=table.inv_cdf.data_ptr(), n_photons=n_each + 77 * i,
+                          instance=i) for i in range(40)]
+    out = []
+    for blocks in (0, 512):
+        run.grid_blocks = blocks
+        t = mc.Tally.alloc_batch(det, len(items), "cuda", sigma=sigma, fix64=True)
+        t.workspace.fill_(-1)
+        mc.mc_simulate_batch(items, W.TINY.n_cdf, src, geo, det, run, t)
+        torch.cuda.synchronize()
+        out.append(t)
+    for k in ("side", "trans", "scalars") + (("side_w2", "trans_w2") if sigma else ()):
+        assert torch.equal(getattr(out[0], k), getattr(out[1], k)), k
