@@ -1826,13 +1826,29 @@ int launch_walk(WalkArgs &a, const mc_detector_t &det, const mc_run_t &rn, const
     const uint64_t lanes_one = (uint64_t)cus * block;
     const bool few = !batch && total_photons <= lanes_one * (tau_z > 6.0 ? 5 : (tau_z > 3.0 ? 4 : 3)) &&
                      !(tau_z > 12.0 && total_photons < lanes_one / 2);
+    // Slots of the tally cache at most (log2), where the LDS holds them.  At the end
+    // every block adds its slots to the images, many of them to the same words, so
+    // few photons, or few pixels, pay for more slots than they use (us at 8, 10 and
+    // 12, HG: 1e6 photons, tau = 4, 512 x 512 84.7 / 87.0 / 101.3, tau = 1 70.0 / 80.5 /
+    // 83.5; 1e7, tau = 1, 64 x 64 201 / 181 / 209, 256 x 256 285 / 277 / 250; 1e8, 256 x
+    // 256 2406 / 2038 / 1590, 512 x 512 2429 / 2264 / 2057).  Squared weights double
+    // what a slot saves.  Batches (whose first media fill the slots) and the exit
+    // log's overflow do not tell 10 from 12.
+    auto slots_for = [&](bool log) -> int {
+        if (log || batch) return 10;
+        if (total_photons <= 1u << 20) return (det.flags & MC_SIGMA) ? 10 : 8;
+        if (total_photons < 1u << 23) return 10;
+        if (total_photons < 1u << 24) return n_total > 1u << 16 ? 11 : 10;
+        const uint64_t few_pixels = total_photons < 1u << 26 ? 1u << 18 : 1u << 16;
+        return n_total <= 1u << 14 ? 10 : (n_total <= few_pixels ? 11 : 12);
+    };
     size_t lds = 0;
     int grid = 0;
     auto launch_shape = [&](bool log) {
         const size_t lds_fixed = table_bytes + scal_bytes + (size_t)(block / 64) * queue_arrays * kQueue * sizeof(float) +
                                  (log ? ((size_t)4 << shape.rbits) : 0);
         a.cache_bits = 0;
-        for (int b = 10; b >= 4; --b)
+        for (int b = slots_for(log); b >= 4; --b)
             if (lds_fixed + (slot_bytes << b) <= lds_half_cu) { a.cache_bits = b; break; }
         lds = lds_fixed + (a.cache_bits ? (slot_bytes << a.cache_bits) : 0);
         const int blocks_per_cu = std::max(1, std::min((int)(160 * 1024 / lds), 32 / (block / 64)));
