@@ -1822,9 +1822,9 @@ int launch_walk(WalkArgs &a, const mc_detector_t &det, const mc_run_t &rn, const
     // long walks over more waves.  Times in us of two blocks and of one: 1e5
     // tau = 4 57.6 / 53.4, 3e5 tau = 2 63.2 / 58.2, 7e5 tau = 0.25 109.7 / 104.9, tau = 16
     // 209 / 167; 1e6 tau = 1 73.9 / 76.0, tau = 4 88.7 / 83.9, tau = 16 219 / 194; 2e6
-    // tau = 4 117.5 / 118.5; 1e4 tau = 16 94.7 / 97.9.
+    // tau = 4 117.5 / 118.5; 1e4 tau = 16 94.7 / 97.9.  (All with the library's block.)
     const uint64_t lanes_one = (uint64_t)cus * block;
-    const bool few = !batch && total_photons <= lanes_one * (tau_z > 6.0 ? 5 : (tau_z > 3.0 ? 4 : 3)) &&
+    const bool few = !batch && rn.block_size == 0 && total_photons <= lanes_one * (tau_z > 6.0 ? 5 : (tau_z > 3.0 ? 4 : 3)) &&
                      !(tau_z > 12.0 && total_photons < lanes_one / 2);
     // Slots of the tally cache at most (log2), where the LDS holds them.  At the end
     // every block adds its slots to the images, many of them to the same words, so
@@ -1833,9 +1833,10 @@ int launch_walk(WalkArgs &a, const mc_detector_t &det, const mc_run_t &rn, const
     // 83.5; 1e7, tau = 1, 64 x 64 201 / 181 / 209, 256 x 256 285 / 277 / 250; 1e8, 256 x
     // 256 2406 / 2038 / 1590, 512 x 512 2429 / 2264 / 2057).  Squared weights double
     // what a slot saves.  Batches (whose first media fill the slots) and the exit
-    // log's overflow do not tell 10 from 12.
+    // log's overflow do not tell 10 from 12, and smaller blocks would fit a CU in
+    // smaller numbers.
     auto slots_for = [&](bool log) -> int {
-        if (log || batch) return 10;
+        if (log || batch || rn.block_size != 0) return 10;
         if (total_photons <= 1u << 20) return (det.flags & MC_SIGMA) ? 10 : 8;
         if (total_photons < 1u << 23) return 10;
         if (total_photons < 1u << 24) return n_total > 1u << 16 ? 11 : 10;
@@ -1847,9 +1848,13 @@ int launch_walk(WalkArgs &a, const mc_detector_t &det, const mc_run_t &rn, const
     auto launch_shape = [&](bool log) {
         const size_t lds_fixed = table_bytes + scal_bytes + (size_t)(block / 64) * queue_arrays * kQueue * sizeof(float) +
                                  (log ? ((size_t)4 << shape.rbits) : 0);
+        // (Under the log the cache, for its overflow alone, takes only LDS that no
+        // further block could use.)
+        const size_t fit = std::max<size_t>(1, std::min<size_t>(160 * 1024 / lds_fixed, 32 / (block / 64)));
+        const size_t lds_most = log ? std::min(lds_half_cu, 160 * 1024 / fit) : lds_half_cu;
         a.cache_bits = 0;
         for (int b = slots_for(log); b >= 4; --b)
-            if (lds_fixed + (slot_bytes << b) <= lds_half_cu) { a.cache_bits = b; break; }
+            if (lds_fixed + (slot_bytes << b) <= lds_most) { a.cache_bits = b; break; }
         lds = lds_fixed + (a.cache_bits ? (slot_bytes << a.cache_bits) : 0);
         const int blocks_per_cu = std::max(1, std::min((int)(160 * 1024 / lds), 32 / (block / 64)));
         grid = rn.grid_blocks > 0 ? rn.grid_blocks : cus * (few ? 1 : blocks_per_cu);
