@@ -146,8 +146,8 @@ PEAK_SLOTS_PER_S = 256 * 4 * 32 * 2.4e9
 # WRITE_SIZE x 1.0); valid only for the tally path and kernel code it was
 # measured on (profiles/walk_tau4_counters.md): the digest covers the walk
 # sources without comments and whitespace, so a comment edit keeps it.
-TRAFFIC = {"tally": "log", "sources_sha256": "efa00119fe49dbc637aa7855bc75d5b865a2f1592615db94498b49766f5e5bac",
-           "fetch_kib": 385.6, "write_kib": 554665.0, "fetch_factor": 2.0, "write_factor": 1.0}
+TRAFFIC = {"tally": "log", "sources_sha256": "ea219363d6c2de453503e7c99e428da869ff973c2837ccc36d3d07701f50ef49",
+           "fetch_kib": 386.2, "write_kib": 554672.7, "fetch_factor": 2.0, "write_factor": 1.0}
 WALK_SOURCES = ("paper_2507_23189_amd/csrc/walk.hip", "paper_2507_23189_amd/csrc/philox.hpp")
 
 
