@@ -245,10 +245,13 @@ __global__ __launch_bounds__(kThreads) void metrics_sums(MetricsArgs m)
         for (int j = 0; j < kPix; ++j) m.blk_sum[kPix * blockIdx.x + j] = acc[j];
     for (int i = tid; i < 4 * m.n_r; i += kThreads)
         if (s_rad[i]) atomicAdd(&m.rad[i], s_rad[i]);
-    // The block that finishes last sees every block's sums: each block makes
-    // its own visible to the device before it counts itself as done (one lane's
-    // fence, after the barrier, covers the block's writes; a fence by each wave
-    // wrote the L2 back once per wave).
+    // The block that finishes last sees every block's sums: each wave waits for its
+    // own annulus adds (a barrier does not: on this GPU it orders LDS only, and the
+    // adds, whose results nobody reads, would still be under way), then one lane
+    // makes the block's pixel sums visible to the device and counts the block as
+    // done.  The adds are device-scope and need no write-back of the L2 (a fence by
+    // each wave wrote it back once per wave).
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (tid == 0) {
         __threadfence();
