@@ -66,19 +66,26 @@ HostResult::HostResult() : slot_(-1)
 
 HostResult::~HostResult()
 {
-    if (slot_ >= 0) g_free.fetch_or(1ull << slot_, std::memory_order_release);
+    if (slot_ >= 0 && !lent_) g_free.fetch_or(1ull << slot_, std::memory_order_release);
 }
 
-double *HostResult::data() const { return g_pinned + slot_ * kHostResult; }
+double *HostResult::data()
+{
+    lent_ = true;
+    return g_pinned + slot_ * kHostResult;
+}
 
-hipError_t wait_result(double *out, int n, const double *result, const HostResult &host, hipStream_t st)
+hipError_t wait_result(double *out, int n, const double *result, HostResult &host, hipStream_t st)
 {
     if (!host) {
         const hipError_t e = hipMemcpyAsync(out, result, n * sizeof(double), hipMemcpyDeviceToHost, st);
         if (e != hipSuccess) return e;
     }
     const hipError_t e = hipStreamSynchronize(st);
-    if (e == hipSuccess && host) std::memcpy(out, host.data(), n * sizeof(double));
+    if (e == hipSuccess && host) {
+        std::memcpy(out, host.data(), n * sizeof(double));
+        host.settle();
+    }
     return e;
 }
 

@@ -30,7 +30,10 @@ void clear_error();
 // its results needs no copy (a copy kernel and its gap, 8 to 10 of the 48 us of a
 // small table build).  The library holds 64 of them until the process ends, each
 // used by one call at a time; false when none is free or the memory cannot be
-// had, and the call copies.
+// had, and the call copies.  A slot whose address a call has handed to a kernel is
+// free again only when wait_result has waited for the stream: where that fails (while
+// another stream captures in global mode, say) the kernel may still be about to write
+// to it, and the slot stays taken.
 constexpr int kHostResult = 16;
 class HostResult {
 public:
@@ -39,14 +42,17 @@ public:
     HostResult(const HostResult &) = delete;
     HostResult &operator=(const HostResult &) = delete;
     explicit operator bool() const { return slot_ >= 0; }
-    double *data() const;
+    double *data();   // for a kernel to write to
+    // The stream has been waited for: no kernel writes to the slot any more.
+    void settle() { lent_ = false; }
 
 private:
     int slot_;
+    bool lent_ = false;
 };
 // Wait for the stream and fetch n results written to `result` (host's, or
 // device memory).
-hipError_t wait_result(double *out, int n, const double *result, const HostResult &host, hipStream_t st);
+hipError_t wait_result(double *out, int n, const double *result, HostResult &host, hipStream_t st);
 
 // Compute units of the current device (cached per device).
 int device_cu_count(int *out);

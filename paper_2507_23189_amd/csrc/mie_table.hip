@@ -1246,7 +1246,7 @@ extern "C" int mie_table_build_poly(const mie_spec_t *spec, const mie_poly_t *po
     a.phase = table->phase;
     std::unique_lock<std::mutex> lock(g_scratch_mu, std::defer_lock);
     if (int rc = scratch_buffers(table, lock, &a.result, nullptr, who)) return rc;
-    const HostResult host;
+    HostResult host;
     a.host_result = host ? host.data() : nullptr;
     hipStream_t st = (hipStream_t)stream;
     const int slices = (s.n_angles + kPhaseThreads - 1) / kPhaseThreads;
@@ -1276,7 +1276,7 @@ extern "C" int mie_table_build(const mie_spec_t *spec, mie_table_t *table, void 
     double *result = nullptr, *work = nullptr;
     std::unique_lock<std::mutex> lock(g_scratch_mu, std::defer_lock);
     if (int rc = scratch_buffers(table, lock, &result, &work, "mie_table_build")) return rc;
-    const HostResult host;
+    HostResult host;
     if (int rc = launch_table(args, table, st, result, work, host ? host.data() : nullptr)) return rc;
     double res[4];
     MC_HIP_CHECK(wait_result(res, 4, result, host, st));

@@ -2429,7 +2429,7 @@ extern "C" int mc_grad(const mc_medium_t *medium, const mc_geometry_t *geometry,
                     (unsigned long long)((kWsScalarWords + 4) * 8));
     const double mu_s = coef.mu_sca;
     hipStream_t st = (hipStream_t)stream;
-    const HostResult host;
+    HostResult host;
     double *dots = host ? host.data() : (double *)t.workspace + 24;    // scalar words 24..27
     const uint64_t n = (uint64_t)det.side_nx * det.side_ny;
     // The blocks' partials go after the scalar words, where mc_simulate keeps
