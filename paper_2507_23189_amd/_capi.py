@@ -542,6 +542,8 @@ def mc_side_l2(detector: Detector, tally: Tally, target, stream=None):
     import torch
     n = detector.side_ny * detector.side_nx
     target = _require(target, "target", torch.float64, numel=n)
+    if target.is_neg():
+        raise ValueError("target must not be a negated view (resolve_neg())")
     tally.validate(detector, target=target)
     g = torch.empty_like(tally.side)
     loss = torch.empty((), dtype=torch.float64, device=g.device)

@@ -55,6 +55,16 @@ class SideImage:
         return med, tally
 
 
+def _reads_as(target, image) -> bool:
+    """The target's memory holds its values as the image's does: neither a
+    negated view, whose memory holds the opposite values, nor a zero tensor
+    without memory."""
+    import torch
+    return (type(target) is torch.Tensor and target.dtype == torch.float64 and target.shape == image.shape
+            and target.device == image.device and target.layout == torch.strided and target.is_contiguous()
+            and not target.is_neg() and target.data_ptr() != 0)
+
+
 _fns = {}
 
 
@@ -88,8 +98,7 @@ def _functions():
             med, tally = sim.run_walk(float(mu_sca), float(mu_abs))
             # The library's pass reads a target laid out as the image; another
             # (broadcast, strided, float32) goes through tensor operations.
-            if (type(target) is torch.Tensor and target.dtype == torch.float64 and target.shape == tally.side.shape
-                    and target.is_contiguous() and target.device == tally.side.device):
+            if _reads_as(target, tally.side):
                 loss, ctx.g = mc_side_l2(sim.detector, tally, target)
             else:
                 diff = tally.side - target
