@@ -1,0 +1,70 @@
+"""The walk's launch plan (CPU): launch shape, tally path and workspace for any
+size, without a launch."""
+import ctypes as C
+import os
+import subprocess
+
+import pytest
+
+from paper_2507_23189_amd import _capi as K
+from paper_2507_23189_amd import build as B
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CU_LDS = 160 * 1024
+
+
+class Request(C.Structure):
+    _fields_ = [("batch", C.c_bool), ("phase", C.c_int), ("n_cdf", C.c_int), ("n_inst", C.c_uint32), ("n_pix", C.c_uint64),
+                ("flags", C.c_uint32), ("photons", C.c_uint64), ("block_size", C.c_int), ("grid_blocks", C.c_int),
+                ("chunk", C.c_uint32), ("tau_z", C.c_double), ("cus", C.c_int), ("max_copies", C.c_uint64),
+                ("ws_bytes", C.c_uint64)]
+
+
+class Plan(C.Structure):
+    _fields_ = [("use_log", C.c_bool), ("block", C.c_int), ("grid", C.c_int), ("cache_bits", C.c_int), ("lds", C.c_size_t),
+                ("bits", C.c_uint32), ("rbits", C.c_uint32), ("parts", C.c_uint32), ("copies", C.c_uint64),
+                ("n_cleared", C.c_uint64), ("permuted", C.c_bool), ("ws_words", C.c_uint64), ("log_at", C.c_uint64),
+                ("log_cap", C.c_uint32), ("chunk", C.c_uint64), ("refill_min", C.c_uint32)]
+
+    @property
+    def path(self):
+        """What decides which kernels run on which memory, launch shape apart."""
+        return (self.use_log, self.copies, self.n_cleared, self.permuted, self.cache_bits, self.log_at)
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("plan") / "plan.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", f"-I{B.INCLUDE}", f"-I{B.CSRC}",
+                    os.path.join(HERE, "walk_plan_driver.cpp"), "-o", so], check=True)
+    lib = C.CDLL(so)
+    lib.words.restype = C.c_uint64
+    lib.words.argtypes = [C.POINTER(K.Detector), C.c_uint64]
+    assert lib.walk_plan_sizes(0) == C.sizeof(Request) and lib.walk_plan_sizes(1) == C.sizeof(Plan)
+    return lib
+
+
+def plan(lib, photons, shape=(512, 512, 512, 512), *, media=0, flags=0, n_cdf=16384, tau=4.0, log_photons=None, **kw):
+    """The plan of a walk (or, with media, of a batch) in a workspace of the size
+    the library asks for."""
+    det = K.Detector(*shape, flags)
+    n = max(media, 1)
+    if flags & K.MC_EXIT_LOG:
+        size = photons if log_photons is None else log_photons
+        ws = K.mc_workspace_bytes_batch_log(det, media, size) if media else K.mc_workspace_bytes_log(det, size)
+    else:
+        ws = K.mc_workspace_bytes_batch(det, media) if media else K.mc_workspace_bytes(det)
+    q = dict(batch=bool(media), phase=K.MC_PHASE_MIE, n_cdf=n_cdf, n_inst=n, n_pix=shape[0] * shape[1] + shape[2] * shape[3],
+             flags=flags, photons=photons, tau_z=-1.0 if media else tau, cus=256, max_copies=8, ws_bytes=ws)
+    q.update(kw)
+    p = Plan()
+    lib.walk_plan(C.byref(Request(**q)), C.byref(p))
+    return p
+
+
+def test_the_headline_plan(lib):
+    p = plan(lib, 100_000_000, flags=K.MC_EXIT_LOG)
+    assert p.use_log and (p.block, p.grid) == (1024, 512) and p.lds <= CU_LDS // 2
+    # Every region holds half as many exits again as an even share of the photons.
+    assert p.log_cap * (1 << p.rbits) * p.grid >= 150_000_000
+    assert not plan(lib, 100_000_000).use_log and plan(lib, 100_000_000).copies == 8
