@@ -17,6 +17,12 @@ constexpr uint64_t kFewPhotons = 1 << 20;  // launches up to here take no exit l
 constexpr uint64_t kLogBinBlocks = 512;    // log_bin blocks that fill the chip (two per CU)
 constexpr int kQueue = 64;                 // queued image exits per wave
 constexpr int kBatchScal = 16;             // LDS scalar words per medium in a batched launch
+// LDS scalar words (of the first medium) that tally nothing, the totals of the
+// imaged faces being taken from their images, and hold what the block keeps beside
+// its tallies: its pool of photon ids and the exits that found the log full.  (Words
+// of their own would cost the largest batch, whose scalars and queues fill half a
+// CU's LDS to the byte, the second block of every CU.)
+constexpr int kLdsPool = MC_S_FACE + 1, kLdsFull = MC_S_FACE + 5;
 constexpr uint64_t kWsScalarWords = 32;    // workspace scalar words per medium
 constexpr uint32_t kLogMinRangeBits = 6;
 constexpr uint32_t kLogHistBits = 13;      // keys per binning block: 2^13 (64 KB of int64 sums)
@@ -237,7 +243,7 @@ inline WalkPlan plan_walk(const WalkRequest &q)
     // two per CU.
     const int block = p.block = q.block_size ? q.block_size : ((q.flags & MC_MOMENTS) ? 768 : 1024);
     const size_t table_bytes = batch ? 0 : (size_t)((q.n_cdf + 3) & ~3) * sizeof(float);
-    const size_t scal_bytes = ((batch ? (size_t)q.n_inst * kBatchScal : MC_N_SCALARS) + 2) * sizeof(double);
+    const size_t scal_bytes = (batch ? (size_t)q.n_inst * kBatchScal : MC_N_SCALARS) * sizeof(double);
     const size_t queue_arrays = batch ? 4 : 3;
     const size_t slot_bytes = sizeof(uint32_t) + sizeof(double) * ((q.flags & MC_SIGMA) ? 2 : 1);
     const size_t lds_half_cu = 80 * 1024;

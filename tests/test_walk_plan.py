@@ -68,3 +68,16 @@ def test_the_headline_plan(lib):
     # Every region holds half as many exits again as an even share of the photons.
     assert p.log_cap * (1 << p.rbits) * p.grid >= 150_000_000
     assert not plan(lib, 100_000_000).use_log and plan(lib, 100_000_000).copies == 8
+
+
+@pytest.mark.parametrize("px", [16, 64, 100, 150], ids=str)
+@pytest.mark.parametrize("log", [False, True], ids=["", "log"])
+def test_every_batch_has_the_blocks_its_tallies_leave_room_for(lib, px, log):
+    """A batch's block needs 16 scalar words a medium, 16 queues of 1 KB and, with the
+    log, its append counters: two fill a CU up to half its LDS, to the byte (512
+    media, or 384, 448 and 480 with 2^12, 2^11 and 2^10 counters)."""
+    for media in range(1, 513):
+        p = plan(lib, 10_000_000, (px,) * 4, media=media, flags=K.MC_EXIT_LOG if log else 0, n_cdf=0, grid_blocks=0)
+        need = 128 * media + 16 * 1024 + ((4 << p.rbits) if p.use_log else 0)
+        assert p.grid == 256 * (2 if need <= CU_LDS // 2 else 1), (media, p.lds)
+        assert p.lds >= need
