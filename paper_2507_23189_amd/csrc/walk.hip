@@ -686,10 +686,12 @@ void walk_kernel(WalkArgs a)
     // Either way it runs when at most round_at lanes walk.
     uint32_t round_at = 64u;
 
-    // The loop begins 16 bytes past a multiple of 32, whatever comes before it:
-    // instructions are fetched in aligned lines, and left to the length of the code
-    // above, 1e5 photons took 41.8 or 43.0 us (at a multiple of 32: 42.8).
-    asm volatile(".p2align 5\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0");
+    // The loop begins 20 bytes past a multiple of 32, whatever comes before it:
+    // instructions are fetched in aligned lines, and where the loop lies in them moves
+    // times by 2 % and the end of some launches by 5 % (0 / 8 / 16 / 20 / 28 bytes past: 1e5
+    // photons 42.8 / 42.3 / 42.0 / 41.9 / 42.6 us, 2e7 at tau = 16 1.484 / 1.484 / 1.568 / 1.49 /
+    // 1.57 ms, 1e8 at tau = 1 1.187 / 1.198 / 1.188 / 1.186 / 1.190).
+    asm volatile(".p2align 5\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0");
     for (;;) {
         if ((uint32_t)__popcll(alive) <= round_at) {
             const ArgsPtr ra = reload_args();
