@@ -169,6 +169,16 @@ inline Claims claims_for(uint64_t units, uint64_t grid, uint64_t block, uint64_t
 }
 
 
+// A CU's LDS is handed out in granules (measured: 9 blocks of 17,908 bytes run at
+// once but only 8 of 18,036, 5 of 31,960 but 4 of 32,088, 3 of 53,677 but 2 of 53,805).
+constexpr size_t kCuLds = 160 * 1024, kLdsGranule = 1280;
+// Blocks of `block` lanes and `lds` bytes that run on a CU at once.
+inline size_t blocks_on_cu(size_t lds, int block)
+{
+    const size_t granules = (lds + kLdsGranule - 1) / kLdsGranule;
+    return std::max<size_t>(1, std::min<size_t>(kCuLds / kLdsGranule / granules, 32 / (block / 64)));
+}
+
 // What a walk's plan depends on.
 struct WalkRequest {
     bool batch;
@@ -281,14 +291,16 @@ inline WalkPlan plan_walk(const WalkRequest &q)
         const size_t lds_fixed = table_bytes + scal_bytes + (size_t)(block / 64) * queue_arrays * kQueue * sizeof(float) +
                                  (log ? ((size_t)4 << shape.rbits) : 0);
         // (Under the log the cache, for its overflow alone, takes only LDS that no
-        // further block could use.)
-        const size_t fit = std::max<size_t>(1, std::min<size_t>(160 * 1024 / lds_fixed, 32 / (block / 64)));
-        const size_t lds_most = log ? std::min(lds_half_cu, 160 * 1024 / fit) : lds_half_cu;
+        // further block could use: blocks of 64 lanes with a 4096-entry table, 5e7
+        // photons, tau = 1, 1.41 ms with 32 slots and 8 blocks a CU, 1.15 with 16 and 9.)
+        const size_t fit = std::max<size_t>(1, std::min<size_t>(kCuLds / lds_fixed, 32 / (block / 64)));
+        const size_t granules = kCuLds / kLdsGranule / blocks_on_cu(lds_fixed, block);
+        const size_t lds_most = log ? std::min({lds_half_cu, kCuLds / fit, granules * kLdsGranule}) : lds_half_cu;
         p.cache_bits = 0;
         for (int b = slots_for(log); b >= 4; --b)
             if (lds_fixed + (slot_bytes << b) <= lds_most) { p.cache_bits = b; break; }
         p.lds = lds_fixed + (p.cache_bits ? (slot_bytes << p.cache_bits) : 0);
-        const int blocks_per_cu = std::max(1, std::min((int)(160 * 1024 / p.lds), 32 / (block / 64)));
+        const int blocks_per_cu = std::max(1, std::min((int)(kCuLds / p.lds), 32 / (block / 64)));
         p.grid = q.grid_blocks > 0 ? q.grid_blocks : q.cus * (few ? 1 : blocks_per_cu);
     };
     const uint64_t ws_words = p.ws_words = kWsScalarWords * q.n_inst + q.max_copies * copy_words;

@@ -10,7 +10,7 @@ from paper_2507_23189_amd import _capi as K
 from paper_2507_23189_amd import build as B
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-CU_LDS = 160 * 1024
+CU_LDS, GRANULE = 160 * 1024, 1280     # LDS is handed out in granules
 
 
 class Request(C.Structure):
@@ -81,3 +81,21 @@ def test_every_batch_has_the_blocks_its_tallies_leave_room_for(lib, px, log):
         need = 128 * media + 16 * 1024 + ((4 << p.rbits) if p.use_log else 0)
         assert p.grid == 256 * (2 if need <= CU_LDS // 2 else 1), (media, p.lds)
         assert p.lds >= need
+
+
+@pytest.mark.parametrize("sigma", [False, True], ids=["", "sigma"])
+def test_the_cache_under_the_log_costs_no_block(lib, sigma):
+    """It takes only LDS that no further block could have, in whole granules."""
+    flags = K.MC_EXIT_LOG | (K.MC_SIGMA if sigma else 0)
+    cached = 0
+    for block in range(64, 1025, 64):
+        for n_cdf in (0, 2, 1000, 1024, 2048, 4096, 5000, 8192, 12345, 16384):
+            p = plan(lib, 100_000_000, flags=flags, n_cdf=n_cdf, block_size=block)
+            waves = block // 64
+            fixed = 4 * ((n_cdf + 3) & ~3) + 160 + 768 * waves + (4 << p.rbits)
+            assert p.use_log and p.lds == fixed + ((20 if sigma else 12) << p.cache_bits if p.cache_bits else 0)
+            fits = lambda lds: max(1, min(CU_LDS // GRANULE // -(-lds // GRANULE), 32 // waves))
+            assert fits(p.lds) == fits(fixed), (block, n_cdf, p.lds)
+            assert p.grid == 256 * max(1, min(CU_LDS // fixed, 32 // waves))
+            cached += p.cache_bits > 0
+    assert cached > 50
