@@ -324,13 +324,19 @@ inline WalkPlan plan_walk(const WalkRequest &q)
     // 335 / 221, 850 x 850 386 / 225, tau = 4 408 / 340; 223 media of 191 x 294 and
     // 5.8e7 photons with squares 5015 / 3080; room for two of three 6540 / 5560, for
     // two of five 1470 / 1795).  Below 2^21 photons it is even, or loses up to 6 %
-    // (1.5e6, 725 x 725, tau = 0.5 124 / 129, tau = 1 117 / 111; 3e6 165 / 148).
+    // (1.5e6, 725 x 725, tau = 0.5 124 / 129, tau = 1 117 / 111; 3e6 165 / 148).  Where the
+    // log's counters cost the second block of every CU (batches from 385 media) it takes
+    // room for nine of ten, unless squares double the atomics (450 to 511 media, so /
+    // with atomics: room for 0.66 0.96 to 1.58, for 0.75 0.93 to 1.11, for 0.98 0.91 to 0.96, for 1.12
+    // 0.88 to 0.95, for 1.4 0.89 to 0.92; squares, 0.7 0.86 to 1.0, 0.8 0.76 to 0.86, 1.0 0.63).
     if (!(q.flags & (MC_EXIT_LOG | MC_RECORD)) && q.grid_blocks <= 0 &&
         total_photons > std::max<uint64_t>(1u << 21, n_total)) {
         const uint64_t at = kWsScalarWords * q.n_inst + copies_for(true) * copy_words;
+        const int grid = p.grid;
         launch_shape(true);
         const uint64_t regions = ((uint64_t)1 << shape.rbits) * p.grid;
-        use_log = at < ws_words && 5 * regions * log_cap_for((ws_words - at) * 8, regions) >= 3 * total_photons;
+        const uint64_t tenths = p.grid < grid && !(q.flags & MC_SIGMA) ? 9 : 6;
+        use_log = at < ws_words && 10 * regions * log_cap_for((ws_words - at) * 8, regions) >= tenths * total_photons;
         if (use_log) {
             p.log_at = at;
             log_end = ws_words;

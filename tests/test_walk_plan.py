@@ -99,3 +99,33 @@ def test_the_cache_under_the_log_costs_no_block(lib, sigma):
             assert p.grid == 256 * max(1, min(CU_LDS // fixed, 32 // waves))
             cached += p.cache_bits > 0
     assert cached > 50
+
+
+def _room(p, photons):
+    """Entries of the log for each photon."""
+    return (p.log_cap << p.rbits) * p.grid / photons
+
+
+@pytest.mark.parametrize("sigma", [False, True], ids=["", "sigma"])
+def test_a_log_beside_the_copies_where_it_pays(lib, sigma):
+    """Without the flag: with room for three exits of five; where the log's counters
+    cost the second block of every CU, and no squares are tallied, for nine of ten."""
+    flags = K.MC_SIGMA if sigma else 0
+    seen = set()
+    for media in (64, 256, 384, 385, 450, 480, 481, 511, 512):
+        for px in (40, 64, 91, 100, 113, 128, 150, 207, 256):
+            for each in (20_000, 60_000, 200_000, 400_000):
+                n = media * each
+                p = plan(lib, n, (px,) * 4, media=media, flags=flags, n_cdf=0)
+                two = 128 * media + 16 * 1024 <= CU_LDS // 2
+                log_two = 128 * media + 16 * 1024 + (4 << p.rbits) <= CU_LDS // 2
+                least = 0.9 if two and not log_two and not sigma else 0.6
+                if p.use_log:
+                    assert n > max(1 << 21, p.ws_words // 8 // (2 if sigma else 1) - 32 * media)
+                    assert _room(p, n) >= least, (media, px, each)
+                    assert p.grid == 256 * (2 if log_two else 1)
+                    assert p.log_at + ((p.grid << p.rbits) + 1) // 2 + (p.log_cap << p.rbits) * p.grid <= p.ws_words
+                else:
+                    assert p.grid == 256 * (2 if two else 1)
+                seen.add((p.use_log, least))
+    assert seen == {(True, 0.6), (False, 0.6)} | (set() if sigma else {(True, 0.9), (False, 0.9)})
