@@ -432,7 +432,8 @@ uint64_t mc_workspace_bytes_batch_log(const mc_detector_t *detector, uint32_t n_
 /*
  * Launch-shape autotuner for mc_simulate_batch.  Runs the batch with every
  * item's photon count scaled by sample_fraction (in (0, 1], at least one
- * photon for a nonzero count) once for each candidate block size
+ * photon for a nonzero count), on the tally path that the unscaled batch takes
+ * (see MC_EXIT_LOG), once for each candidate block size
  * {256, 512, 1024} and chunk {256, 512, 1024, 2048, 4096} (block-major order),
  * timing each candidate's second launch with HIP events on `stream`, and
  * writes the fastest pair to *block_size and *chunk and its time to *best_ms.

@@ -187,6 +187,9 @@ struct WalkRequest {
     uint64_t n_pix;               // pixels of one medium's images
     uint32_t flags;               // of the detector
     uint64_t photons;             // over all media
+    // Photons of the launch whose tally path is taken (log or not, copies, their
+    // order, slots): more than `photons` when a sample of a launch is timed for it.
+    uint64_t path_photons;
     int block_size, grid_blocks;  // the caller's, 0: the library's choice
     uint32_t chunk;
     double tau_z;                 // optical depth along the beam axis (negative: a batch)
@@ -213,7 +216,7 @@ inline WalkPlan plan_walk(const WalkRequest &q)
 {
     WalkPlan p{};
     const bool batch = q.batch;
-    const uint64_t total_photons = q.photons, n_total = q.n_pix * q.n_inst, copy_words = n_total * ((q.flags & MC_SIGMA) ? 2 : 1);
+    const uint64_t total_photons = q.path_photons, n_total = q.n_pix * q.n_inst, copy_words = n_total * ((q.flags & MC_SIGMA) ? 2 : 1);
     // A batched launch keeps its schedule after the workspace words; the exit
     // log follows: its counts, then the regions.  A workspace without room for
     // the counts takes the atomic path (the same sums).
@@ -268,8 +271,8 @@ inline WalkPlan plan_walk(const WalkRequest &q)
     // 209 / 167; 1e6 tau = 1 73.9 / 76.0, tau = 4 88.7 / 83.9, tau = 16 219 / 194; 2e6
     // tau = 4 117.5 / 118.5; 1e4 tau = 16 94.7 / 97.9.  (All with the library's block.)
     const uint64_t lanes_one = (uint64_t)q.cus * block;
-    const bool few = !batch && q.block_size == 0 && total_photons <= lanes_one * (tau_z > 6.0 ? 5 : (tau_z > 3.0 ? 4 : 3)) &&
-                     !(tau_z > 12.0 && total_photons < lanes_one / 2);
+    const bool few = !batch && q.block_size == 0 && q.photons <= lanes_one * (tau_z > 6.0 ? 5 : (tau_z > 3.0 ? 4 : 3)) &&
+                     !(tau_z > 12.0 && q.photons < lanes_one / 2);
     // Slots of the tally cache at most (log2), where the LDS holds them.  At the end
     // every block adds its slots to the images, many of them to the same words, so
     // few photons, or few pixels, pay for more slots than they use (us at 8, 10 and
@@ -363,9 +366,9 @@ inline WalkPlan plan_walk(const WalkRequest &q)
     p.permuted = !use_log && total_photons > std::max<uint64_t>(1u << 22, 8 * n_total);
     const uint64_t waves_total = (uint64_t)p.grid * (block / 64);
     p.chunk = q.chunk;
-    if (p.chunk == 0) p.chunk = chunk_for(total_photons, waves_total, batch);
+    if (p.chunk == 0) p.chunk = chunk_for(q.photons, waves_total, batch);
     // Work units are counted in 31 bits.
-    if (batch) p.chunk = std::max<uint64_t>(p.chunk, total_photons >> 29);
+    if (batch) p.chunk = std::max<uint64_t>(p.chunk, q.photons >> 29);
     // Refill threshold from the optical depth; batched launches take the
     // fixed one (256 media, ms at 12 / 20 / 24 / 28 / 32 / 40: 20.5 / 19.3 /
     // 19.05 / 18.97 / 19.01 / 19.5).

@@ -1617,9 +1617,10 @@ __global__ void set_schedule(BatchInst *dst, InstChunk c)
 }
 
 // Enqueue init, walk and finalize for n_inst media (a single medium, or a
-// batch whose schedule `sched` is given) on `st`.
+// batch whose schedule `sched` is given) on `st`; path_photons: WalkRequest.
 int launch_walk(WalkArgs &a, const mc_detector_t &det, const mc_run_t &rn, const mc_tally_t &t, int phase,
-                uint32_t n_inst, uint64_t total_photons, const std::vector<BatchInst> *sched, hipStream_t st)
+                uint32_t n_inst, uint64_t total_photons, uint64_t path_photons, const std::vector<BatchInst> *sched,
+                hipStream_t st)
 {
     const bool batch = sched != nullptr;
     int cus = 0;
@@ -1631,8 +1632,8 @@ int launch_walk(WalkArgs &a, const mc_detector_t &det, const mc_run_t &rn, const
     const double tau_z = !batch && a.neg_ln2_over_mu < 0.f && std::isfinite(a.neg_ln2_over_mu)
                              ? -M_LN2 / (double)a.neg_ln2_over_mu * a.size[2]
                              : -1.0;
-    const WalkPlan p = plan_walk({batch, phase, a.n_cdf, n_inst, n_pix, det.flags, total_photons, rn.block_size,
-                                  rn.grid_blocks, rn.chunk, tau_z, cus, (uint64_t)a.copy_mask + 1, t.workspace_bytes});
+    const WalkPlan p = plan_walk({batch, phase, a.n_cdf, n_inst, n_pix, det.flags, total_photons, path_photons,
+                                  rn.block_size, rn.grid_blocks, rn.chunk, tau_z, cus, (uint64_t)a.copy_mask + 1, t.workspace_bytes});
     const bool use_log = p.use_log;
     const int block = p.block, grid = p.grid;
     const size_t lds = p.lds;
@@ -1790,7 +1791,7 @@ int launch_walk(WalkArgs &a, const mc_detector_t &det, const mc_run_t &rn, const
 int prepare_batch(const char *fn, const mc_batch_item_t *items, uint32_t n_items, int32_t n_cdf,
                   const mc_source_t *source, const mc_geometry_t *geometry, const mc_detector_t *detector,
                   const mc_run_t *run, const mc_tally_t *tally, double photon_scale, WalkArgs &a,
-                  std::vector<BatchInst> &sched, uint64_t &total)
+                  std::vector<BatchInst> &sched, uint64_t &total, uint64_t &full)
 {
     if (!items || !source || !geometry || !detector || !run || !tally) return fail(MC_EINVAL, "%s: null argument", fn);
     if (n_items < 1 || n_items > MC_MAX_BATCH) return fail(MC_EINVAL, "%s: n_items must be in 1..%d", fn, MC_MAX_BATCH);
@@ -1812,7 +1813,7 @@ int prepare_batch(const char *fn, const mc_batch_item_t *items, uint32_t n_items
         return fail(MC_EINVAL, "%s: workspace needs %llu bytes, 8-byte aligned", fn,
                     (unsigned long long)(batch_workspace_words(det, n_items) * 8));
     sched.clear();
-    total = 0;
+    total = full = 0;
     std::vector<double> cost;
     for (uint32_t i = 0; i < n_items; ++i) {
         const mc_batch_item_t &it = items[i];
@@ -1821,6 +1822,7 @@ int prepare_batch(const char *fn, const mc_batch_item_t *items, uint32_t n_items
             return fail(MC_EINVAL, "%s: item %u: albedo must be in [0, 1]", fn, i);
         if (!it.inv_cdf) return fail(MC_EINVAL, "%s: item %u: inv_cdf is required", fn, i);
         uint64_t n = it.n_photons;
+        full += n;
         if (photon_scale < 1.0 && n > 0) n = std::max<uint64_t>(1, (uint64_t)std::llround((double)n * photon_scale));
         if (int rc = check_overflow(fn, n, det, rn)) return rc;
         BatchInst b{};
@@ -1945,7 +1947,7 @@ int simulate(const char *fn, const mc_medium_t *medium, const mc_source_t *sourc
     a.side_w2l = (det.flags & MC_MOMENTS_PIXEL2) ? t.side_w2l : nullptr;
     a.rec_rows = (det.flags & MC_RECORD) ? t.rec_rows : 0;
     a.record_stride = rn.record_stride >= 1 ? rn.record_stride : 1;
-    return launch_walk(a, det, rn, t, m.phase, 1, rn.n_photons, nullptr, (hipStream_t)stream);
+    return launch_walk(a, det, rn, t, m.phase, 1, rn.n_photons, rn.n_photons, nullptr, (hipStream_t)stream);
 }
 
 // Address of this device's copy of `scratch`, looked up once per device
@@ -2061,11 +2063,11 @@ extern "C" int mc_simulate_batch(const mc_batch_item_t *items, uint32_t n_items,
     clear_error();
     WalkArgs a{};
     std::vector<BatchInst> sched;
-    uint64_t total = 0;
+    uint64_t total = 0, full = 0;
     if (int rc = prepare_batch("mc_simulate_batch", items, n_items, n_cdf, source, geometry, detector, run, tally,
-                               1.0, a, sched, total))
+                               1.0, a, sched, total, full))
         return rc;
-    return launch_walk(a, *detector, *run, *tally, MC_PHASE_MIE, n_items, total, &sched, (hipStream_t)stream);
+    return launch_walk(a, *detector, *run, *tally, MC_PHASE_MIE, n_items, total, full, &sched, (hipStream_t)stream);
 }
 
 extern "C" int mc_autotune_batch(const mc_batch_item_t *items, uint32_t n_items, int32_t n_cdf,
@@ -2081,9 +2083,9 @@ extern "C" int mc_autotune_batch(const mc_batch_item_t *items, uint32_t n_items,
         return fail(MC_EINVAL, "mc_autotune_batch: sample_fraction must be in (0, 1]");
     WalkArgs a0{};
     std::vector<BatchInst> sched;
-    uint64_t total = 0;
+    uint64_t total = 0, full = 0;
     if (int rc = prepare_batch("mc_autotune_batch", items, n_items, n_cdf, source, geometry, detector, run, tally,
-                               sample_fraction, a0, sched, total))
+                               sample_fraction, a0, sched, total, full))
         return rc;
     static const int32_t blocks[3] = {256, 512, 1024};
     static const uint32_t chunks[5] = {256, 512, 1024, 2048, 4096};
@@ -2105,7 +2107,7 @@ extern "C" int mc_autotune_batch(const mc_batch_item_t *items, uint32_t n_items,
             for (int rep = 0; rep < 2 && rc == MC_OK; ++rep) {
                 WalkArgs a = a0;
                 if (rep == 1 && hipEventRecord(e0, st) != hipSuccess) rc = fail(MC_EDEVICE, "hipEventRecord failed");
-                if (rc == MC_OK) rc = launch_walk(a, *detector, rn, *tally, MC_PHASE_MIE, n_items, total, &sched, st);
+                if (rc == MC_OK) rc = launch_walk(a, *detector, rn, *tally, MC_PHASE_MIE, n_items, total, full, &sched, st);
                 if (rc == MC_OK && rep == 1) {
                     if (hipEventRecord(e1, st) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
                         hipEventElapsedTime(&ms, e0, e1) != hipSuccess)

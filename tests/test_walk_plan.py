@@ -15,7 +15,7 @@ CU_LDS, GRANULE = 160 * 1024, 1280     # LDS is handed out in granules
 
 class Request(C.Structure):
     _fields_ = [("batch", C.c_bool), ("phase", C.c_int), ("n_cdf", C.c_int), ("n_inst", C.c_uint32), ("n_pix", C.c_uint64),
-                ("flags", C.c_uint32), ("photons", C.c_uint64), ("block_size", C.c_int), ("grid_blocks", C.c_int),
+                ("flags", C.c_uint32), ("photons", C.c_uint64), ("path_photons", C.c_uint64), ("block_size", C.c_int), ("grid_blocks", C.c_int),
                 ("chunk", C.c_uint32), ("tau_z", C.c_double), ("cus", C.c_int), ("max_copies", C.c_uint64),
                 ("ws_bytes", C.c_uint64)]
 
@@ -55,7 +55,7 @@ def plan(lib, photons, shape=(512, 512, 512, 512), *, media=0, flags=0, n_cdf=16
     else:
         ws = K.mc_workspace_bytes_batch(det, media) if media else K.mc_workspace_bytes(det)
     q = dict(batch=bool(media), phase=K.MC_PHASE_MIE, n_cdf=n_cdf, n_inst=n, n_pix=shape[0] * shape[1] + shape[2] * shape[3],
-             flags=flags, photons=photons, tau_z=-1.0 if media else tau, cus=256, max_copies=8, ws_bytes=ws)
+             flags=flags, photons=photons, path_photons=photons, tau_z=-1.0 if media else tau, cus=256, max_copies=8, ws_bytes=ws)
     q.update(kw)
     p = Plan()
     lib.walk_plan(C.byref(Request(**q)), C.byref(p))
@@ -129,3 +129,19 @@ def test_a_log_beside_the_copies_where_it_pays(lib, sigma):
                     assert p.grid == 256 * (2 if two else 1)
                 seen.add((p.use_log, least))
     assert seen == {(True, 0.6), (False, 0.6)} | (set() if sigma else {(True, 0.9), (False, 0.9)})
+
+
+@pytest.mark.parametrize("flags", [0, K.MC_EXIT_LOG, K.MC_SIGMA, K.MC_EXIT_LOG | K.MC_SIGMA], ids=["", "log", "sigma", "log-sigma"])
+def test_a_sample_takes_the_path_of_its_launch(lib, flags):
+    """The tuner's sample, a sixteenth of the photons: the log, the copies and their
+    order are those of the launch it is timed for, at every block size it tries."""
+    for media in (2, 32, 256, 500):
+        for px in (16, 64, 150, 256):
+            for each in (2_000, 20_000, 200_000, 2_000_000):
+                n = media * each
+                for block in K.AUTOTUNE_BLOCKS:
+                    kw = dict(media=media, flags=flags, n_cdf=0, block_size=block, log_photons=n)
+                    whole = plan(lib, n, (px,) * 4, **kw)
+                    sample = plan(lib, n // 16, (px,) * 4, path_photons=n, **kw)
+                    assert sample.path == whole.path and (sample.grid, sample.lds) == (whole.grid, whole.lds)
+                    assert (sample.log_cap, sample.rbits) == (whole.log_cap, whole.rbits)
