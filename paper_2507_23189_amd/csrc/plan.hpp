@@ -254,7 +254,8 @@ inline WalkPlan plan_walk(const WalkRequest &q)
     // log: the block's append counters and no cache) ----
     // Path-moment kernels are built for six waves per SIMD: 768-lane blocks,
     // two per CU.
-    const int block = p.block = q.block_size ? q.block_size : ((q.flags & MC_MOMENTS) ? 768 : 1024);
+    const int own_block = (q.flags & MC_MOMENTS) ? 768 : 1024;
+    const int block = p.block = q.block_size ? q.block_size : own_block;
     const size_t table_bytes = batch ? 0 : (size_t)((q.n_cdf + 3) & ~3) * sizeof(float);
     const size_t scal_bytes = (batch ? (size_t)q.n_inst * kBatchScal : MC_N_SCALARS) * sizeof(double);
     const size_t queue_arrays = batch ? 4 : 3;
@@ -271,7 +272,7 @@ inline WalkPlan plan_walk(const WalkRequest &q)
     // 209 / 167; 1e6 tau = 1 73.9 / 76.0, tau = 4 88.7 / 83.9, tau = 16 219 / 194; 2e6
     // tau = 4 117.5 / 118.5; 1e4 tau = 16 94.7 / 97.9.  (All with the library's block.)
     const uint64_t lanes_one = (uint64_t)q.cus * block;
-    const bool few = !batch && q.block_size == 0 && q.photons <= lanes_one * (tau_z > 6.0 ? 5 : (tau_z > 3.0 ? 4 : 3)) &&
+    const bool few = !batch && block == own_block && q.photons <= lanes_one * (tau_z > 6.0 ? 5 : (tau_z > 3.0 ? 4 : 3)) &&
                      !(tau_z > 12.0 && q.photons < lanes_one / 2);
     // Slots of the tally cache at most (log2), where the LDS holds them.  At the end
     // every block adds its slots to the images, many of them to the same words, so
@@ -283,7 +284,7 @@ inline WalkPlan plan_walk(const WalkRequest &q)
     // log's overflow do not tell 10 from 12, and smaller blocks would fit a CU in
     // smaller numbers.
     auto slots_for = [&](bool log) -> int {
-        if (log || batch || q.block_size != 0) return 10;
+        if (log || batch || block != own_block) return 10;
         if (total_photons <= 1u << 20) return (q.flags & MC_SIGMA) ? 10 : 8;
         if (total_photons < 1u << 23) return 10;
         if (total_photons < 1u << 24) return n_total > 1u << 16 ? 11 : 10;

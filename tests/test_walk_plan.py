@@ -145,3 +145,15 @@ def test_a_sample_takes_the_path_of_its_launch(lib, flags):
                     sample = plan(lib, n // 16, (px,) * 4, path_photons=n, **kw)
                     assert sample.path == whole.path and (sample.grid, sample.lds) == (whole.grid, whole.lds)
                     assert (sample.log_cap, sample.rbits) == (whole.log_cap, whole.rbits)
+
+
+@pytest.mark.parametrize("moments", [False, True], ids=["", "moments"])
+def test_the_library_block_set_by_the_caller(lib, moments):
+    """A caller who sets the block that the library takes gets the library's plan."""
+    for log in (0, K.MC_EXIT_LOG):
+        for n in (10_000, 300_000, 1_000_000, 3_000_000, 10_000_000, 50_000_000, 200_000_000):
+            for px in (32, 128, 200, 512):
+                for tau in (0.5, 4.0, 16.0):
+                    kw = dict(flags=log | (K.MC_MOMENTS if moments else 0), tau=tau)
+                    a, b = (plan(lib, n, (px,) * 4, block_size=block, **kw) for block in (0, 768 if moments else 1024))
+                    assert bytes(a) == bytes(b), (n, px, tau)
