@@ -276,20 +276,25 @@ inline WalkPlan plan_walk(const WalkRequest &q)
                      !(tau_z > 12.0 && q.photons < lanes_one / 2);
     // Slots of the tally cache at most (log2), where the LDS holds them.  At the end
     // every block adds its slots to the images, many of them to the same words, so
-    // few photons, or few pixels, pay for more slots than they use (us at 8, 10 and
-    // 12, HG: 1e6 photons, tau = 4, 512 x 512 84.7 / 87.0 / 101.3, tau = 1 70.0 / 80.5 /
-    // 83.5; 1e7, tau = 1, 64 x 64 201 / 181 / 209, 256 x 256 285 / 277 / 250; 1e8, 256 x
-    // 256 2406 / 2038 / 1590, 512 x 512 2429 / 2264 / 2057).  Squared weights double
-    // what a slot saves.  Batches (whose first media fill the slots) and the exit
-    // log's overflow do not tell 10 from 12, and smaller blocks would fit a CU in
-    // smaller numbers.
+    // few photons, or few pixels, pay for more slots than they use, and squared weights
+    // double what a slot saves.  Us at 8 / 10 / 12, HG: 1e6 photons, tau = 4, 512 x 512
+    // 84.7 / 87.0 / 101.3, tau = 1 70.0 / 80.5 / 83.5.  At 10 / 11 / 12, tau = 1, HG (4096 entries,
+    // tau = 4, in brackets), by pixels of both images: 9e6 photons, 16200 177 / 200 / 219 (281 /
+    // 294 / 322), 65522 225 / 216 / 228 (297 / 293 / 324), 131072 255 / 243 / 233 (325 / 324 / 330; tau = 8,
+    // HG, 11 and 12 436 / 480); 2e7, 8192 286 / 309 / 336 (523 / 534 / 557), 16200 367 / 325 / 358 (571 /
+    // 543 / 569), 131072 469 / 435 / 405 (641 / 615 / 581; tau = 8 897 / 925),
+    // 524288 515 / 503 / 495 (681 / 684 / 684); 5e7, 32768 795 / 653 / 664 (1220 /
+    // 1200 / 1221), 65522 985 / 881 / 703 (1429 / 1288 / 1230), 524288 1160 / 1118 / 1070 (1545 / 1535 / 1503);
+    // 2e8, 8192 2265 / 2276 / 2300 (4529 / 4531 / 4554), 16200 3150 / 2293 / 2309 (5255 / 4535 / 4560), 65522
+    // 3798 / 3255 / 2547 (5566 / 5062 / 4568).  Batches (whose first media fill the slots)
+    // and the exit log's overflow do not tell 10 from 12, and smaller blocks would fit
+    // a CU in smaller numbers.
     auto slots_for = [&](bool log) -> int {
         if (log || batch || block != own_block) return 10;
         if (total_photons <= 1u << 20) return (q.flags & MC_SIGMA) ? 10 : 8;
         if (total_photons < 1u << 23) return 10;
         if (total_photons < 1u << 24) return n_total > 1u << 16 ? 11 : 10;
-        const uint64_t few_pixels = total_photons < 1u << 26 ? 1u << 18 : 1u << 16;
-        return n_total <= 1u << 14 ? 10 : (n_total <= few_pixels ? 11 : 12);
+        return n_total <= 1u << 13 ? 10 : (n_total <= 1u << (total_photons < 1u << 25 ? 18 : 15) ? 11 : 12);
     };
     auto launch_shape = [&](bool log) {
         const size_t lds_fixed = table_bytes + scal_bytes + (size_t)(block / 64) * queue_arrays * kQueue * sizeof(float) +

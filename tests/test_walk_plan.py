@@ -157,3 +157,15 @@ def test_the_library_block_set_by_the_caller(lib, moments):
                     kw = dict(flags=log | (K.MC_MOMENTS if moments else 0), tau=tau)
                     a, b = (plan(lib, n, (px,) * 4, block_size=block, **kw) for block in (0, 768 if moments else 1024))
                     assert bytes(a) == bytes(b), (n, px, tau)
+
+
+@pytest.mark.parametrize("photons, pixels, bits", [
+    (1 << 20, 64, 8), ((1 << 20) + 1, 1024, 10), ((1 << 23) - 1, 1 << 18, 10),
+    (1 << 23, 1 << 16, 10), (1 << 23, (1 << 16) + 2, 11), ((1 << 24) - 1, 1 << 16, 10), ((1 << 24) - 1, 1 << 19, 11),
+    (1 << 24, 1 << 13, 10), (1 << 24, (1 << 13) + 2, 11), ((1 << 25) - 1, 1 << 18, 11), ((1 << 25) - 1, (1 << 18) + 2, 12), (1 << 25, 1 << 13, 10),
+    (1 << 25, 1 << 15, 11), (1 << 25, (1 << 15) + 2, 12), (1 << 30, 1 << 13, 10)], ids=str)
+def test_slots_by_photons_and_pixels(lib, photons, pixels, bits):
+    shape = (pixels // 2, 1, 1, pixels - pixels // 2)
+    p = plan(lib, photons, shape, n_cdf=0)
+    assert not p.use_log and p.cache_bits == bits
+    assert plan(lib, photons, shape, n_cdf=16384).cache_bits == min(bits, 8)    # what the LDS beside the table holds
