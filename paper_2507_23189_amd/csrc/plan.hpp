@@ -179,6 +179,12 @@ inline size_t blocks_on_cu(size_t lds, int block)
     return std::max<size_t>(1, std::min<size_t>(kCuLds / kLdsGranule / granules, 32 / (block / 64)));
 }
 
+// The countdown to a wave's next look at roulette and the step cap, at a round: 0
+// when a photon took a step there (the look is due), else never below 0, so that
+// the steps between two rounds, at most 2^24, cannot carry it past the least
+// integer, where it would turn into a long stretch without looks.
+constexpr int calm_at_round(int calm, bool stepped) { return stepped || calm < 0 ? 0 : calm; }
+
 // What a walk's plan depends on.
 struct WalkRequest {
     bool batch;

@@ -555,6 +555,7 @@ void walk_kernel(WalkArgs a)
     float out = kOutside;
     // Steps the wave may still take before it has to look again whether one of
     // its photons could meet roulette or the step cap (0 or less: some could now).
+    // It counts down in every step and starts anew at the rounds (calm_at_round).
     int calm = 0;
     uint64_t id = 0;
     PhotonKey pk{};
@@ -686,12 +687,15 @@ void walk_kernel(WalkArgs a)
     // Either way it runs when at most round_at lanes walk.
     uint32_t round_at = 64u;
 
-    // The loop begins 20 bytes past a multiple of 32, whatever comes before it:
-    // instructions are fetched in aligned lines, and where the loop lies in them moves
-    // times by 2 % and the end of some launches by 5 % (0 / 8 / 16 / 20 / 28 bytes past: 1e5
-    // photons 42.8 / 42.3 / 42.0 / 41.9 / 42.6 us, 2e7 at tau = 16 1.484 / 1.484 / 1.568 / 1.49 /
-    // 1.57 ms, 1e8 at tau = 1 1.187 / 1.198 / 1.188 / 1.186 / 1.190).
-    asm volatile(".p2align 5\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0");
+    // The loop begins 12 (with the log) or 20 bytes past a multiple of 32, whatever
+    // comes before it: instructions are fetched in aligned lines, and where the loop
+    // lies in them moves times by 2 % and the end of some launches by 5 % (0 / 8 / 12 /
+    // 16 / 20 / 24 bytes past: 1e5 photons, without the log, 42.9 / 42.0 / 41.9 / 41.8 / 41.6 /
+    // 41.7 us; tau = 16 with it, nine counts from 3e6 to 3.3e7, geometric mean relative to
+    // the first 1 / 1.003 / 1.004 / 1.017 / 1.020 / 1.008; 1e8 at tau = 1 1 / 0.992 / 0.990 / 0.993 /
+    // 0.992 / 0.992).
+    if (LOG) asm volatile(".p2align 5\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0");
+    else asm volatile(".p2align 5\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0");
     for (;;) {
         if ((uint32_t)__popcll(alive) <= round_at) {
             const ArgsPtr ra = reload_args();
@@ -741,7 +745,7 @@ void walk_kernel(WalkArgs a)
                 }
             }
             // Rare: the step stayed inside after all and interacts.
-            calm = __builtin_amdgcn_ballot_w64(early) ? 0 : calm;
+            calm = calm_at_round(calm, __builtin_amdgcn_ballot_w64(early) != 0ull);
             if (early) {
                 const Block4 r = draw(step - 1u);
                 interact(r.r1, r.r2);

@@ -169,3 +169,16 @@ def test_slots_by_photons_and_pixels(lib, photons, pixels, bits):
     p = plan(lib, photons, shape, n_cdf=0)
     assert not p.use_log and p.cache_bits == bits
     assert plan(lib, photons, shape, n_cdf=16384).cache_bits == min(bits, 8)    # what the LDS beside the table holds
+
+
+def test_the_countdown_to_the_next_look_never_wraps(lib):
+    """A wave whose photons may always meet roulette, for as many rounds as a walk of
+    2^31 photons by one wave could have."""
+    most = 1 << 24          # steps between two rounds: a photon takes no more
+    calm = 0
+    for _ in range(1000):
+        calm -= most
+        assert calm >= -(1 << 31)
+        calm = lib.calm(calm, 0)
+        assert calm == 0    # (no look is skipped for it)
+    assert lib.calm(17, 0) == 17 and lib.calm(17, 1) == 0 and lib.calm(-3, 1) == 0
