@@ -127,6 +127,15 @@ struct MieArgs {
 constexpr int kScanFrom = 256;
 constexpr int kChunk = 256, kAhead = 16;   // kAhead: entries before the first that reading ahead may touch
 
+// Orders LDS accesses of a wave's lanes: those before it come before those after
+// it, for every lane (the hardware keeps a wave's accesses in order; this keeps the
+// compiler from moving them past each other).
+__device__ __forceinline__ void wave_lds_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // A vector (P, Q) of the downward recurrence, its step from n to n - 1 with
 // k = n/(mx), and its scaling by a power of two (see mie_series_block).  With a
 // real index the imaginary parts are zero and left out.
@@ -291,6 +300,7 @@ __device__ __forceinline__ void downward(cplx inv_mx, int N, int n_start, double
             if (REAL) s_kr[kAhead + i] = k.re;
             else s_k[kAhead + i] = double2{k.re, k.im};
         }
+        wave_lds_order();
         if (lane == 0) {
             auto factor = [&](int n) -> cplx {
                 if (REAL) return cplx{s_kr[kAhead + n - bot], 0.0};
@@ -341,6 +351,7 @@ __device__ __forceinline__ void downward(cplx inv_mx, int N, int n_start, double
                 else group(b, false);
             }
         }
+        wave_lds_order();
         top = bot - 1;
     }
 }
@@ -356,6 +367,7 @@ __device__ __forceinline__ void upward(double x, int N, double *s_f, double2 *s_
     for (int n0 = 1; n0 <= N; n0 += kChunk) {
         const int steps = min(kChunk, N + 1 - n0);
         for (int i = lane; i < steps; i += 64) s_f[i] = (2.0 * (n0 + i) - 1.0) / x;
+        wave_lds_order();
         if (lane == 0) {
             auto up = [&](int i, double f) {
                 const double psi_n = f * psi - psi_prev;
@@ -387,6 +399,7 @@ __device__ __forceinline__ void upward(double x, int N, double *s_f, double2 *s_
             }
             for (; i < steps; ++i) up(i, s_f[i]);
         }
+        wave_lds_order();
     }
 }
 
