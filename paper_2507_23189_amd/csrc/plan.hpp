@@ -256,8 +256,8 @@ inline WalkPlan plan_walk(const WalkRequest &q)
 
     // ---- launch shape: 1024-lane blocks (768 with path moments), two per CU, each with
     // the table (single medium), the scalar words, the per-wave exit queues and
-    // as large a tally cache as fits in half the CU's 160 KB LDS (with the exit
-    // log: the block's append counters and no cache) ----
+    // as large a tally cache as fits in half the CU's 160 KB LDS, or, with the exit
+    // log, the block's append counters and a cache for what overflows it ----
     // Path-moment kernels are built for six waves per SIMD: 768-lane blocks,
     // two per CU.
     const int own_block = (q.flags & MC_MOMENTS) ? 768 : 1024;

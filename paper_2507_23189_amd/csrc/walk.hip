@@ -46,9 +46,9 @@
 // arithmetic runs with full lanes instead of on the few lanes that exit in
 // any one step.  A flush then either
 //   * appends them to the exit log (MC_EXIT_LOG, or room for it among the image
-//     copies): each block owns a region
-//     of every key range and appends at the position an LDS counter of the
-//     block hands out (one LDS add and one store per exit); a second kernel
+//     copies): each block owns a region of every key range and appends at the
+//     position an LDS counter of the block hands out (one LDS add and one store
+//     per exit); a second kernel
 //     (log_bin) sums each range in an LDS histogram and writes the sums into
 //     image copies with plain loads and stores.  Exits that find their region
 //     full are added as in the other path; or
@@ -64,9 +64,9 @@
 // sums the copies in integer arithmetic and converts to the caller's images.
 // Scalar tallies use LDS atomics and lane accumulators, flushed once per
 // block; reflections are not counted but derived from the step, event and
-// exit counts when finalizing.  The kernel is specialised at compile time on the phase function,
-// the squared-weight tally, per-photon records, path moments, batching and
-// the exit log.
+// exit counts when finalizing.  The kernel is specialised at compile time on
+// the phase function, the squared-weight tally, per-photon records, path
+// moments, batching and the exit log.
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
 
@@ -114,18 +114,17 @@ struct WalkArgs {
     float pos0[3], dir0[3], w0;
     float beam_radius;        // > 0: entry points uniform on the disk of this radius around pos0
     float roulette_w, roulette_p, inv_roulette_p;
-    int phase, n_cdf;
+    int n_cdf;
     const float *inv_cdf;
     float hg_a, hg_b, hg_c, hg_d;   // 1 + g, 2g, 1 - g^2, 1 - g
     uint32_t key0, key1, instance, max_steps;
-    uint64_t n_photons, photon_offset;
+    uint64_t photon_offset;
     uint32_t chunk;           // ids a wave takes from its block's pool (batched: photons of a work unit)
     // Ids (work units) of the launch, those each block starts with, and the
     // least and the share (1 / 2^shift) of the rest a block claims at once.
     uint32_t n_ids, claim0, claim_min, claim_shift;
     uint32_t quiet_steps;     // a photon of fewer steps meets neither roulette nor the step cap in kQuietSteps more
     uint32_t refill_min;      // lanes not walking that trigger a round (1..64)
-    uint32_t flags;
     int cache_bits;           // log2 of the tally-cache slots (0: no cache)
     uint32_t n_side;          // pixels of the side image (cache key offset of the transmitted image)
     int side_nx, side_ny, trans_nx, trans_ny;
@@ -348,7 +347,8 @@ void walk_kernel(WalkArgs a)
     constexpr bool GLOBAL_TABLE = BATCH;   // batched: each medium's inverse table stays in global memory
     // LDS layout: inverse table (n_cdf floats, padded to 4; batched launches
     // read each medium's table from global memory instead), scalar words
-    // (MC_N_SCALARS, or kBatchScal per medium), tally cache (slots words of
+    // (MC_N_SCALARS, or kBatchScal per medium; two of them hold the id pool and the
+    // count of exits past the log), tally cache (slots words of
     // weight, [SIGMA] slots words of squared weight, slots uint32 keys),
     // per-wave exit queues (3 x kQueue floats, a fourth for the medium's slot),
     // with the exit log then the block's 2^log_rbits append counters.
@@ -1075,12 +1075,11 @@ __global__ __launch_bounds__(1024) void log_bin(const unsigned long long *log, c
     const uint32_t lane = threadIdx.x & 63u, waves = blockDim.x >> 6;
     constexpr uint32_t U = 4;   // entries in flight per lane
     // Copy s takes the walk's blocks s, s + n_copies, s + 2 n_copies, ...:
-    // the walk's blocks log very unequal numbers of exits (work is claimed
-    // per wave, and the older workgroup on a compute unit wins most issue
-    // cycles: at the headline the first 256 of 512 blocks log four times as
-    // many as the rest), so contiguous shares would load some copies 1.6
-    // times the mean.  Each wave takes every waves-th of them and reads its
-    // entries U x 64 at a time.
+    // the walk's blocks log very unequal numbers of exits (each claims as it goes,
+    // and the older workgroup on a compute unit wins most issue cycles: at tau = 4
+    // and 1e8 photons the first 256 of 512 blocks log 3.6 times as many as the
+    // rest), so contiguous shares would load some copies 1.56 times the mean.  Each
+    // wave takes every waves-th of them and reads its entries U x 64 at a time.
     for (uint32_t g = s + n_copies * (threadIdx.x >> 6); g < walk_blocks; g += n_copies * waves) {
         const uint64_t region = (uint64_t)b * walk_blocks + g;
         const uint32_t n = count[region];
@@ -1518,7 +1517,6 @@ void fill_common(WalkArgs &a, const mc_source_t &src, const mc_geometry_t &geo, 
     a.key0 = (uint32_t)rn.seed;
     a.key1 = (uint32_t)(rn.seed >> 32);
     a.max_steps = rn.max_steps;
-    a.flags = det.flags;
     a.side_nx = det.side_nx; a.side_ny = det.side_ny;
     a.trans_nx = det.trans_nx; a.trans_ny = det.trans_ny;
     a.pix_scale[0] = (float)(det.side_ny / geo.size_mm[1]);
@@ -1848,11 +1846,9 @@ int prepare_batch(const char *fn, const mc_batch_item_t *items, uint32_t n_items
 
     a = WalkArgs{};
     fill_common(a, *source, geo, det, rn);
-    a.phase = MC_PHASE_MIE;
     a.n_cdf = n_cdf;
     a.inv_cdf = nullptr;
     a.instance = 0;
-    a.n_photons = 0;
     a.photon_offset = 0;
     a.record_stride = 1;
     for (const BatchInst &b : sched) limit_quiet(a, b.albedo);
@@ -1866,8 +1862,8 @@ namespace mcmie {
 namespace {
 
 // The walk of mc_simulate.  With `scratch_ws` set, the caller's workspace is
-// ignored: the images are tallied in one fixed-point copy held in that device
-// array (noalloc callers) instead of in per-XCD copies in the workspace.
+// ignored: the images are tallied in as many fixed-point copies as fit that device
+// array (noalloc callers) instead of in the workspace's.
 int simulate(const char *fn, const mc_medium_t *medium, const mc_source_t *source, const mc_geometry_t *geometry,
              const mc_detector_t *detector, const mc_run_t *run, const mc_tally_t *tally, void *scratch_ws,
              void *stream)
@@ -1934,7 +1930,6 @@ int simulate(const char *fn, const mc_medium_t *medium, const mc_source_t *sourc
     fill_medium(a.neg_ln2_over_mu, a.albedo, a.absorb, coef.mu_ext, coef.albedo);
     limit_quiet(a, a.albedo);
     a.copy_mask = (uint32_t)(copies - 1);
-    a.phase = m.phase;
     a.n_cdf = m.phase == MC_PHASE_MIE ? m.n_cdf : 0;
     a.inv_cdf = m.inv_cdf;
     a.hg_a = (float)(1.0 + m.g);
@@ -1942,7 +1937,6 @@ int simulate(const char *fn, const mc_medium_t *medium, const mc_source_t *sourc
     a.hg_c = (float)(1.0 - m.g * m.g);
     a.hg_d = (float)(1.0 - m.g);
     a.instance = rn.instance;
-    a.n_photons = rn.n_photons;
     a.photon_offset = rn.photon_offset;
     a.rec_i = t.rec_i; a.rec_f = t.rec_f;
     a.side_wk = (det.flags & MC_MOMENTS) ? t.side_wk : nullptr;
