@@ -144,11 +144,13 @@ PEAK_SLOTS_PER_S = 256 * 4 * 32 * 2.4e9
 # from rocprofv3 --pmc FETCH_SIZE and WRITE_SIZE (KiB per dispatch) scaled by
 # what the same counters read for a 256 MiB device copy (FETCH_SIZE x 2.0,
 # WRITE_SIZE x 1.0); valid only for the tally path and kernel code it was
-# measured on (profiles/walk_tau4_counters.md): the digest covers the walk
-# sources without comments and whitespace, so a comment edit keeps it.
-TRAFFIC = {"tally": "log", "sources_sha256": "ea219363d6c2de453503e7c99e428da869ff973c2837ccc36d3d07701f50ef49",
-           "fetch_kib": 386.2, "write_kib": 554672.7, "fetch_factor": 2.0, "write_factor": 1.0}
-WALK_SOURCES = ("paper_2507_23189_amd/csrc/walk.hip", "paper_2507_23189_amd/csrc/philox.hpp")
+# measured on (profiles/walk_tau4_counters.md): the digest covers the walk's
+# sources and launch plan without comments and whitespace, so a comment edit
+# keeps it.
+TRAFFIC = {"tally": "log", "sources_sha256": "d0355aa7717cc133b9a8d0cc7bf1d7dd34b4745701810cab55c157e206b6fca4",
+           "fetch_kib": 388.4, "write_kib": 554329.1, "fetch_factor": 2.0, "write_factor": 1.0}
+WALK_SOURCES = ("paper_2507_23189_amd/csrc/walk.hip", "paper_2507_23189_amd/csrc/plan.hpp",
+                "paper_2507_23189_amd/csrc/philox.hpp")
 
 
 def code_digest(text: str) -> str:

@@ -16,8 +16,10 @@
  *          alive until the stream has drained.
  *   Ownership: the caller allocates every buffer, including the walk's
  *          workspace (size from mc_workspace_bytes).  The library keeps no
- *          pointer after a call returns.  Its only device memory of its own
- *          is a small per-device scratch block for the table build.
+ *          pointer after a call returns.  Memory of its own: per device a
+ *          small scratch block for the table build and the array of
+ *          mc_simulate_noalloc, and 8 KB of pinned host memory through which
+ *          calls that wait get their results; all until the process ends.
  *   Tallies: weights are accumulated in 64-bit fixed point (weight * 2^32,
  *          rounded to nearest), so every sum is exact and independent of the
  *          order in which photons finish: results are bit-identical for any

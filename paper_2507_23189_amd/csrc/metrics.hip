@@ -21,9 +21,9 @@
 // At 512 x 512 with a third image the call reads 6.3 MB, 1.3 us at the copy
 // rate; it is bound by latency, each kernel being a few dependent trips to
 // memory.  One lane that walked over the blocks' sums and the annuli took 200
-// of the 263 us the call took; now the kernels take 4.6 and 19.4 us (about 5 of
-// them the annulus adds in LDS, 6 the last block's part) and the call 57, the
-// rest of which is launches and the wait (48 since the results need no copy).
+// of the 263 us the call took; now the kernels take 4.7 and 18.6 us (about 5 of
+// them the annulus adds in LDS, 6 the last block's part) and the call 48, the
+// rest of which is launches and the wait.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
